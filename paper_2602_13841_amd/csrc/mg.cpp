@@ -235,13 +235,24 @@ void mg_allocate(stmg_ctx *ctx)
         const int n = (int)Lc.N, m = n + (mg.border ? Lc.nt : 0);
         mg.cX.alloc((size_t)n * n * 8);
         mg.cY.alloc((size_t)n * n * 8);
-        mg.cA.alloc((size_t)m * m * 8);
-        mg.cpiv.alloc((size_t)m * 4);
-        mg.cinfo.alloc(4);
-        mg.cr64.alloc((size_t)m * 8);
-        mg.cx64.alloc((size_t)m * 8);
         mg.cn = n;
         mg.cm = m;
+        mg.inverse = m <= DINV_MAX_M;
+        if (mg.inverse) {
+            const size_t ld = (size_t)dinv_ld(m);
+            mg.cA.alloc((size_t)m * ld * 8);
+            mg.cW.alloc(ld * 32 * 8);
+            mg.cB.alloc(32 * ld * 8);
+            mg.cdinv.alloc(32 * 32 * 8);
+            mg.crow.alloc((size_t)m * 4);
+            mg.cperm.alloc((size_t)m * 4);
+        } else {
+            mg.cA.alloc((size_t)m * m * 8);
+            mg.cpiv.alloc((size_t)m * 4);
+            mg.cinfo.alloc(4);
+            mg.cr64.alloc((size_t)m * 8);
+            mg.cx64.alloc((size_t)m * 8);
+        }
     }
     const long long N = mg.lv[0].L->N;
     ctx->kry.ensure(N, std::max(1, o.fgmres_maxit));
@@ -266,7 +277,8 @@ void mg_set_state(stmg_ctx *ctx, const double *u)
     if (mg.prec == STMG_F32)
         for (int l = 0; l < nl; ++l)
             STMG_HIP((vec_cast<double, float>(mg.lv[l].L->N, mg.lv[l].st64.as<double>(), mg.lv[l].st32.as<float>(), s)));
-    // coarsest level: dense Jacobian from J e_i, bordered, LU in FP64
+    // coarsest level: dense Jacobian from J e_i, bordered, inverted in FP64
+    // (beyond DINV_MAX_M unknowns: LU)
     MgLevel &C = mg.lv[nl - 1];
     Level &Lc = *C.L;
     const int n = (int)Lc.N, nb = mg.border ? Lc.nt : 0, m = n + nb;
@@ -275,13 +287,16 @@ void mg_set_state(stmg_ctx *ctx, const double *u)
         TimerScope ts(&ctx->timers, "coarse_factor", s);
         STMG_HIP(launch_identity(mg.cX.as<double>(), n, s));
         Lc.apply<double>(Mode::Jac, C.st64.as<double>(), mg.cX.as<double>(), mg.cY.as<double>(), nullptr, nullptr, n, s);
-        STMG_HIP(launch_coarse_matrix(mg.cY.as<double>(), n, nb, Lc.nt, (long long)Lc.nt * Lc.Nv1, Lc.Np1, Lc.npm,
-                                      Lc.ncell, mg.cA.as<double>(), s));
-        STMG_HIP(hipMemsetAsync(mg.cinfo.p, 0, 4, s));
-        // one workgroup suffices for small systems; larger ones (e.g. 3^3-cell
-        // coarse meshes, m = 2274) use the device-wide blocked factorization
-        if (m > 256) STMG_HIP(launch_lu_dense(mg.cA.as<double>(), mg.cpiv.as<int>(), m, mg.cinfo.as<int>(), s));
-        else STMG_HIP(launch_lu<double>(mg.cA.as<double>(), mg.cpiv.as<int>(), m, 1, mg.cinfo.as<int>(), mg.max_lds, s));
+        if (mg.inverse) {
+            const DenseInverse w = mg.dense_inverse();
+            STMG_HIP(launch_inv_matrix(mg.cY.as<double>(), n, nb, (long long)Lc.nt * Lc.Nv1, Lc.Np1, Lc.npm, w.A, w.ld, s));
+            STMG_HIP(launch_dense_inverse(w, s));
+        } else {
+            STMG_HIP(launch_coarse_matrix(mg.cY.as<double>(), n, nb, Lc.nt, (long long)Lc.nt * Lc.Nv1, Lc.Np1, Lc.npm,
+                                          Lc.ncell, mg.cA.as<double>(), s));
+            STMG_HIP(hipMemsetAsync(mg.cinfo.p, 0, 4, s));
+            STMG_HIP(launch_lu_dense(mg.cA.as<double>(), mg.cpiv.as<int>(), m, mg.cinfo.as<int>(), s));
+        }
     }
     mg.state_set = true;
 }
@@ -581,6 +596,10 @@ template <typename T> void mg_vcycle(stmg_ctx *ctx, int l, const T *r, T *d)
     Level &L = *M.L;
     if (l == nl - 1) {
         TimerScope ts(&ctx->timers, "coarse_solve", s);
+        if (mg.inverse) {
+            STMG_HIP(launch_inverse_apply<T>(mg.dense_inverse(), r, d, mg.cn, s));
+            return;
+        }
         STMG_HIP((vec_cast<T, double>(L.N, r, mg.cr64.as<double>(), s)));
         STMG_HIP(launch_dense_solve(mg.cA.as<double>(), mg.cpiv.as<int>(), mg.cm, mg.cr64.as<double>(),
                                     mg.cx64.as<double>(), mg.cn, s));

@@ -74,6 +74,13 @@ struct Mg {
     // coarsest level direct solve (FP64)
     DevBuf cX, cY, cA, cpiv, cinfo, cr64, cx64;
     int cn = 0, cm = 0;
+    DevBuf cW, cB, cdinv, crow, cperm;   // inverse of the coarse matrix (up to DINV_MAX_M unknowns)
+    bool inverse = false;
+    DenseInverse dense_inverse() const
+    {
+        return DenseInverse{cA.as<double>(), cm, dinv_ld(cm), cW.as<double>(), cB.as<double>(), cdinv.as<double>(),
+                            crow.as<int>(), cperm.as<int>()};
+    }
     bool border = false;
     bool state_set = false;
     size_t max_lds = 65536;

@@ -1,0 +1,69 @@
+"""The coarsest-level direct solve (dense inverse, one application per V-cycle)
+against the oracle's LU of the same bordered Jacobian (GPU).
+
+A context with one level has the direct solve as its whole V-cycle.  Sizes
+straddle the panel shapes of the inversion (candidate rows 256, 512, 1024,
+1536, 3072 and remainders of 32, 16 and 8 columns).  Tolerance: the operators
+agree to about 1e-13 (test_gpu_operators) and both factorizations are
+backward stable to less than that, so the solutions agree to 1e-13 times the
+condition number; FP32 vectors add their own rounding."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle  # noqa: E402
+import scipy.linalg as sla  # noqa: E402
+from oracle import solver as S  # noqa: E402
+from paper_2602_13841_amd import inputs as I  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+CASES = [  # dim, n, k, mask
+    (2, (1, 2), 0, None),       # 37
+    (2, (2, 2), 1, None),       # 126
+    (2, (4, 4), 0, None),       # 211
+    (2, (5, 4), 0, 0b1101),     # 258
+    (2, (3, 3), 3, None),       # 504
+    (2, (5, 5), 2, None),       # 954
+    (3, (2, 2, 2), 1, None),    # 816
+    (2, (7, 7), 1, None),       # 1196
+    (2, (12, 12), 0, 0b1101),   # 1682
+    (2, (17, 16), 0, None),     # 3127
+]
+
+
+@pytest.mark.parametrize("d,n,k,mask", CASES, ids=[f"{c[0]}d_{'x'.join(map(str, c[1]))}_k{c[2]}" for c in CASES])
+def test_coarse_inverse(d, n, k, mask):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2602_13841_amd import stmg
+    prob = oracle.Problem(dim=d, n=n, r=1, k=k, nu=0.05, tau=0.1, dirichlet_mask=mask,
+                          vertices=I.perturbed_vertices(d, n, 0.2, 31))
+    H = S.Hierarchy(prob, max_levels=1)
+    s = H.levels[0].slab
+    A = s.jacobian(I.uniform(s.N, 32)).toarray()
+    N = len(A)
+    if H.pure_dirichlet:
+        E = S.constant_pressure_vectors(s)
+        A = np.block([[A, E], [E.T, np.zeros((E.shape[1],) * 2)]])
+    tol = 1e-13 * np.linalg.cond(A, 1)
+    lu = sla.lu_factor(A)
+    for prec, dt, extra in ((stmg.STMG_F64, torch.float64, 0.0), (stmg.STMG_F32, torch.float32, 1e-6)):
+        ctx = stmg.Context(d, n, 1, k, 0.05, 0.1, vertices=prob.vertices, dirichlet_faces=prob.dirichlet_mask,
+                           prec_mg=prec, max_levels=1, fgmres_maxit=1)
+        assert ctx.num_levels() == 1 and ctx.N == N
+        for seed in (33, 34):   # a new state each time
+            U = I.uniform(N, seed)
+            if seed == 34:
+                A[:N, :N] = s.jacobian(U).toarray()
+                lu = sla.lu_factor(A)
+            else:
+                U = I.uniform(N, 32)
+            r = torch.tensor(I.uniform(N, seed + 10), dtype=dt, device="cuda")
+            ctx.smoother_rebuild(torch.tensor(U, device="cuda"))
+            x = ctx.vcycle(r).double().cpu().numpy()
+            ref = sla.lu_solve(lu, np.concatenate([r.double().cpu().numpy(), np.zeros(len(A) - N)]))[:N]
+            assert np.linalg.norm(x - ref) <= (tol + extra) * np.linalg.norm(ref)
+        A[:N, :N] = s.jacobian(I.uniform(N, 32)).toarray()
+        lu = sla.lu_factor(A)
