@@ -17,7 +17,7 @@
 // Against the LU it replaced (panel in global memory, 25 us per column at
 // m = 2274; one workgroup per substitution): the factorization was bound by
 // the latency of its panel columns, the substitution by one CU's.
-#include "vanka.h"
+#include "coarse.h"
 
 #include "stmg_internal.h"
 
@@ -50,38 +50,41 @@ __device__ __forceinline__ double wave_max(double v)
     v = step(v, [](int x) { return __builtin_amdgcn_update_dpp(x, x, 0x112, 0xf, 0xf, false); });   // row_shr 2
     v = step(v, [](int x) { return __builtin_amdgcn_update_dpp(x, x, 0x114, 0xf, 0xf, false); });   // row_shr 4
     v = step(v, [](int x) { return __builtin_amdgcn_update_dpp(x, x, 0x118, 0xf, 0xf, false); });   // row_shr 8
-    // lanes 15, 31, 47, 63 hold the maxima of their rows
-    const long long b = __double_as_longlong(v);
-    double r = -1.0;
-#pragma unroll
-    for (int l = 15; l < 64; l += 16) {
-        const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffff), l);
-        const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
-        r = fmax(r, __longlong_as_double(((long long)hi << 32) | (unsigned)lo));
-    }
-    return r;
+    v = step(v, [](int x) { return __builtin_amdgcn_update_dpp(x, x, 0x142, 0xa, 0xf, false); });   // row_bcast 15
+    v = step(v, [](int x) { return __builtin_amdgcn_update_dpp(x, x, 0x143, 0xc, 0xf, false); });   // row_bcast 31
+    const long long b = __double_as_longlong(v);   // lane 63: all lanes
+    const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffff), 63);
+    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), 63);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
 // ---------------------------------------------------------------------------
-// Pivots and D^{-1} of one panel: columns [j0, j0 + nb), candidate rows
-// [j0, m), each thread RPT rows of NB columns in registers (RPT NTH >= m - j0).
-// Rows stay where they are; a thread tracks the logical position of its rows
-// under the interchanges.  Two barriers per column (candidates of the
-// wavefronts; the pivot row).  Latency bound: 0.3-0.5 us per column.
-// Writes rowsrc[i] = row that the interchanges bring to position i >= j0, the
-// accumulated permutation perm, and D^{-1} (NB x NB, zero padded); A is only
-// read.
+// Pivots and D^{-1} of one panel: columns [j0, j0 + nb),
+// candidate rows [j0, m), each thread RPT rows of NB columns in registers (RPT
+// NTH >= m - j0).  Rows stay where they are; a thread tracks the logical
+// position of its rows under the interchanges.  A latency chain: two barriers
+// per column (candidates of the wavefronts; the pivot row).  The column loops
+// are not unrolled: each step shifts the row by one column as it updates it
+// (the current column is always a[.][0]), eight columns per loop with the
+// width shrinking in between.
+//
+// The panel comes from its transposed copy Pt [column][row], so that the loads
+// of consecutive rows are contiguous (from A, one 256-byte row segment per
+// lane, they took 13 us of a 55 us panel); the multipliers of all rows go to
+// Lt [column][row].  Writes rowsrc[i] = row that the interchanges bring to
+// position i >= j0, the accumulated permutation perm, and D^{-1} (NB x NB, zero
+// beyond nb).
 // ---------------------------------------------------------------------------
 template <int NB, int RPT, int NTH>
-__global__ void __launch_bounds__(NTH) inv_panel_kernel(const double *__restrict__ A, int m, int ld, int j0, int nb,
-                                                        double *__restrict__ dinv, int *__restrict__ rowsrc,
-                                                        int *__restrict__ perm)
+__global__ void __launch_bounds__(NTH) inv_panel_kernel(const double *__restrict__ Pt, double *__restrict__ Lt, int m,
+                                                        int ld, int j0, int nb, double *__restrict__ dinv,
+                                                        int *__restrict__ rowsrc, int *__restrict__ perm)
 {
     constexpr int NW = NTH / 64;
     __shared__ double wval[NW];
     __shared__ int wlog[NW];
-    __shared__ double prow[NB];
-    __shared__ double Dt[NB][NB];   // transposed: Dt[column][row]
+    __shared__ alignas(16) double urow[NB][NB];   // urow[c][j] = U of D, row c, column c + j
+    __shared__ int pivrow[NB];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int mr = m - j0;
     double a[RPT][NB];
@@ -92,70 +95,83 @@ __global__ void __launch_bounds__(NTH) inv_panel_kernel(const double *__restrict
         const int r = tid + i * NTH;
         lg[i] = r;
         if (r < mr) open |= 1u << i;
-        const double *src = A + (long long)(j0 + min(r, mr - 1)) * ld + j0;
+        const double *src = Pt + j0 + min(r, mr - 1);
 #pragma unroll
-        for (int k = 0; k < NB; ++k) a[i][k] = src[min(k, nb - 1)];
+        for (int k = 0; k < NB; ++k) a[i][k] = src[(long long)min(k, nb - 1) * ld];
     }
-    auto column = [&](auto cc) {
-        constexpr int c = decltype(cc)::value;
-        if (c >= nb) return;
-        double best = -1.0;
-        int bl = 0;
+    auto columns = [&](auto width, int c0) {
+        constexpr int WD = decltype(width)::value;   // columns that are left
+        const int c1 = min(c0 + 8, nb);
+#pragma unroll 1
+        for (int c = c0; c < c1; ++c) {
+            double best = -1.0;
+            int bl = 0;
 #pragma unroll
-        for (int i = 0; i < RPT; ++i) {
-            const double v = fabs(a[i][c]);
-            if (((open >> i) & 1u) && v > best) {
-                best = v;
-                bl = lg[i];
+            for (int i = 0; i < RPT; ++i) {
+                const double v = fabs(a[i][0]);
+                if (((open >> i) & 1u) && v > best) {
+                    best = v;
+                    bl = lg[i];
+                }
             }
-        }
-        const double wm = wave_max(best);
-        const unsigned long long hit = __ballot(best == wm);
-        if (lane == __builtin_ctzll(hit | (1ull << 63))) {
-            wval[wv] = wm;
-            wlog[wv] = bl;
-        }
-        __syncthreads();
-        // a column without a comparable entry (all NaN) keeps its own row
-        double bv = -1.0;
-        int p = c;
-#pragma unroll
-        for (int w = 0; w < NW; ++w) {
-            const double v = wval[w];
-            if (v > bv) {
-                bv = v;
-                p = wlog[w];
+            const double wm = wave_max(best);
+            const unsigned long long hit = __ballot(best == wm);
+            if (lane == __builtin_ctzll(hit | (1ull << 63))) {
+                wval[wv] = wm;
+                wlog[wv] = bl;
             }
-        }
+            __syncthreads();
+            double bv[NW];
+            int bp[NW];
 #pragma unroll
-        for (int i = 0; i < RPT; ++i)
-            if (((open >> i) & 1u) && lg[i] == p) {
-#pragma unroll
-                for (int k = c; k < NB; ++k) prow[k] = a[i][k];
+            for (int w = 0; w < NW; ++w) {
+                bv[w] = wval[w];
+                bp[w] = wlog[w];
             }
-        __syncthreads();
-        const double d = prow[c];
-        const double inv = d != 0.0 ? 1.0 / d : 0.0;
-        double l[RPT];
 #pragma unroll
-        for (int i = 0; i < RPT; ++i) {
-            const bool op = (open >> i) & 1u, piv = op && lg[i] == p;
-            if (op && !piv) a[i][c] *= inv;
-            l[i] = op && !piv ? a[i][c] : 0.0;   // pivotal rows stay
-            if (op && !piv && lg[i] == c) lg[i] = p;
-            if (piv) {
-                lg[i] = c;
-                open &= ~(1u << i);
+            for (int h = NW / 2; h > 0; h /= 2)
+#pragma unroll
+                for (int w = 0; w < h; ++w)
+                    if (bv[w + h] > bv[w]) {
+                        bv[w] = bv[w + h];
+                        bp[w] = bp[w + h];
+                    }
+            // a column without a comparable entry (all NaN) keeps its own row
+            const int p = bv[0] < 0.0 ? c : bp[0];
+#pragma unroll
+            for (int i = 0; i < RPT; ++i)
+                if (((open >> i) & 1u) && lg[i] == p) {
+                    pivrow[c] = j0 + tid + i * NTH;
+#pragma unroll
+                    for (int k = 0; k < WD; ++k) urow[c][k] = a[i][k];
+                }
+            __syncthreads();
+            const double d = urow[c][0];
+            const double inv = d != 0.0 ? 1.0 / d : 0.0;
+            double l[RPT];
+#pragma unroll
+            for (int i = 0; i < RPT; ++i) {
+                const bool op = (open >> i) & 1u, piv = op && lg[i] == p;
+                l[i] = op && !piv ? a[i][0] * inv : 0.0;
+                if (op && !piv) Lt[(long long)c * ld + j0 + tid + i * NTH] = l[i];
+                if (op && !piv && lg[i] == c) lg[i] = p;
+                if (piv) {
+                    lg[i] = c;
+                    open &= ~(1u << i);
+                }
             }
-        }
 #pragma unroll
-        for (int k = c + 1; k < NB; ++k) {
-            const double u = prow[k];
+            for (int k = 1; k < WD; ++k) {
+                const double u = urow[c][k];
 #pragma unroll
-            for (int i = 0; i < RPT; ++i) a[i][k] -= l[i] * u;
+                for (int i = 0; i < RPT; ++i) a[i][k - 1] = a[i][k] - l[i] * u;
+            }
         }
     };
-    static_for(std::make_integer_sequence<int, NB>{}, column);
+    static_for(std::make_integer_sequence<int, NB / 8>{}, [&](auto s) {
+        constexpr int c0 = 8 * decltype(s)::value;
+        if (c0 < nb) columns(std::integral_constant<int, NB - c0>{}, c0);
+    });
     int before[RPT];
 #pragma unroll
     for (int i = 0; i < RPT; ++i) {
@@ -163,39 +179,45 @@ __global__ void __launch_bounds__(NTH) inv_panel_kernel(const double *__restrict
         if (r < mr) {
             before[i] = j0 == 0 ? r : perm[j0 + r];
             rowsrc[j0 + lg[i]] = j0 + r;
-            if (lg[i] < nb) {
-#pragma unroll
-                for (int k = 0; k < NB; ++k) Dt[k][lg[i]] = a[i][k];
-            }
         }
     }
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < RPT; ++i)
         if (tid + i * NTH < mr) perm[j0 + lg[i]] = before[i];
-    // D^{-1} = U^{-1} L^{-1}, one column per lane
-    if (tid < NB) {
-        double y[NB];
+    // D^{-1} = U^{-1} L^{-1}: lane i holds row i, each wavefront CPW columns;
+    // both substitutions are y -= coef_k y_k with y_k broadcast from lane k (U
+    // divided by its diagonal, which scales the rows at the end)
+    constexpr int CPW = NB / NW;
+    const int i = min(lane, NB - 1), ir = min(i, nb - 1);
+    double coef[NB], y[CPW];
 #pragma unroll
-        for (int c = 0; c < NB; ++c) y[c] = c == tid ? 1.0 : 0.0;
-        // (identity beyond nb)
-        static_for(std::make_integer_sequence<int, NB>{}, [&](auto kk) {
-            constexpr int k = decltype(kk)::value;
-            if (k < nb) {
+    for (int k = 0; k < NB; ++k) coef[k] = k < i && i < nb ? Lt[(long long)k * ld + pivrow[ir]] : 0.0;
 #pragma unroll
-                for (int c = k + 1; c < NB; ++c) y[c] -= Dt[k][c] * y[k];
-            }
-        });
-        static_for(std::make_integer_sequence<int, NB>{}, [&](auto kk) {
-            constexpr int k = NB - 1 - decltype(kk)::value;
-            if (k < nb) {
-                y[k] /= Dt[k][k];
+    for (int q = 0; q < CPW; ++q) y[q] = i == wv * CPW + q ? 1.0 : 0.0;
+    auto bcast = [](double x, int l) {
+        const long long b = __double_as_longlong(x);
+        const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffff), l);
+        const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
+        return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+    };
 #pragma unroll
-                for (int c = 0; c < k; ++c) y[c] -= Dt[k][c] * y[k];
-            }
-        });
+    for (int k = 0; k < NB - 1; ++k)
 #pragma unroll
-        for (int c = 0; c < NB; ++c) dinv[c * NB + tid] = c < nb && tid < nb ? y[c] : 0.0;
+        for (int q = 0; q < CPW; ++q) y[q] -= coef[k] * bcast(y[q], k);
+    const double rd = i < nb ? 1.0 / urow[ir][0] : 1.0;
+#pragma unroll
+    for (int k = 0; k < NB; ++k) coef[k] = k > i && k < nb ? urow[i][k - i] * bcast(rd, k) : 0.0;
+#pragma unroll
+    for (int k = NB - 1; k > 0; --k)
+#pragma unroll
+        for (int q = 0; q < CPW; ++q) y[q] -= coef[k] * bcast(y[q], k);
+    if (lane < NB) {
+#pragma unroll
+        for (int q = 0; q < CPW; ++q) {
+            const int j = wv * CPW + q;
+            dinv[lane * NB + j] = lane < nb && j < nb ? y[q] * rd : 0.0;
+        }
     }
 }
 
@@ -268,14 +290,15 @@ __global__ void __launch_bounds__(256) inv_swap_kernel(double *__restrict__ A, i
 }
 
 // ---------------------------------------------------------------------------
-// A <- A + W B (rows J: W B alone; columns J: W), one 32 x 32 tile per
-// wavefront on v_mfma_f64_16x16x4f64 (A lane l -> (row l%16, k l/16), B lane
+// A <- A + W B (rows J: W B alone; columns J: W), with a transposed copy of the
+// next panel's columns [jn, jn + nbn) to Pt; one 32 x 32 tile per wavefront on v_mfma_f64_16x16x4f64 (A lane l -> (row l%16, k l/16), B lane
 // l -> (k l/16, col l%16), D register i -> (row l/16 + 4i, col l%16)).  Bound
 // by the read and write of A; W (m x nb) and B stay in L2.
 // ---------------------------------------------------------------------------
 template <int NB>
 __global__ void __launch_bounds__(256) inv_update_kernel(double *__restrict__ A, int m, int ld, int j0, int nb,
-                                                         const double *__restrict__ W, const double *__restrict__ B)
+                                                         const double *__restrict__ W, const double *__restrict__ B,
+                                                         double *__restrict__ Pt, int jn, int nbn)
 {
     const int lane = threadIdx.x & 63, l16 = lane & 15, g = lane >> 4;
     const int nt = (m + 31) / 32, t = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -317,6 +340,7 @@ __global__ void __launch_bounds__(256) inv_update_kernel(double *__restrict__ A,
                 if (row < m) {
                     const bool inj = col >= j0 && col < j0 + nb;
                     A[(long long)row * ld + col] = inj ? W[(long long)row * NB + col - j0] : acc[si][sj][i];
+                    if (col >= jn && col < jn + nbn) Pt[(long long)(col - jn) * ld + row] = acc[si][sj][i];
                 }
             }
 }
@@ -358,7 +382,8 @@ __global__ void __launch_bounds__(256) inv_apply_kernel(const double *__restrict
 // coarse matrix from the columns J e_i (row i of Y) and the border of
 // constant pressures: transposed through LDS, 32 x 32 tiles
 __global__ void __launch_bounds__(256) inv_matrix_kernel(const double *__restrict__ Y, int n, int nb, long long pbase,
-                                                         long long Np1, int npm, double *__restrict__ A, int ld)
+                                                         long long Np1, int npm, double *__restrict__ A, int ld,
+                                                         double *__restrict__ Pt)
 {
     __shared__ double t[32][33];
     const int m = n + nb, r0 = blockIdx.y * 32, c0 = blockIdx.x * 32;
@@ -380,16 +405,21 @@ __global__ void __launch_bounds__(256) inv_matrix_kernel(const double *__restric
             v = q >= a * Np1 && q < (a + 1) * Np1 && (q - a * Np1) % npm == 0 ? 1.0 : 0.0;
         }
         A[(long long)row * ld + col] = v;
+        if (col < 32) Pt[(long long)col * ld + row] = v;   // the first panel, transposed
     }
 }
 
+// the widest panel whose candidate rows fit the registers of one workgroup
+// (RPT NB = 96 doubles per thread at 8 wavefronts)
+int panel_width(int rows) { return min(rows, rows <= 1536 ? 32 : rows <= 3072 ? 16 : 8); }
+
 } // namespace
 
-hipError_t launch_inv_matrix(const double *Y, int n, int nb, long long pbase, long long Np1, int npm, double *A,
-                             int ld, hipStream_t s)
+hipError_t launch_inv_matrix(const double *Y, int n, int nb, long long pbase, long long Np1, int npm,
+                             const DenseInverse &w, hipStream_t s)
 {
     const unsigned nt = (unsigned)((n + nb + 31) / 32);
-    hipLaunchKernelGGL(inv_matrix_kernel, dim3(nt, nt), dim3(256), 0, s, Y, n, nb, pbase, Np1, npm, A, ld);
+    hipLaunchKernelGGL(inv_matrix_kernel, dim3(nt, nt), dim3(256), 0, s, Y, n, nb, pbase, Np1, npm, w.A, w.ld, w.Pt);
     return hipGetLastError();
 }
 
@@ -400,42 +430,38 @@ hipError_t launch_dense_inverse(const DenseInverse &w, hipStream_t s)
     if (m > DINV_MAX_M) return hipErrorInvalidValue;
     const int wblk = (m + 63) / 64, cblk = (m + 255) / 256, nt = (m + 31) / 32, ublk = (nt * nt + 3) / 4;
     for (int j0 = 0; j0 < m;) {
-        // the widest panel whose candidate rows fit the registers of one
-        // workgroup (RPT NB doubles per thread: 192 registers at 8 wavefronts,
-        // 96 at 16), and the fewest wavefronts that hold them
-        const int mr = m - j0;
-        int nb = 0;
+        const int mr = m - j0, nb = panel_width(mr), jn = j0 + nb, nbn = jn < m ? panel_width(m - jn) : 0;
 #define STMG_PANEL(NB, RPT, NTH)                                                                                       \
-    {                                                                                                                  \
-        nb = min(NB, mr);                                                                                              \
-        hipLaunchKernelGGL((inv_panel_kernel<NB, RPT, NTH>), dim3(1), dim3(NTH), 0, s, (const double *)w.A, m, ld, j0, \
-                           nb, w.dinv, w.rowsrc, w.perm);                                                              \
-    }
+    hipLaunchKernelGGL((inv_panel_kernel<NB, RPT, NTH>), dim3(1), dim3(NTH), 0, s, (const double *)w.Pt, w.B, m, ld, \
+                       j0, nb, w.dinv, w.rowsrc, w.perm)
 #define STMG_REST(NB)                                                                                                  \
     {                                                                                                                  \
         hipLaunchKernelGGL(inv_swap_kernel<NB>, dim3(wblk + cblk), dim3(256), 0, s, w.A, m, ld, j0, nb,                \
                            (const double *)w.dinv, (const int *)w.rowsrc, w.W, w.B, wblk);                             \
         hipLaunchKernelGGL(inv_update_kernel<NB>, dim3(ublk), dim3(256), 0, s, w.A, m, ld, j0, nb,                     \
-                           (const double *)w.W, (const double *)w.B);                                                  \
+                           (const double *)w.W, (const double *)w.B, w.Pt, jn, nbn);                                   \
     }
+        // the fewest wavefronts that hold the candidate rows: every wavefront
+        // reads the whole pivot row from LDS in each column
         if (mr <= 1536) {
-            if (mr <= 256) STMG_PANEL(32, 1, 256)
-            else if (mr <= 512) STMG_PANEL(32, 1, 512)
-            else if (mr <= 1024) STMG_PANEL(32, 2, 512)
-            else STMG_PANEL(32, 3, 512)
+            if (mr <= 256) STMG_PANEL(32, 1, 256);
+            else if (mr <= 512) STMG_PANEL(32, 2, 256);
+            else if (mr <= 768) STMG_PANEL(32, 3, 256);
+            else if (mr <= 1024) STMG_PANEL(32, 2, 512);
+            else STMG_PANEL(32, 3, 512);
             STMG_REST(32)
         } else if (mr <= 3072) {
-            STMG_PANEL(16, 3, 1024)
+            STMG_PANEL(16, 6, 512);
             STMG_REST(16)
         } else {
-            STMG_PANEL(8, 6, 1024)
+            STMG_PANEL(8, 12, 512);
             STMG_REST(8)
         }
 #undef STMG_PANEL
 #undef STMG_REST
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        j0 += nb;
+        j0 = jn;
     }
     return hipSuccess;
 }

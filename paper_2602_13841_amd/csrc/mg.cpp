@@ -243,6 +243,7 @@ void mg_allocate(stmg_ctx *ctx)
             mg.cA.alloc((size_t)m * ld * 8);
             mg.cW.alloc(ld * 32 * 8);
             mg.cB.alloc(32 * ld * 8);
+            mg.cP.alloc(32 * ld * 8);
             mg.cdinv.alloc(32 * 32 * 8);
             mg.crow.alloc((size_t)m * 4);
             mg.cperm.alloc((size_t)m * 4);
@@ -289,7 +290,7 @@ void mg_set_state(stmg_ctx *ctx, const double *u)
         Lc.apply<double>(Mode::Jac, C.st64.as<double>(), mg.cX.as<double>(), mg.cY.as<double>(), nullptr, nullptr, n, s);
         if (mg.inverse) {
             const DenseInverse w = mg.dense_inverse();
-            STMG_HIP(launch_inv_matrix(mg.cY.as<double>(), n, nb, (long long)Lc.nt * Lc.Nv1, Lc.Np1, Lc.npm, w.A, w.ld, s));
+            STMG_HIP(launch_inv_matrix(mg.cY.as<double>(), n, nb, (long long)Lc.nt * Lc.Nv1, Lc.Np1, Lc.npm, w, s));
             STMG_HIP(launch_dense_inverse(w, s));
         } else {
             STMG_HIP(launch_coarse_matrix(mg.cY.as<double>(), n, nb, Lc.nt, (long long)Lc.nt * Lc.Nv1, Lc.Np1, Lc.npm,

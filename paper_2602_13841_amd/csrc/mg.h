@@ -1,6 +1,7 @@
 // hp space-time multigrid hierarchy, Krylov and Newton drivers (internal).
 #pragma once
 
+#include "coarse.h"
 #include "context.h"
 #include "transfers.h"
 #include "vanka.h"
@@ -74,12 +75,12 @@ struct Mg {
     // coarsest level direct solve (FP64)
     DevBuf cX, cY, cA, cpiv, cinfo, cr64, cx64;
     int cn = 0, cm = 0;
-    DevBuf cW, cB, cdinv, crow, cperm;   // inverse of the coarse matrix (up to DINV_MAX_M unknowns)
+    DevBuf cW, cB, cP, cdinv, crow, cperm;   // inverse of the coarse matrix (up to DINV_MAX_M unknowns)
     bool inverse = false;
     DenseInverse dense_inverse() const
     {
-        return DenseInverse{cA.as<double>(), cm, dinv_ld(cm), cW.as<double>(), cB.as<double>(), cdinv.as<double>(),
-                            crow.as<int>(), cperm.as<int>()};
+        return DenseInverse{cA.as<double>(), cm, dinv_ld(cm), cW.as<double>(), cB.as<double>(), cP.as<double>(),
+                            cdinv.as<double>(), crow.as<int>(), cperm.as<int>()};
     }
     bool border = false;
     bool state_set = false;
