@@ -1,0 +1,1133 @@
+// LU factorizations of the time-decoupled patch systems and the sweeps that
+// use them.
+//
+// One workgroup factors one matrix (real or complex planar, FP32 or FP64,
+// row-major), left-looking in block columns of 32: the block column is held in
+// MFMA accumulators (32 x 32 row tiles over the wavefronts), receives the
+// updates of all finished block columns, is factored in panels of 16 columns
+// and written once.  A right-looking factorization moves the trailing matrix
+// through HBM once per block (13.3 MB per 395 x 395 complex FP32 matrix of 1.25
+// MB measured for the two-level kernel this replaced); here each block column
+// is read and written once and L once per later block column (6.4 MB).
+// 13824 matrices of 395 complex FP32: 93.7 -> 43.7 ms (52 TFLOP/s of the 148
+// that a large FP32 product reaches); 1728 of 202: 3.7 -> 1.7 ms; 13824 of 85:
+// 7.0 -> 2.1 ms; 512 complex FP64 of 202: 2.0 -> 1.2 ms.  What bounds it at 395,
+// two workgroups per CU (cycles of a workgroup, per matrix): the MFMA updates
+// 1.27 M (they keep the matrix cores busy 38 % of the time), the panel columns
+// 1.1 M (a latency chain of 1100 cycles in pivot search and publishing per
+// column), U products 0.3 M, panel staging and inverses 0.6 M.
+//
+// Rows never move: cur[p] is the stored row at position p of the permuted
+// matrix, and everything addresses rows through it (loads and stores of whole
+// row segments, so the indirection costs nothing).  Position tiles are
+// therefore exact: tile K < J of block column J holds the pivot rows of block
+// K, and the update with block K touches the tiles behind it only.
+//
+// Format left in A (position p at row perm[p]): L below the diagonal blocks, U
+// above them, and in each 32 x 32 diagonal block the strict lower part of
+// L_JJ^{-1} and the upper triangle of U_JJ^{-1}; the factorization applies
+// L_JJ^{-1} by MFMA and the sweeps replace both substitutions of a diagonal
+// block by products.
+#include "vanka.h"
+
+#include "stmg_internal.h"
+
+#include <type_traits>
+#include <utility>
+
+namespace stmg {
+
+namespace {
+
+typedef float floatx4_t __attribute__((ext_vector_type(4)));
+typedef double doublex4_t __attribute__((ext_vector_type(4)));
+// 16-byte row segments at element alignment
+typedef float floatx4_u __attribute__((ext_vector_type(4), aligned(4)));
+typedef double doublex2_u __attribute__((ext_vector_type(2), aligned(8)));
+
+template <typename T> struct Vec;
+template <> struct Vec<float> {
+    using acc = floatx4_t;
+    using seg = floatx4_u;
+    static constexpr int W = 4;      // elements of a 16-byte segment
+    static constexpr int LDU = 36;   // row stride of a U block in LDS: the four k groups on disjoint banks
+    static __device__ __forceinline__ acc mfma(float a, float b, acc c)
+    {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+    }
+    // row of accumulator register i of lane group g
+    static __device__ __forceinline__ int row(int g, int i) { return 4 * g + i; }
+};
+template <> struct Vec<double> {
+    using acc = doublex4_t;
+    using seg = doublex2_u;
+    static constexpr int W = 2;
+    static constexpr int LDU = 40;
+    static __device__ __forceinline__ acc mfma(double a, double b, acc c)
+    {
+        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+    }
+    static __device__ __forceinline__ int row(int g, int i) { return g + 4 * i; }
+};
+
+template <int... I, typename F> __device__ __forceinline__ void static_for(std::integer_sequence<int, I...>, F &&f)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+
+// x moved by a DPP control (both halves of a double)
+template <int CTRL, int RM> __device__ __forceinline__ float dpp(float x)
+{
+    const int b = __float_as_int(x);
+    return __int_as_float(__builtin_amdgcn_update_dpp(b, b, CTRL, RM, 0xf, false));
+}
+template <int CTRL, int RM> __device__ __forceinline__ double dpp(double x)
+{
+    const long long b = __double_as_longlong(x);
+    const int lo = (int)(b & 0xffffffff), hi = (int)(b >> 32);
+    const int l = __builtin_amdgcn_update_dpp(lo, lo, CTRL, RM, 0xf, false);
+    const int h = __builtin_amdgcn_update_dpp(hi, hi, CTRL, RM, 0xf, false);
+    return __longlong_as_double(((long long)h << 32) | (unsigned)l);
+}
+__device__ __forceinline__ float lane_value(float x, int l)
+{
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l));
+}
+__device__ __forceinline__ double lane_value(double x, int l)
+{
+    const long long b = __double_as_longlong(x);
+    const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffff), l);
+    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+// wavefront maximum, uniform (row_shr 1, 2, 4, 8, then row_bcast 15 and 31).
+// FP32: as integers, which order like the values for v >= 0 and the sentinel
+// -1, so that each step is one instruction.
+__device__ __forceinline__ float wave_max(float x)
+{
+    int v = __float_as_int(x);
+    constexpr int lowest = -0x7fffffff - 1;
+    v = max(v, __builtin_amdgcn_update_dpp(lowest, v, 0x111, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(lowest, v, 0x112, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(lowest, v, 0x114, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(lowest, v, 0x118, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(lowest, v, 0x142, 0xa, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(lowest, v, 0x143, 0xc, 0xf, false));
+    return __int_as_float(__builtin_amdgcn_readlane(v, 63));
+}
+__device__ __forceinline__ double wave_max(double v)
+{
+    v = fmax(v, dpp<0x111, 0xf>(v));
+    v = fmax(v, dpp<0x112, 0xf>(v));
+    v = fmax(v, dpp<0x114, 0xf>(v));
+    v = fmax(v, dpp<0x118, 0xf>(v));
+    v = fmax(v, dpp<0x142, 0xa>(v));
+    v = fmax(v, dpp<0x143, 0xc>(v));
+    return lane_value(v, 63);
+}
+
+// ---------------------------------------------------------------------------
+// small dense pieces, one wavefront each, 16 x 16 blocks in LDS (row stride
+// LS entries of P words)
+// ---------------------------------------------------------------------------
+constexpr int TD_BW = 32;   // block columns
+constexpr int TD_PW = 16;   // panel columns
+constexpr int TD_LS = 17;   // row stride of panels and small blocks (entries)
+
+// C (+)= A B on one 16 x 16 tile, K = 16, A and B as LDS blocks: lane (r, g)
+// supplies A[r][k] and B[k][r] for k = 4W h + W g + s
+template <typename T, bool CX>
+__device__ __forceinline__ void mm16(const T *A, const T *B, typename Vec<T>::acc &cr, typename Vec<T>::acc &ci)
+{
+    constexpr int P = CX ? 2 : 1, W = Vec<T>::W;
+    const int l = threadIdx.x & 63, r = l & 15, g = l >> 4;
+#pragma unroll
+    for (int h = 0; h < 16 / (4 * W); ++h)
+#pragma unroll
+        for (int s = 0; s < W; ++s) {
+            const int k = 4 * W * h + W * g + s;
+            const T *a = A + (r * TD_LS + k) * P, *b = B + (k * TD_LS + r) * P;
+            cr = Vec<T>::mfma(a[0], b[0], cr);
+            if constexpr (CX) {
+                cr = Vec<T>::mfma(-a[1], b[1], cr);
+                ci = Vec<T>::mfma(a[0], b[1], ci);
+                ci = Vec<T>::mfma(a[1], b[0], ci);
+            }
+        }
+}
+
+// inverse of a 16 x 16 triangular block (unit lower, or upper): lane (i, g)
+// holds row i of columns 4g .. 4g+3; one step per eliminated row, its values
+// broadcast inside the 16-lane rows.  coef(i, k): entry (i, k) of the block,
+// zero outside the strict triangle; rd: reciprocal of the lane's own diagonal
+// entry (1 for the lower block)
+template <typename T, bool CX, bool UPPER, typename F>
+__device__ __forceinline__ void tri_inverse16(F coef, T rdr, T rdi, T (&yr)[4], T (&yi)[4])
+{
+    const int l = threadIdx.x & 63, i = l & 15, g = l >> 4;
+    T cr[16], ci[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) coef(i, k, cr[k], ci[k]);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        yr[q] = i == 4 * g + q ? T(1) : T(0);
+        yi[q] = T(0);
+    }
+    static_for(std::make_integer_sequence<int, 15>{}, [&](auto kk) {
+        constexpr int k = UPPER ? 15 - decltype(kk)::value : decltype(kk)::value;
+        constexpr int BC = 0x150 + k;   // row_newbcast
+        T ar = cr[k], ai = ci[k];
+        if constexpr (UPPER) {
+            // column k divided by its diagonal entry: the rows are scaled last
+            const T dr = dpp<BC, 0xf>(rdr);
+            if constexpr (CX) {
+                const T di = dpp<BC, 0xf>(rdi), t = ar * dr - ai * di;
+                ai = ar * di + ai * dr;
+                ar = t;
+            } else {
+                ar *= dr;
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const T br = dpp<BC, 0xf>(yr[q]);
+            if constexpr (CX) {
+                const T bi = dpp<BC, 0xf>(yi[q]);
+                yr[q] -= ar * br;
+                yr[q] += ai * bi;
+                yi[q] -= ar * bi;
+                yi[q] -= ai * br;
+            } else {
+                yr[q] -= ar * br;
+            }
+        }
+    });
+    if constexpr (UPPER) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if constexpr (CX) {
+                const T t = yr[q] * rdr - yi[q] * rdi;
+                yi[q] = yr[q] * rdi + yi[q] * rdr;
+                yr[q] = t;
+            } else {
+                yr[q] *= rdr;
+            }
+        }
+    }
+}
+
+template <typename T, bool CX> __device__ __forceinline__ void reciprocal(T dr, T di, T &ir, T &ii)
+{
+    if constexpr (CX) {
+        const T den = dr * dr + di * di;
+        ir = den != T(0) ? dr / den : T(0);
+        ii = den != T(0) ? -di / den : T(0);
+    } else {
+        const T inv = T(1) / dr;
+        ir = dr != T(0) ? inv : T(0);
+        ii = T(0);
+    }
+}
+
+// LDS words of T and of int for one factorization
+template <typename T, bool CX> constexpr size_t td_lu_lds_bytes(int m)
+{
+    constexpr int P = CX ? 2 : 1;
+    const size_t pan = (size_t)m * TD_LS * P, ub = (size_t)P * TD_BW * Vec<T>::LDU;
+    return (pan + 2 * ub) * sizeof(T) + (size_t)(2 * ((m + 31) & ~31) + TD_BW) * sizeof(int);
+}
+
+// ---------------------------------------------------------------------------
+// the factorization: NW wavefronts, SLOTS row tiles per wavefront (32 NW SLOTS
+// >= m), RPT panel rows per thread (64 NW RPT >= m)
+// ---------------------------------------------------------------------------
+template <typename T, bool CX, int NW, int SLOTS, int RPT>
+__global__ void __launch_bounds__(64 * NW, 2) lu_td_kernel(T *__restrict__ Aall, int *__restrict__ permall, int m, int ld,
+                                                        long long a_stride, int *info)
+{
+    using V = Vec<T>;
+    using acc_t = typename V::acc;
+    using seg_t = typename V::seg;
+    constexpr int P = CX ? 2 : 1, W = V::W, LDU = V::LDU, NTH = 64 * NW;
+    constexpr int NH = TD_BW / (4 * W);   // 16-byte segments per lane along K = 32
+    extern __shared__ unsigned char lds_raw[];
+    T *pan = reinterpret_cast<T *>(lds_raw);                  // [rows from the block on][TD_LS][P]
+    T *ub1 = pan + (size_t)m * TD_LS * P;                      // [P][32][LDU]
+    T *ub2 = ub1 + P * TD_BW * LDU;                            // [P][32][LDU] (negated U)
+    // 16 x 16 blocks of the panel phase, in the U blocks: A12 (then L21), a
+    // product and V2 in the first, U12, I1, V1 and I2 in the second
+    constexpr int SB = 16 * TD_LS * P;
+    static_assert(4 * SB <= P * TD_BW * LDU, "four small blocks fit a U block");
+    T *sV2 = ub1 + 2 * SB, *sI1 = ub2 + SB, *sV1 = ub2 + 2 * SB, *sI2 = ub2 + 3 * SB;
+    int *cur = reinterpret_cast<int *>(ub2 + P * TD_BW * LDU);   // stored row at each position
+    int *rk = cur + ((m + 31) & ~31);                          // rank of a panel row among the block's pivots, or -1
+    int *pl = rk + ((m + 31) & ~31);                           // panel row of each pivot of the block
+    // pivot candidates of the wavefronts, by column parity: value, panel row |
+    // position << 16, and the row from its current column on
+    __shared__ alignas(16) T wval[2][NW];
+    __shared__ alignas(16) int wkey[2][NW];
+    __shared__ alignas(16) T pub[2][NW][16 * P];
+
+    const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    T *Ar = Aall + (long long)blockIdx.x * a_stride;
+    T *Ai = Ar + (CX ? (long long)m * ld : 0);
+    int *perm = permall + (long long)blockIdx.x * m;
+    // entries of A by byte offset (32-bit offsets from a uniform base)
+    const unsigned ldb = ld * sizeof(T);
+    auto at = [](T *base, unsigned o) { return reinterpret_cast<T *>(reinterpret_cast<char *>(base) + o); };
+    const int nt = (m + 31) / 32;
+    for (int p = tid; p < m; p += NTH) cur[p] = p;
+    __syncthreads();
+
+    for (int J = 0; J < nt; ++J) {
+        const int j0 = 32 * J, nbj = min(32, m - j0), mr = m - j0;
+        // opaque to the compiler, so that it does not keep every address that
+        // depends on the lane alive (spilled) across the block columns
+        int lane = tid & 63;
+        asm volatile("" : "+v"(lane));
+        const int l16 = lane & 15, g = lane >> 4;
+        const unsigned jb = j0 * sizeof(T);
+        // ---- the block column, rows in position order ------------------------------
+        acc_t ar[SLOTS][2][2], ai[CX ? SLOTS : 1][2][2];
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s) {
+            // (tiles past the end reload the last row: no branch between the loads)
+            const int t = wv + NW * s;
+#pragma unroll
+            for (int si = 0; si < 2; ++si)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const unsigned o = cur[min(32 * t + 16 * si + V::row(g, i), m - 1)] * ldb + jb;
+#pragma unroll
+                    for (int sj = 0; sj < 2; ++sj) {
+                        const unsigned c = min(16 * sj + l16, nbj - 1) * sizeof(T);
+                        ar[s][si][sj][i] = *at(Ar, o + c);
+                        if constexpr (CX) ai[s][si][sj][i] = *at(Ai, o + c);
+                    }
+                }
+        }
+        // ---- updates of the finished block columns ------------------------------------
+        // row offsets of the L operands of this wavefront's tiles
+        unsigned ro[SLOTS][2];
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s)
+#pragma unroll
+            for (int si = 0; si < 2; ++si) 
+                ro[s][si] = cur[min(32 * (wv + NW * s) + 16 * si + l16, m - 1)] * ldb + 16 * g;
+        // U = L_KK^{-1} (tile K), its four 16 x 16 tiles spread over the
+        // wavefronts (tile q: rows 16 (q / 2), columns 16 (q % 2)); the rows
+        // of L_KK^{-1} are loaded one block ahead
+        constexpr int UT = NW >= 4 ? 1 : 4 / NW;
+        seg_t fr[UT][NH], fi[CX ? UT : 1][NH];
+        auto load_inverse = [&](int K) {
+#pragma unroll
+            for (int u = 0; u < UT; ++u) {
+                const int si0 = ((wv + NW * u) >> 1) & 1;
+                const unsigned o = cur[32 * K + 16 * si0 + l16] * ldb + 32 * K * sizeof(T) + 16 * g;
+#pragma unroll
+                for (int h = 0; h < NH; ++h) {
+                    fr[u][h] = *(const seg_t *)at(Ar, o + 64 * h);
+                    if constexpr (CX) fi[u][h] = *(const seg_t *)at(Ai, o + 64 * h);
+                }
+            }
+        };
+        if (J > 0 && wv < 4) load_inverse(0);
+#pragma unroll 1
+        for (int K = 0; K < J; ++K) {
+            // tile K: the pivot rows of block K
+#pragma unroll
+            for (int s = 0; s < SLOTS; ++s)
+                if (wv + NW * s == K) {
+#pragma unroll
+                    for (int si = 0; si < 2; ++si)
+#pragma unroll
+                        for (int sj = 0; sj < 2; ++sj)
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) {
+                                const int o = (16 * si + V::row(g, i)) * LDU + 16 * sj + l16;
+                                ub1[o] = ar[s][si][sj][i];
+                                if constexpr (CX) ub1[TD_BW * LDU + o] = ai[s][si][sj][i];
+                            }
+                }
+            __syncthreads();
+            if (wv < 4) {
+#pragma unroll
+                for (int u = 0; u < UT; ++u) {
+                    const int si0 = ((wv + NW * u) >> 1) & 1, sj0 = (wv + NW * u) & 1;
+                    acc_t dr = {0, 0, 0, 0}, di = {0, 0, 0, 0};
+                    const int row = 16 * si0 + l16;
+#pragma unroll
+                    for (int h = 0; h < NH; ++h)
+#pragma unroll
+                        for (int s = 0; s < W; ++s) {
+                            const int k = 4 * W * h + W * g + s, o = k * LDU + 16 * sj0 + l16;
+                            const T lr = k < row ? fr[u][h][s] : (k == row ? T(1) : T(0));
+                            const T br = ub1[o];
+                            dr = V::mfma(lr, br, dr);
+                            if constexpr (CX) {
+                                const T li = k < row ? fi[u][h][s] : T(0), bi = ub1[TD_BW * LDU + o];
+                                dr = V::mfma(-li, bi, dr);
+                                di = V::mfma(lr, bi, di);
+                                di = V::mfma(li, br, di);
+                            }
+                        }
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int r = 16 * si0 + V::row(g, i), c = 16 * sj0 + l16, o = r * LDU + c;
+                        ub2[o] = -dr[i];
+                        if constexpr (CX) ub2[TD_BW * LDU + o] = -di[i];
+                        if (c < nbj) {
+                            const unsigned a = cur[32 * K + r] * ldb + jb + c * sizeof(T);
+                            *at(Ar, a) = dr[i];
+                            if constexpr (CX) *at(Ai, a) = di[i];
+                        }
+                    }
+                }
+                if (K + 1 < J) load_inverse(K + 1);
+            }
+            __syncthreads();
+            // tiles behind K: C -= L U
+            T br[NH][W][2], bi[CX ? NH : 1][W][2];
+#pragma unroll
+            for (int h = 0; h < NH; ++h)
+#pragma unroll
+                for (int s = 0; s < W; ++s)
+#pragma unroll
+                    for (int sj = 0; sj < 2; ++sj) {
+                        const int o = (4 * W * h + W * g + s) * LDU + 16 * sj + l16;
+                        br[h][s][sj] = ub2[o];
+                        if constexpr (CX) bi[h][s][sj] = ub2[TD_BW * LDU + o];
+                    }
+#pragma unroll
+            for (int s = 0; s < SLOTS; ++s) {
+                const int t = wv + NW * s;
+                if (t > K && t < nt) {
+                    seg_t lr[2][NH], li[CX ? 2 : 1][CX ? NH : 1];
+#pragma unroll
+                    for (int si = 0; si < 2; ++si)
+#pragma unroll
+                        for (int h = 0; h < NH; ++h) {
+                            const unsigned o = ro[s][si] + 32 * K * sizeof(T) + 64 * h;
+                            lr[si][h] = *(const seg_t *)at(Ar, o);
+                            if constexpr (CX) li[si][h] = *(const seg_t *)at(Ai, o);
+                        }
+#pragma unroll
+                    for (int h = 0; h < NH; ++h)
+#pragma unroll
+                        for (int u = 0; u < W; ++u)
+#pragma unroll
+                            for (int si = 0; si < 2; ++si)
+#pragma unroll
+                                for (int sj = 0; sj < 2; ++sj) {
+                                    ar[s][si][sj] = V::mfma(lr[si][h][u], br[h][u][sj], ar[s][si][sj]);
+                                    if constexpr (CX) {
+                                        ar[s][si][sj] = V::mfma(-li[si][h][u], bi[h][u][sj], ar[s][si][sj]);
+                                        ai[s][si][sj] = V::mfma(lr[si][h][u], bi[h][u][sj], ai[s][si][sj]);
+                                        ai[s][si][sj] = V::mfma(li[si][h][u], br[h][u][sj], ai[s][si][sj]);
+                                    }
+                                }
+                }
+            }
+        }
+        // ---- the block's panels -------------------------------------------------------
+        int lg[RPT];         // position of this thread's rows, relative to the block
+        unsigned open = 0;   // rows that are not pivotal yet
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) {
+            const int r = tid + i * NTH;
+            lg[i] = r;
+            if (r < mr) {
+                open |= 1u << i;
+                rk[r] = -1;
+            }
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int c0 = 16 * h, nb = min(16, nbj - c0);
+            if (nb <= 0) break;
+            __syncthreads();   // the panel region is free
+#pragma unroll
+            for (int s = 0; s < SLOTS; ++s) {
+                const int t = wv + NW * s;
+                if (t >= J && t < nt) {
+#pragma unroll
+                    for (int si = 0; si < 2; ++si)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const int r = 32 * (t - J) + 16 * si + V::row(g, i);
+                            if (r < mr) {
+                                T *q = pan + (r * TD_LS + l16) * P;
+                                q[0] = ar[s][si][h][i];
+                                if constexpr (CX) q[1] = ai[s][si][h][i];
+                            }
+                        }
+                }
+            }
+            __syncthreads();
+            {
+                T xr[RPT][16], xi[CX ? RPT : 1][16];
+#pragma unroll
+                for (int i = 0; i < RPT; ++i) {
+                    const T *q = pan + min(tid + i * NTH, mr - 1) * TD_LS * P;
+#pragma unroll
+                    for (int k = 0; k < 16; ++k) {
+                        xr[i][k] = q[k * P];
+                        if constexpr (CX) xi[i][k] = q[k * P + 1];
+                    }
+                }
+                // columns c .. of a row are x[.][0 ..]: every step shifts by one as it updates.
+                // One barrier per column; no branches but the publishing ones.
+                T *urow = ub1;   // [16][16] pivot rows from their own column on
+                auto columns = [&](auto width, int cb) {
+                    constexpr int WD = decltype(width)::value;
+                    const int ce = min(cb + 4, nb);
+#pragma unroll 1
+                    for (int c = cb; c < ce; ++c) {
+                        const int par = c & 1;
+                        T best = T(-1);
+                        int bi_ = 0;
+#pragma unroll
+                        for (int i = 0; i < RPT; ++i) {
+                            T v = CX ? xr[i][0] * xr[i][0] + xi[CX ? i : 0][0] * xi[CX ? i : 0][0]
+                                     : (xr[i][0] < 0 ? -xr[i][0] : xr[i][0]);
+                            v = v >= T(0) ? v : T(0);   // NaN
+                            const bool better = ((open >> i) & 1u) && v > best;
+                            best = better ? v : best;
+                            bi_ = better ? i : bi_;
+                        }
+                        const T wm = wave_max(best);
+                        const bool cand = lane == __builtin_ctzll(__ballot(best == wm));
+                        // the wavefront's candidate publishes its row
+                        auto publish = [&](T *q, int i) {
+#pragma unroll
+                            for (int k = 0; k < WD; ++k) {
+                                q[k * P] = xr[i][k];
+                                if constexpr (CX) q[k * P + 1] = xi[i][k];
+                            }
+                        };
+#pragma unroll
+                        for (int i = 0; i < RPT; ++i)
+                            if (cand && i == bi_) {
+                                publish(pub[par][wv], i);
+                                wval[par][wv] = wm;
+                                wkey[par][wv] = min(tid + i * NTH, mr - 1) | lg[i] << 16;
+                            }
+                        __syncthreads();
+                        T bv[NW];
+                        int bk[NW];
+#pragma unroll
+                        for (int w = 0; w < NW; ++w) {
+                            bv[w] = wval[par][w];
+                            bk[w] = wkey[par][w] | w << 12;
+                        }
+#pragma unroll
+                        for (int hh = NW / 2; hh > 0; hh /= 2)
+#pragma unroll
+                            for (int w = 0; w < hh; ++w) {
+                                const bool better = bv[w + hh] > bv[w];
+                                bv[w] = better ? bv[w + hh] : bv[w];
+                                bk[w] = better ? bk[w + hh] : bk[w];
+                            }
+                        const int key = __builtin_amdgcn_readfirstlane(bk[0]);
+                        const int R = key & 0xfff, p = key >> 16;
+                        const T *u = pub[par][(key >> 12) & 0xf];
+                        T ur[WD], ui[WD];
+#pragma unroll
+                        for (int k = 0; k < WD; ++k) {
+                            ur[k] = u[k * P];
+                            ui[k] = CX ? u[CX ? k * P + 1 : 0] : T(0);
+                        }
+                        // (the whole row in flight before its first use)
+                        __builtin_amdgcn_sched_barrier(0);
+                        if (tid == 0) {
+                            pl[c0 + c] = R;
+                            rk[R] = c0 + c;
+                            if (info && bv[0] == T(0)) atomicAdd(info, 1);
+                        }
+                        T ir, ii;
+                        reciprocal<T, CX>(ur[0], ui[0], ir, ii);
+                        T lr[RPT], li[RPT];
+#pragma unroll
+                        for (int i = 0; i < RPT; ++i) {
+                            const int r = tid + i * NTH;
+                            const bool op = (open >> i) & 1u, me = op && r == R, upd = op && !me;
+                            T tr, ti;
+                            if constexpr (CX) {
+                                tr = xr[i][0] * ir - xi[i][0] * ii;
+                                ti = xr[i][0] * ii + xi[i][0] * ir;
+                            } else {
+                                tr = xr[i][0] * ir;
+                                ti = T(0);
+                            }
+                            lr[i] = upd ? tr : T(0);
+                            li[i] = upd ? ti : T(0);
+                            // (other rows write their padding entry)
+                            T *q = pan + (min(r, m - 1) * TD_LS + (upd ? c : 16)) * P;
+                            q[0] = lr[i];
+                            if constexpr (CX) q[1] = li[i];
+                            if (me) publish(urow + c * 16 * P, i);
+                            lg[i] = me ? c0 + c : (op && lg[i] == c0 + c ? p : lg[i]);
+                            open = me ? open & ~(1u << i) : open;
+                        }
+                        // (entries beyond the panel are never used; row sets of the
+                        // wavefront past the end are skipped)
+#pragma unroll
+                        for (int i = 0; i < RPT; ++i) {
+                            if (64 * wv + i * NTH >= mr) continue;
+#pragma unroll
+                            for (int k = 1; k < WD; ++k) {
+                                T vr = xr[i][k] - lr[i] * ur[k];
+                                if constexpr (CX) {
+                                    T vi = xi[i][k] - lr[i] * ui[k];
+                                    vr += li[i] * ui[k];
+                                    vi -= li[i] * ur[k];
+                                    xi[i][k - 1] = vi;
+                                }
+                                xr[i][k - 1] = vr;
+                            }
+                        }
+                    }
+                };
+                columns(std::integral_constant<int, 16>{}, 0);
+                if (nb > 4) columns(std::integral_constant<int, 12>{}, 4);
+                if (nb > 8) columns(std::integral_constant<int, 8>{}, 8);
+                if (nb > 12) columns(std::integral_constant<int, 4>{}, 12);
+                __syncthreads();
+                for (int e = tid; e < 256; e += NTH) {
+                    const int c = e >> 4, k = e & 15;
+                    if (c < nb && c + k < 16) {
+                        T *q = pan + (pl[c0 + c] * TD_LS + c + k) * P;
+                        q[0] = urow[(c * 16 + k) * P];
+                        if constexpr (CX) q[1] = urow[(c * 16 + k) * P + 1];
+                    }
+                }
+            }
+            __syncthreads();
+            // the panel to A (rows that became pivots in the first panel hold U here already)
+#pragma unroll 4
+            for (int r = tid >> 4; r < mr; r += NTH / 16) {
+                const int c = tid & 15;
+                if (c < nb && !(h == 1 && rk[r] >= 0 && rk[r] < 16)) {
+                    const unsigned o = cur[j0 + r] * ldb + jb + (c0 + c) * sizeof(T);
+                    *at(Ar, o) = pan[(r * TD_LS + c) * P];
+                    if constexpr (CX) *at(Ai, o) = pan[(r * TD_LS + c) * P + 1];
+                }
+            }
+            // inverses of the panel's triangles (identity beyond nb)
+            if (wv < 2) {
+                T yr[4], yi[4];
+                const T *prow = pan + pl[c0 + min(l16, nb - 1)] * TD_LS * P;
+                auto entry = [&](int i, int k, bool in, T &cr, T &ci) {
+                    const T vr = prow[k * P], vi = CX ? prow[k * P + 1] : T(0);
+                    cr = in && i < nb && k < nb ? vr : T(0);
+                    ci = in && i < nb && k < nb ? vi : T(0);
+                };
+                T *dst;
+                if (wv == 0) {
+                    tri_inverse16<T, CX, false>([&](int i, int k, T &cr, T &ci) { entry(i, k, k < i, cr, ci); }, T(1),
+                                                T(0), yr, yi);
+                    dst = h == 0 ? sI1 : sI2;
+                } else {
+                    T dr, di, rr = T(1), ri = T(0);
+                    entry(l16, l16, true, dr, di);
+                    if (l16 < nb) {
+                        if constexpr (CX) {
+                            const T den = dr * dr + di * di;
+                            rr = dr / den;
+                            ri = -di / den;
+                        } else {
+                            rr = T(1) / dr;
+                        }
+                    }
+                    tri_inverse16<T, CX, true>([&](int i, int k, T &cr, T &ci) { entry(i, k, k > i, cr, ci); }, rr, ri,
+                                               yr, yi);
+                    dst = h == 0 ? sV1 : sV2;
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    T *d = dst + (l16 * TD_LS + 4 * g + q) * P;
+                    d[0] = yr[q];
+                    if constexpr (CX) d[1] = yi[q];
+                }
+            }
+            if (h == 0 && nbj > 16) {
+                // the rest of the block: U12 = L11^{-1} A12, then C -= L21 U12
+                T *u0 = ub1, *u12 = ub2;   // 16 x 16 blocks of row stride TD_LS
+#pragma unroll
+                for (int s = 0; s < SLOTS; ++s) {
+                    const int t = wv + NW * s;
+                    if (t >= J && t < nt) {
+#pragma unroll
+                        for (int si = 0; si < 2; ++si)
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) {
+                                const int r = 32 * (t - J) + 16 * si + V::row(g, i);
+                                const int q = r < mr ? rk[r] : -1;
+                                if (q >= 0) {
+                                    u0[(q * TD_LS + l16) * P] = ar[s][si][1][i];
+                                    if constexpr (CX) u0[(q * TD_LS + l16) * P + 1] = ai[s][si][1][i];
+                                }
+                            }
+                    }
+                }
+                __syncthreads();
+                if (wv == 0) {
+                    acc_t dr = {0, 0, 0, 0}, di = {0, 0, 0, 0};
+                    mm16<T, CX>(sI1, u0, dr, di);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int r = V::row(g, i);
+                        u12[(r * TD_LS + l16) * P] = dr[i];
+                        if constexpr (CX) u12[(r * TD_LS + l16) * P + 1] = di[i];
+                        if (16 + l16 < nbj) {
+                            const unsigned o = cur[j0 + pl[r]] * ldb + jb + (16 + l16) * sizeof(T);
+                            *at(Ar, o) = dr[i];
+                            if constexpr (CX) *at(Ai, o) = di[i];
+                        }
+                    }
+                }
+                __syncthreads();
+                T br[16 / (4 * W)][W], bi[16 / (4 * W)][W];
+#pragma unroll
+                for (int hh = 0; hh < 16 / (4 * W); ++hh)
+#pragma unroll
+                    for (int s = 0; s < W; ++s) {
+                        const T *q = u12 + ((4 * W * hh + W * g + s) * TD_LS + l16) * P;
+                        br[hh][s] = -q[0];
+                        bi[hh][s] = CX ? -q[CX ? 1 : 0] : T(0);
+                    }
+#pragma unroll
+                for (int s = 0; s < SLOTS; ++s) {
+                    const int t = wv + NW * s;
+                    if (t >= J && t < nt) {
+#pragma unroll
+                        for (int si = 0; si < 2; ++si) {
+                            const T *q = pan + min(32 * (t - J) + 16 * si + l16, mr - 1) * TD_LS * P;
+#pragma unroll
+                            for (int hh = 0; hh < 16 / (4 * W); ++hh)
+#pragma unroll
+                                for (int u = 0; u < W; ++u) {
+                                    const int k = 4 * W * hh + W * g + u;
+                                    const T lr = q[k * P];
+                                    ar[s][si][1] = V::mfma(lr, br[hh][u], ar[s][si][1]);
+                                    if constexpr (CX) {
+                                        const T li = q[k * P + 1];
+                                        ar[s][si][1] = V::mfma(-li, bi[hh][u], ar[s][si][1]);
+                                        ai[s][si][1] = V::mfma(lr, bi[hh][u], ai[s][si][1]);
+                                        ai[s][si][1] = V::mfma(li, br[hh][u], ai[s][si][1]);
+                                    }
+                                }
+                        }
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        // ---- the diagonal block: L_JJ^{-1} = [I1; -I2 L21 I1, I2], U_JJ^{-1} =
+        //      [V1, -V1 U12 V2; V2] -------------------------------------------------------
+        if (wv < 2) {
+            // scratch blocks: L21, product of the lower part, product of the upper part
+            T *l21 = ub1, *p1 = ub1 + SB, *p2 = pan;
+            acc_t dr = {0, 0, 0, 0}, di = {0, 0, 0, 0};
+            if (nbj > 16) {
+                if (wv == 0) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int r = 4 * q + g;   // panel row of pivot 16 + r, columns l16
+                        T vr = T(0), vi = T(0);
+                        if (16 + r < nbj) {
+                            const unsigned o = cur[j0 + pl[16 + r]] * ldb + jb + l16 * sizeof(T);
+                            vr = *at(Ar, o);
+                            if constexpr (CX) vi = *at(Ai, o);
+                        }
+                        l21[(r * TD_LS + l16) * P] = vr;
+                        if constexpr (CX) l21[(r * TD_LS + l16) * P + 1] = vi;
+                    }
+                    mm16<T, CX>(l21, sI1, dr, di);
+                } else {
+                    mm16<T, CX>(ub2, sV2, dr, di);
+                }
+                T *pp = wv == 0 ? p1 : p2;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    pp[(V::row(g, i) * TD_LS + l16) * P] = -dr[i];
+                    if constexpr (CX) pp[(V::row(g, i) * TD_LS + l16) * P + 1] = -di[i];
+                }
+                dr = acc_t{0, 0, 0, 0};
+                di = acc_t{0, 0, 0, 0};
+                if (wv == 0) mm16<T, CX>(sI2, p1, dr, di);
+                else mm16<T, CX>(sV1, p2, dr, di);
+            }
+            // wavefront 0: strict lower part, wavefront 1: upper triangle
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                const T *src = wv == 0 ? (b ? sI2 : sI1) : (b ? sV2 : sV1);
+                for (int q = 0; q < 4; ++q) {
+                    const int r = 4 * q + g, c = l16;
+                    const bool in = wv == 0 ? c < r : c >= r;
+                    if (in && 16 * b + r < nbj && 16 * b + c < nbj) {
+                        const unsigned o = cur[j0 + pl[16 * b + r]] * ldb + jb + (16 * b + c) * sizeof(T);
+                        *at(Ar, o) = src[(r * TD_LS + c) * P];
+                        if constexpr (CX) *at(Ai, o) = src[(r * TD_LS + c) * P + 1];
+                    }
+                }
+            }
+            if (nbj > 16) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int r = V::row(g, i) + (wv == 0 ? 16 : 0), c = l16 + (wv == 0 ? 0 : 16);
+                    if (r < nbj && c < nbj) {
+                        const unsigned o = cur[j0 + pl[r]] * ldb + jb + c * sizeof(T);
+                        *at(Ar, o) = dr[i];
+                        if constexpr (CX) *at(Ai, o) = di[i];
+                    }
+                }
+            }
+        }
+        // ---- positions after the block's interchanges --------------------------------------
+        int row[RPT];
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) row[i] = cur[j0 + min(tid + i * NTH, mr - 1)];
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < RPT; ++i)
+            if (tid + i * NTH < mr) cur[j0 + lg[i]] = row[i];
+        __syncthreads();
+    }
+    for (int p = tid; p < m; p += NTH) perm[p] = cur[p];
+}
+
+// ---------------------------------------------------------------------------
+// sweeps: one patch per workgroup
+// ---------------------------------------------------------------------------
+constexpr int TDS_THREADS = 256;   // 32 rows x 8 lanes
+
+// four consecutive factor entries of a row
+template <typename TP, typename TF> struct Quad {
+    TP v[4];
+    __device__ __forceinline__ void load(const TF *p)
+    {
+        if constexpr (std::is_same<TF, unsigned short>::value) {
+            typedef unsigned short u16x4 __attribute__((ext_vector_type(4), aligned(2)));
+            const u16x4 q = *(const u16x4 *)p;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = __uint_as_float((unsigned)q[i] << 16);
+        } else {
+            typedef TF seg __attribute__((ext_vector_type(16 / sizeof(TF)), aligned(sizeof(TF))));
+            constexpr int W = 16 / sizeof(TF);
+#pragma unroll
+            for (int h = 0; h < 4 / W; ++h) {
+                const seg q = *(const seg *)(p + W * h);
+#pragma unroll
+                for (int i = 0; i < W; ++i) v[W * h + i] = q[i];
+            }
+        }
+    }
+    // columns c .. c+3 of a row of MS entries; entries past its end repeat the
+    // last one (their unknowns are zero)
+    __device__ __forceinline__ void load_edge(const TF *row, int c, int MS)
+    {
+        if (c + 4 <= MS) {
+            load(row + c);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const TF q = row[min(c + i, MS - 1)];
+                if constexpr (std::is_same<TF, unsigned short>::value) v[i] = __uint_as_float((unsigned)q << 16);
+                else v[i] = q;
+            }
+        }
+    }
+};
+
+// sum over the 8 lanes of a row group, in every lane (fixed order)
+template <typename T> __device__ __forceinline__ T sum8(T x)
+{
+    x += dpp<0xB1, 0xf>(x);    // quad_perm 1,0,3,2
+    x += dpp<0x4E, 0xf>(x);    // quad_perm 2,3,0,1
+    x += dpp<0x141, 0xf>(x);   // row_half_mirror
+    return x;
+}
+
+// Substitutions with the factors of lu_td_kernel, b (br, bi, NB blocks of 32,
+// zero padded) in LDS, overwritten.  Bound by the read of the factors where
+// there are enough of them (r = 3, 13824 cells: 4.2 -> 3.3 ms, 5.3 TB/s; a
+// device copy reaches 5.2), by the chain of block rows below (r = 1, 4096
+// cells: 145 -> 62 us; before, each diagonal block was substituted by one
+// wavefront, 32 dependent steps).  Per block of 32 rows: the products with
+// the solved blocks (8 lanes per row, 16 bytes per lane and block: every row
+// segment is a whole 128-byte line in FP32), then the inverse diagonal block.
+// The factors depend on nothing, so a batch of UB column blocks is in flight
+// per thread and, up to three blocks (SMALL), the whole matrix before the
+// first product.
+template <typename TP, typename TF, bool CX, int MS, int LDM>
+__device__ __forceinline__ void td_substitute(const TF *__restrict__ Lr, const TF *__restrict__ Li, const int *perm,
+                                              TP *br, TP *bi, TP *tr, TP *ti)
+{
+    constexpr int NB = (MS + 31) / 32, UB = sizeof(TP) == 8 ? 2 : 4;
+    const int tid = threadIdx.x, rr = tid >> 3, q4 = (tid & 7) * 4;
+    using Q = Quad<TP, TF>;
+    // s -= (or +=) row segment . x
+    auto dot = [&](const Q &ar, const Q &ai, const TP *xr, const TP *xi, TP &sr, TP &si) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if constexpr (CX) {
+                sr += ar.v[e] * xr[e];
+                sr -= ai.v[e] * xi[e];
+                si += ar.v[e] * xi[e];
+                si += ai.v[e] * xr[e];
+            } else {
+                sr += ar.v[e] * xr[e];
+            }
+        }
+    };
+    // the diagonal block: x_I = D^{-1} t (strictly lower with unit diagonal, or
+    // upper), t = b_I - sums
+    auto finish = [&](int I, bool lower, Q dr, Q di, TP sr, TP si) {
+        sr = sum8(sr);
+        if constexpr (CX) si = sum8(si);
+        const int row = 32 * I + rr;
+        if (q4 == 0) {
+            // (rows past the end stay zero: the edge columns multiply them)
+            tr[rr] = row < MS ? br[row] - sr : TP(0);
+            if constexpr (CX) ti[rr] = row < MS ? bi[row] - si : TP(0);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const bool in = lower ? q4 + e < rr : q4 + e >= rr;
+            dr.v[e] = in ? dr.v[e] : TP(0);
+            di.v[e] = in ? di.v[e] : TP(0);
+        }
+        __syncthreads();
+        TP yr = 0, yi = 0;
+        dot(dr, di, tr + q4, ti + q4, yr, yi);
+        yr = sum8(yr);
+        if constexpr (CX) yi = sum8(yi);
+        if (q4 == 0 && row < MS) {
+            br[row] = lower ? yr + tr[rr] : yr;
+            if constexpr (CX) bi[row] = lower ? yi + ti[rr] : yi;
+        }
+        __syncthreads();
+    };
+    if constexpr (NB <= 3 && NB * NB * (CX ? 2 : 1) * sizeof(TP) <= 72) {
+        Q fr[NB][NB], fi[CX ? NB : 1][CX ? NB : 1];
+#pragma unroll
+        for (int I = 0; I < NB; ++I) {
+            const int o = perm[min(32 * I + rr, MS - 1)] * LDM;
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                fr[I][j].load_edge(Lr + o, 32 * j + q4, MS);
+                if constexpr (CX) fi[I][j].load_edge(Li + o, 32 * j + q4, MS);
+            }
+        }
+#pragma unroll
+        for (int I = 0; I < NB; ++I) {
+            TP sr = 0, si = 0;
+#pragma unroll
+            for (int j = 0; j < I; ++j)
+                dot(fr[I][j], fi[CX ? I : 0][CX ? j : 0], br + 32 * j + q4, bi + 32 * j + q4, sr, si);
+            finish(I, true, fr[I][I], fi[CX ? I : 0][CX ? I : 0], sr, si);
+        }
+#pragma unroll
+        for (int I = NB - 1; I >= 0; --I) {
+            TP sr = 0, si = 0;
+#pragma unroll
+            for (int j = I + 1; j < NB; ++j)
+                dot(fr[I][j], fi[CX ? I : 0][CX ? j : 0], br + 32 * j + q4, bi + 32 * j + q4, sr, si);
+            finish(I, false, fr[I][I], fi[CX ? I : 0][CX ? I : 0], sr, si);
+        }
+    } else {
+        // products with the column blocks [j0, j1) of one block row
+        auto products = [&](int o, int j0, int j1, TP &sr, TP &si) {
+#pragma unroll 1
+            for (int jb = j0; jb < j1; jb += UB) {
+                Q ar[UB], ai[CX ? UB : 1];
+#pragma unroll
+                for (int u = 0; u < UB; ++u) {
+                    // (blocks past the range reload the last one against zero)
+                    const int j = min(jb + u, j1 - 1);
+                    ar[u].load_edge(Lr + o, 32 * j + q4, MS);
+                    if constexpr (CX) ai[u].load_edge(Li + o, 32 * j + q4, MS);
+                }
+#pragma unroll
+                for (int u = 0; u < UB; ++u)
+                    if (jb + u < j1)
+                        dot(ar[u], ai[CX ? u : 0], br + 32 * (jb + u) + q4, bi + 32 * (jb + u) + q4, sr, si);
+            }
+        };
+#pragma unroll 1
+        for (int I = 0; I < NB; ++I) {
+            const int o = perm[min(32 * I + rr, MS - 1)] * LDM;
+            Q dr, di;
+            dr.load_edge(Lr + o, 32 * I + q4, MS);
+            if constexpr (CX) di.load_edge(Li + o, 32 * I + q4, MS);
+            else di = dr;
+            TP sr = 0, si = 0;
+            products(o, 0, I, sr, si);
+            finish(I, true, dr, di, sr, si);
+        }
+#pragma unroll 1
+        for (int I = NB - 1; I >= 0; --I) {
+            const int o = perm[min(32 * I + rr, MS - 1)] * LDM;
+            Q dr, di;
+            dr.load_edge(Lr + o, 32 * I + q4, MS);
+            if constexpr (CX) di.load_edge(Li + o, 32 * I + q4, MS);
+            else di = dr;
+            TP sr = 0, si = 0;
+            products(o, I + 1, NB, sr, si);
+            finish(I, false, dr, di, sr, si);
+        }
+    }
+}
+
+template <int DIM, int R> struct TdSize {
+    static constexpr int N1 = R + 2;
+    static constexpr int NL = DIM == 2 ? N1 * N1 : N1 * N1 * N1;
+    static constexpr int NPM = DIM == 2 ? (R + 1) * (R + 2) / 2 : (R + 1) * (R + 2) * (R + 3) / 6;
+    static constexpr int NV = DIM * NL, MS = NV + NPM, MSP = (MS + 31) & ~31;
+};
+
+// one time-decoupled patch solve per cell: gather the patch defect of all
+// time nodes, per eigen-system transform (with the row permutation of the
+// factors), substitute, transform back; velocity to the cell buffer E, pressure
+// updated in place (pressure unknowns belong to one cell)
+template <int DIM, int R, typename T, typename TP, typename TF>
+__global__ void __launch_bounds__(TDS_THREADS, sizeof(TP) == 8 ? 2 : 4) solve_td_kernel(SolveTdArgs<T, TP, TF> A)
+{
+    using Z = TdSize<DIM, R>;
+    constexpr int N1 = Z::N1, NL = Z::NL, NPM = Z::NPM, NV = Z::NV, MS = Z::MS, MSP = Z::MSP;
+    constexpr int LDM = td_ld(MS);
+    constexpr long long MAT = (long long)MS * LDM;
+    extern __shared__ unsigned char lds_raw[];
+    const int nt = A.nt;
+    TP *br = reinterpret_cast<TP *>(lds_raw), *bi = br + MSP, *tr = bi + MSP, *ti = tr + 32;
+    TP *rl = ti + 32;                           // [nt][MSP] patch defect
+    TP *out = rl + nt * MSP;                    // [nt][MSP] patch correction
+    int *perm = reinterpret_cast<int *>(out + nt * MSP);   // [MSP]
+    const int cell = xcd_cell(blockIdx.x, gridDim.x), tid = threadIdx.x;
+    const int c0 = cell % A.n0, c1 = (cell / A.n0) % A.n1, c2 = DIM == 3 ? cell / (A.n0 * A.n1) : 0;
+    const long long N0 = (long long)(R + 1) * A.n0 + 1, N1g = (long long)(R + 1) * A.n1 + 1;
+    const long long pbase = (long long)nt * A.Nv1;
+    for (int j = tid; j < MS; j += TDS_THREADS) {
+        perm[j] = A.perm[0][(long long)cell * MS + j];
+        long long g, st;
+        if (j < NV) {
+            const int l = j % NL, c = j / NL;
+            const int i0 = l % N1, i1 = (l / N1) % N1, i2 = DIM == 3 ? l / (N1 * N1) : 0;
+            g = c * A.Nn +
+                (((long long)(R + 1) * c0 + i0) + N0 * (((long long)(R + 1) * c1 + i1) + N1g * ((long long)(R + 1) * c2 + i2)));
+            st = A.Nv1;
+        } else {
+            g = pbase + (long long)cell * NPM + (j - NV);
+            st = A.Np1;
+        }
+        for (int a = 0; a < nt; ++a) {
+            rl[a * MSP + j] = (TP)A.defect[g + a * st];
+            out[a * MSP + j] = TP(0);
+        }
+    }
+    __syncthreads();
+    for (int s = 0; s < A.nsys; ++s) {
+        const bool cx = A.cplx[s] != 0;
+        if (s > 0) {
+            for (int i = tid; i < MS; i += TDS_THREADS) perm[i] = A.perm[s][(long long)cell * MS + i];
+            __syncthreads();
+        }
+        for (int i = tid; i < MSP; i += TDS_THREADS) {
+            TP sr = 0, si = 0;
+            if (i < MS) {
+                const int src = perm[i];
+                for (int a = 0; a < nt; ++a) {
+                    sr += A.Tre[s * 4 + a] * rl[a * MSP + src];
+                    si += A.Tim[s * 4 + a] * rl[a * MSP + src];
+                }
+            }
+            br[i] = sr;
+            bi[i] = si;
+        }
+        __syncthreads();
+        const TF *LU = A.sys[s] + (long long)cell * (cx ? 2 : 1) * MAT;
+        if (cx) td_substitute<TP, TF, true, MS, LDM>(LU, LU + MAT, perm, br, bi, tr, ti);
+        else td_substitute<TP, TF, false, MS, LDM>(LU, LU, perm, br, bi, tr, ti);
+        for (int j = tid; j < MS; j += TDS_THREADS)
+            for (int a = 0; a < nt; ++a) {
+                TP v = A.Fre[a * 4 + s] * br[j];
+                if (cx) v -= A.Fim[a * 4 + s] * bi[j];
+                out[a * MSP + j] += v;
+            }
+        __syncthreads();
+    }
+    T *Ec = A.E + (long long)cell * nt * NV;
+    for (int j = tid; j < MS; j += TDS_THREADS)
+        for (int a = 0; a < nt; ++a) {
+            if (j < NV) Ec[a * NV + j] = (T)out[a * MSP + j];
+            else A.d[pbase + a * A.Np1 + (long long)cell * NPM + (j - NV)] += A.omega * (T)out[a * MSP + j];
+        }
+}
+
+} // namespace
+
+// Workgroup shapes, by the row tiles that the accumulators hold (32 rows and
+// 32 columns each: 16 registers per lane and plane in FP32, 32 in FP64, of 256):
+// two workgroups of 4 wavefronts per CU share it best (FP32 complex m = 395,
+// 4096 matrices: 13.9 ms, 17.0 ms with one of 8 wavefronts); up to 128 rows 2
+// wavefronts (cheaper barriers: 8192 of m = 85 in 1.2 instead of 1.6 ms); FP64
+// complex tiles need 8 wavefronts from 129 rows on.
+template <typename T>
+hipError_t launch_lu_td(T *A, int *perm, int m, int ld, bool cplx, int batch, int *info, hipStream_t s)
+{
+    if (batch <= 0) return hipSuccess;
+    const long long st = (long long)(cplx ? 2 : 1) * m * ld;
+#define LTD(CX, NW, SLOTS, RPT)                                                                                        \
+    {                                                                                                                  \
+        static_assert(SLOTS <= 2 * RPT, "panel rows cover the tiles");                                                 \
+        const size_t bytes = td_lu_lds_bytes<T, CX>(m);                                                                \
+        hipError_t e = lds_attr((const void *)lu_td_kernel<T, CX, NW, SLOTS, RPT>, bytes);                             \
+        if (e != hipSuccess) return e;                                                                                 \
+        hipLaunchKernelGGL((lu_td_kernel<T, CX, NW, SLOTS, RPT>), dim3(batch), dim3(64 * NW), bytes, s, A, perm, m,    \
+                           ld, st, info);                                                                              \
+        return hipGetLastError();                                                                                      \
+    }
+    constexpr bool wide = sizeof(T) == 8;
+    if (m < 17 || m > 512) return hipErrorInvalidValue;
+    if (cplx) {
+        if constexpr (wide) {
+            if (m <= 128) LTD(true, 4, 1, 1)
+            if (m <= 256) LTD(true, 8, 1, 1)
+            LTD(true, 8, 2, 1)
+        } else {
+            if (m <= 128) LTD(true, 2, 2, 1)
+            if (m <= 256) LTD(true, 4, 2, 1)
+            LTD(true, 4, 4, 2)
+        }
+    }
+    if (m <= 128) LTD(false, 2, 2, 1)
+    if (m <= 256) LTD(false, 4, 2, 1)
+    LTD(false, 4, 4, 2)
+#undef LTD
+}
+
+template <typename T, typename TP, typename TF>
+hipError_t launch_solve_td(int dim, int r, const SolveTdArgs<T, TP, TF> &a, int ncell, hipStream_t s)
+{
+#define SC(D, RR)                                                                                                      \
+    if (dim == D && r == RR) {                                                                                         \
+        constexpr size_t msp = TdSize<D, RR>::MSP;                                                                     \
+        const size_t bytes = ((2 + 2 * (size_t)a.nt) * msp + 64) * sizeof(TP) + msp * sizeof(int);                     \
+        hipError_t e = lds_attr((const void *)solve_td_kernel<D, RR, T, TP, TF>, bytes);                               \
+        if (e != hipSuccess) return e;                                                                                 \
+        hipLaunchKernelGGL((solve_td_kernel<D, RR, T, TP, TF>), dim3(ncell), dim3(TDS_THREADS), bytes, s, a);         \
+        return hipGetLastError();                                                                                      \
+    }
+    SC(2, 1) SC(2, 2) SC(2, 3) SC(3, 1) SC(3, 2) SC(3, 3)
+#undef SC
+    return hipErrorInvalidValue;
+}
+
+template hipError_t launch_lu_td<double>(double *, int *, int, int, bool, int, int *, hipStream_t);
+template hipError_t launch_lu_td<float>(float *, int *, int, int, bool, int, int *, hipStream_t);
+template hipError_t launch_solve_td(int, int, const SolveTdArgs<double, double, double> &, int, hipStream_t);
+template hipError_t launch_solve_td(int, int, const SolveTdArgs<float, float, float> &, int, hipStream_t);
+template hipError_t launch_solve_td(int, int, const SolveTdArgs<float, float, unsigned short> &, int, hipStream_t);
+
+} // namespace stmg

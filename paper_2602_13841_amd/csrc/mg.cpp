@@ -213,7 +213,6 @@ void mg_allocate(stmg_ctx *ctx)
             M.nfac = off;
             M.patches.alloc((size_t)off * w);
             const size_t ib = (size_t)M.tdg.nsys * L.ncell * ms * 4;
-            M.piv.alloc(ib);
             M.perm.alloc(ib);
             if (mg.diag) {
                 const int nv = mg.diag_block ? L.nl * L.dim * L.dim : L.dim * L.nl, npm = L.npm, ns = M.tdg.nsys;
@@ -388,19 +387,9 @@ template <typename T> static void rebuild_level(stmg_ctx *ctx, MgLevel &M, size_
         }
         {
             TimerScope ts(&ctx->timers, "vanka_lu", s);
-            for (int sy = 0; sy < M.tdg.nsys; ++sy) {
-                T *A = M.patches.as<T>() + M.sys_off[sy];
-                int *pv = M.piv.as<int>() + M.piv_off[sy];
-                if (M.tdg.cplx[sy])
-                    STMG_HIP(launch_lu_c<T>(A, pv, M.ms, (int)ld, 2 * mat, (int)L.ncell, M.info.as<int>(), max_lds, s));
-                else {
-                    LuBatch vb{};
-                    vb.uniform_m = M.ms;
-                    vb.uniform_ld = (int)ld;
-                    STMG_HIP(launch_lu<T>(A, pv, M.ms, (int)L.ncell, M.info.as<int>(), max_lds, s, &vb));
-                }
-            }
-            STMG_HIP(launch_piv_to_perm(M.piv.as<int>(), M.perm.as<int>(), M.ms, (long long)M.tdg.nsys * L.ncell, s));
+            for (int sy = 0; sy < M.tdg.nsys; ++sy)
+                STMG_HIP(launch_lu_td<T>(M.patches.as<T>() + M.sys_off[sy], M.perm.as<int>() + M.piv_off[sy], M.ms, (int)ld,
+                                         M.tdg.cplx[sy] != 0, (int)L.ncell, M.info.as<int>(), s));
             if constexpr (std::is_same<T, float>::value) {
                 if (ctx->mg->factor_bf16) {
                     // the sweeps read a BF16 copy of the factors (half the bytes)
@@ -528,7 +517,7 @@ template <typename T> void mg_smooth(stmg_ctx *ctx, int l, const T *r, T *d, boo
             sb.E = M.E.as<float>();
             sb.d = d;
             sb.omega = (float)mg.omega;
-            STMG_HIP(launch_solve_td_bf16(L.dim, L.r, sb, (int)L.ncell, M.ms, s));
+            STMG_HIP((launch_solve_td<float, float, unsigned short>(L.dim, L.r, sb, (int)L.ncell, s)));
             applied = true;
         }
     }
@@ -559,7 +548,7 @@ template <typename T> void mg_smooth(stmg_ctx *ctx, int l, const T *r, T *d, boo
         sa.E = M.E.as<T>();
         sa.d = d;
         sa.omega = (T)mg.omega;
-        STMG_HIP((launch_solve_td<T, T>(L.dim, L.r, sa, (int)L.ncell, M.ms, s)));
+        STMG_HIP((launch_solve_td<T, T, T>(L.dim, L.r, sa, (int)L.ncell, s)));
     } else {
         SolveArgs<T, T> sa{};
         sa.n0 = L.n[0];

@@ -65,7 +65,7 @@ template <typename T, typename TP, typename TF = TP> struct SolveTdArgs {
     const T *defect;
     int nsys;
     int cplx[4];
-    const TF *sys[4];      // LU factors per system
+    const TF *sys[4];      // factors per system (launch_lu_td)
     const int *perm[4];    // row permutation per system: [cell][ms]
     TP Tre[16], Tim[16];   // [s * 4 + a]
     TP Fre[16], Fim[16];   // [a * 4 + s]
@@ -126,17 +126,19 @@ template <typename T, typename TP>
 hipError_t launch_solve(int dim, int r, const SolveArgs<T, TP> &a, int ncell, int m, hipStream_t s);
 template <typename TE, typename TP>
 hipError_t launch_patch_td(int dim, int r, const PatchTdArgs<TE, TP> &a, int ncell, hipStream_t s);
-// batched complex LU: matrix b at A + b * a_stride (real plane, imaginary plane)
+// Time-decoupled patch systems (lu_td.hip): LU with partial pivoting of a batch
+// of m x m matrices (17 <= m <= 512, row stride ld; cplx: planar, real plane
+// then imaginary plane), rows in place: position p of the permuted matrix is
+// stored row perm[p].  Diagonal blocks of 32 hold the inverses of their
+// triangles (strict lower part: L^{-1}, upper triangle: U^{-1}).
 template <typename T>
-hipError_t launch_lu_c(T *A, int *piv, int m, int ld, long long a_stride, int batch, int *info, size_t max_lds,
-                       hipStream_t s);
-hipError_t launch_piv_to_perm(const int *piv, int *perm, int m, long long nmat, hipStream_t s);
-size_t solve_td_lds_bytes(int ms, int nt, size_t word);
-template <typename T, typename TP>
-hipError_t launch_solve_td(int dim, int r, const SolveTdArgs<T, TP> &a, int ncell, int ms, hipStream_t s);
-// the same with BF16-stored FP32 factors
-hipError_t launch_solve_td_bf16(int dim, int r, const SolveTdArgs<float, float, unsigned short> &a, int ncell, int ms,
-                                hipStream_t s);
+hipError_t launch_lu_td(T *A, int *perm, int m, int ld, bool cplx, int batch, int *info, hipStream_t s);
+// one sweep's patch solves with those factors
+template <typename T, typename TP, typename TF>
+hipError_t launch_solve_td(int dim, int r, const SolveTdArgs<T, TP, TF> &a, int ncell, hipStream_t s);
+// dynamic-LDS limit of a kernel, raised only when a launch needs more than
+// any earlier one (keeps driver calls out of replayed or captured launches)
+hipError_t lds_attr(const void *kern, size_t bytes);
 // FP32 -> BF16 bits (round to nearest even), n elements
 hipError_t launch_pack_bf16(const float *src, unsigned short *dst, long long n, hipStream_t s);
 

@@ -55,12 +55,6 @@ __device__ __forceinline__ short bf16_rne(float f)
     return (short)(u >> 16);
 }
 
-// load one stored factor entry as T (unsigned short: BF16 bits, exact widening)
-template <typename T, typename TF> __device__ __forceinline__ T ld_factor(const TF *p)
-{
-    if constexpr (std::is_same<TF, unsigned short>::value) return (T)__uint_as_float((unsigned)(*p) << 16);
-    else return (T)(*p);
-}
 typedef double doublex4_t __attribute__((ext_vector_type(4)));
 
 // 16 x 16 x 4 matrix FMA per precision (v_mfma_f32_16x16x4f32 /
@@ -906,15 +900,6 @@ constexpr int LU_NBO_MIN_M = 192; // larger matrices: outer blocks of LU_CB colu
 // (32-column panels stay on one level: their register arrays leave no room
 // for the code of the second level)
 __host__ __device__ constexpr int lu_outer_block(int m, int nb) { return m > LU_NBO_MIN_M && nb < 32 ? LU_CB : nb; }
-constexpr int LU_CBD = 32;       // column block of the complex once-per-block update
-constexpr int LU_C2_ROWS = 4;    // panel rows per thread of lu_kernel_c2 (m <= LU_C2_ROWS LU_THREADS)
-// words per plane of the complex U block: the panels' [NB][LU_CB] and the
-// outer block's [nbo][LU_CBD]
-__host__ __device__ constexpr int lu_c_u_words(int nb, int nbo)
-{
-    return nb * LU_CB > nbo * LU_CBD ? nb * LU_CB : nbo * LU_CBD;
-}
-
 
 // trailing update A22 -= L21 U12 of one column block, FP32 on MFMA
 // (v_mfma_f32_16x16x4f32: A lane l -> (row l%16, k l/16), B lane l ->
@@ -1418,28 +1403,26 @@ __global__ void __launch_bounds__(NTH) lu_queue_kernel(T *__restrict__ Aall, int
 constexpr int SV_THREADS = 256;
 
 // b[r] -= L[r, kb:kb+nbk] . b[kb:kb+nbk] for rows r in [rbeg, rend) of a
-// row-major factor with row stride ld (complex planar when CX: Lr/Li and br/bi), nbk <= KB.
-// One 16-lane group per row, KB/16 columns per lane; each group keeps RU rows of
-// loads in flight before it reduces, so a pass over the rows costs about one
-// memory latency instead of one per row.  Per row the summation order is
-// fixed: columns l16, l16+16, ..., then a 16-lane xor tree.
-template <typename T, bool CX, int KB = 64, int RU = 4, typename TF = T>
-__device__ __forceinline__ void block_gemv_update(const TF *__restrict__ Lr, const TF *__restrict__ Li, int ld, int kb,
-                                                  int nbk, int rbeg, int rend, T *br, T *bi)
+// row-major factor with row stride ld, nbk <= KB.  One 16-lane group per row,
+// KB/16 columns per lane; each group keeps RU rows of loads in flight before it
+// reduces, so a pass over the rows costs about one memory latency instead of
+// one per row.  Per row the summation order is fixed: columns l16, l16+16, ...,
+// then a 16-lane xor tree.
+template <typename T, int KB = 64, int RU = 4>
+__device__ __forceinline__ void block_gemv_update(const T *__restrict__ L, int ld, int kb, int nbk, int rbeg, int rend,
+                                                  T *b)
 {
     constexpr int NG = SV_THREADS / 16, CPL = KB / 16;   // columns per lane
     const int tid = threadIdx.x, g = tid >> 4, l16 = tid & 15;
-    T xr[CPL], xi[CPL];
+    T x[CPL];
 #pragma unroll
     for (int i = 0; i < CPL; ++i) {
         const int c = l16 + 16 * i;
-        const bool ok = c < nbk;
-        xr[i] = ok ? br[kb + c] : T(0);
-        xi[i] = CX && ok ? bi[kb + c] : T(0);
+        x[i] = c < nbk ? b[kb + c] : T(0);
     }
 #pragma unroll 1
     for (int r0 = rbeg + g; r0 < rend; r0 += RU * NG) {
-        T lr[RU][CPL], li[RU][CPL];
+        T l[RU][CPL];
 #pragma unroll
         for (int u = 0; u < RU; ++u) {
             // unconditional loads from a clamped in-range address, then a
@@ -1449,45 +1432,24 @@ __device__ __forceinline__ void block_gemv_update(const TF *__restrict__ Lr, con
 #pragma unroll
             for (int i = 0; i < CPL; ++i) {
                 const int c = l16 + 16 * i;
-                const bool ok = r < rend && c < nbk;
-                const long long oc = o + min(c, nbk - 1);
-                const T vr = ld_factor<T>(Lr + oc);
-                lr[u][i] = ok ? vr : T(0);
-                if constexpr (CX) {
-                    const T vi = ld_factor<T>(Li + oc);
-                    li[u][i] = ok ? vi : T(0);
-                } else {
-                    li[u][i] = T(0);
-                }
+                const T v = L[o + min(c, nbk - 1)];
+                l[u][i] = r < rend && c < nbk ? v : T(0);
             }
         }
 #pragma unroll
         for (int u = 0; u < RU; ++u) {
-            T sr = 0, si = 0;
+            T s = 0;
 #pragma unroll
-            for (int i = 0; i < CPL; ++i) {
-                if constexpr (CX) {
-                    sr += lr[u][i] * xr[i] - li[u][i] * xi[i];
-                    si += lr[u][i] * xi[i] + li[u][i] * xr[i];
-                } else {
-                    sr += lr[u][i] * xr[i];
-                }
-            }
-            for (int off = 8; off > 0; off >>= 1) {
-                sr += __shfl_xor(sr, off, 16);
-                if constexpr (CX) si += __shfl_xor(si, off, 16);
-            }
+            for (int i = 0; i < CPL; ++i) s += l[u][i] * x[i];
+            for (int off = 8; off > 0; off >>= 1) s += __shfl_xor(s, off, 16);
             const int r = r0 + u * NG;
-            if (l16 == 0 && r < rend) {
-                br[r] -= sr;
-                if constexpr (CX) bi[r] -= si;
-            }
+            if (l16 == 0 && r < rend) b[r] -= s;
         }
     }
 }
 
-template <typename T, int KB = 64, typename TF = T>
-__device__ __forceinline__ void lu_substitute(const TF *__restrict__ LU, int m, int ld, T *b, T *dblk)
+template <typename T, int KB = 64>
+__device__ __forceinline__ void lu_substitute(const T *__restrict__ LU, int m, int ld, T *b, T *dblk)
 {
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int g = tid >> 4, l16 = tid & 15;
@@ -1496,7 +1458,7 @@ __device__ __forceinline__ void lu_substitute(const TF *__restrict__ LU, int m, 
         const int nbk = min(KB, m - kb);
         for (int e = tid; e < nbk * KB; e += SV_THREADS) {
             int i = e / KB, j = e % KB;
-            if (j < nbk) dblk[i * (KB + 1) + j] = ld_factor<T>(LU + (long long)(kb + i) * ld + kb + j);
+            if (j < nbk) dblk[i * (KB + 1) + j] = LU[(long long)(kb + i) * ld + kb + j];
         }
         __syncthreads();
         if (wv == 0) {
@@ -1508,7 +1470,7 @@ __device__ __forceinline__ void lu_substitute(const TF *__restrict__ LU, int m, 
             if (lane < nbk) b[kb + lane] = y;
         }
         __syncthreads();
-        block_gemv_update<T, false, KB, 4, TF>(LU, (const TF *)nullptr, ld, kb, nbk, kb + nbk, m, b, nullptr);
+        block_gemv_update<T, KB>(LU, ld, kb, nbk, kb + nbk, m, b);
         __syncthreads();
     }
     // backward: upper with diagonal
@@ -1517,7 +1479,7 @@ __device__ __forceinline__ void lu_substitute(const TF *__restrict__ LU, int m, 
         const int kb = bk * KB, nbk = min(KB, m - kb);
         for (int e = tid; e < nbk * KB; e += SV_THREADS) {
             int i = e / KB, j = e % KB;
-            if (j < nbk) dblk[i * (KB + 1) + j] = ld_factor<T>(LU + (long long)(kb + i) * ld + kb + j);
+            if (j < nbk) dblk[i * (KB + 1) + j] = LU[(long long)(kb + i) * ld + kb + j];
         }
         __syncthreads();
         if (wv == 0) {
@@ -1530,7 +1492,7 @@ __device__ __forceinline__ void lu_substitute(const TF *__restrict__ LU, int m, 
             if (lane < nbk) b[kb + lane] = x;
         }
         __syncthreads();
-        block_gemv_update<T, false, KB, 4, TF>(LU, (const TF *)nullptr, ld, kb, nbk, 0, kb, b, nullptr);
+        block_gemv_update<T, KB>(LU, ld, kb, nbk, 0, kb, b);
         __syncthreads();
     }
 }
@@ -1662,921 +1624,6 @@ __global__ void __launch_bounds__(256) patch_td_kernel(PatchTdArgs<TE, TP> A)
             o[0] = (TP)(A.lre[s] * mv + lv);
             if (A.cplx[s]) o[MAT] = (TP)(A.lim[s] * mv);
         }
-    }
-}
-
-// complex trailing update C -= L21 U12 of one column block (planar), FP32 on
-// MFMA: four real products per k step
-template <int NBP>
-__device__ __forceinline__ void trailing_update_c(float *Ar, float *Ai, int m, int ld, int j0, int nb, int cb, int ncb,
-                                                  const float *pr, const float *pi, const float *ur, const float *ui)
-{
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int r0 = j0 + nb;
-    const int nrt = (m - r0 + 31) / 32, nct = (ncb + 31) / 32, ntile = nrt * nct;
-    // the next tile's C block (both planes) is loaded before the current one
-    // is computed (tiles are disjoint)
-    auto load = [&](int t, floatx4_t (&xr)[2][2], floatx4_t (&xi)[2][2]) {
-        const int R = r0 + 32 * (t / nct), C = cb + 32 * (t % nct);
-#pragma unroll
-        for (int si = 0; si < 2; ++si)
-#pragma unroll
-            for (int sj = 0; sj < 2; ++sj)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int row = R + 16 * si + 4 * (lane >> 4) + i, col = C + 16 * sj + (lane & 15);
-                    const bool ok = row < m && col < cb + ncb;
-                    xr[si][sj][i] = ok ? Ar[(long long)row * ld + col] : 0.0f;
-                    xi[si][sj][i] = ok ? Ai[(long long)row * ld + col] : 0.0f;
-                }
-    };
-    floatx4_t cr[2][2], ci[2][2], nr[2][2], ni[2][2];
-    if (wv < ntile) load(wv, cr, ci);
-    for (int t = wv; t < ntile; t += LU_THREADS / 64) {
-        const int R = r0 + 32 * (t / nct), C = cb + 32 * (t % nct);
-        const int tn = t + LU_THREADS / 64;
-        if (tn < ntile) load(tn, nr, ni);
-        for (int k0 = 0; k0 < nb; k0 += 4) {
-            const int k = k0 + (lane >> 4);
-            float ar[2], ai[2], nai[2], br[2], bi[2];
-#pragma unroll
-            for (int si = 0; si < 2; ++si) {
-                const int row = R + 16 * si + (lane & 15);
-                const bool ok = row < m && k < nb;
-                ar[si] = ok ? -pr[(row - j0) * NBP + k] : 0.0f;
-                ai[si] = ok ? -pi[(row - j0) * NBP + k] : 0.0f;
-                nai[si] = -ai[si];
-            }
-#pragma unroll
-            for (int sj = 0; sj < 2; ++sj) {
-                br[sj] = ur[k * LU_CB + (C - cb) + 16 * sj + (lane & 15)];
-                bi[sj] = ui[k * LU_CB + (C - cb) + 16 * sj + (lane & 15)];
-            }
-#pragma unroll
-            for (int si = 0; si < 2; ++si)
-#pragma unroll
-                for (int sj = 0; sj < 2; ++sj) {
-                    cr[si][sj] = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[si], br[sj], cr[si][sj], 0, 0, 0);
-                    cr[si][sj] = __builtin_amdgcn_mfma_f32_16x16x4f32(nai[si], bi[sj], cr[si][sj], 0, 0, 0);
-                    ci[si][sj] = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[si], bi[sj], ci[si][sj], 0, 0, 0);
-                    ci[si][sj] = __builtin_amdgcn_mfma_f32_16x16x4f32(ai[si], br[sj], ci[si][sj], 0, 0, 0);
-                }
-        }
-#pragma unroll
-        for (int si = 0; si < 2; ++si)
-#pragma unroll
-            for (int sj = 0; sj < 2; ++sj)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int row = R + 16 * si + 4 * (lane >> 4) + i, col = C + 16 * sj + (lane & 15);
-                    if (row < m && col < cb + ncb) {
-                        Ar[(long long)row * ld + col] = cr[si][sj][i];
-                        Ai[(long long)row * ld + col] = ci[si][sj][i];
-                    }
-                }
-        if (tn < ntile) {
-#pragma unroll
-            for (int si = 0; si < 2; ++si)
-#pragma unroll
-                for (int sj = 0; sj < 2; ++sj) {
-                    cr[si][sj] = nr[si][sj];
-                    ci[si][sj] = ni[si][sj];
-                }
-        }
-    }
-}
-
-// FP64: complex register tiles of 4 x 4 per thread on the vector ALUs
-template <int NBP>
-__device__ __forceinline__ void trailing_update_c(double *Ar, double *Ai, int m, int ld, int j0, int nb, int cb, int ncb,
-                                                  const double *pr, const double *pi, const double *ur,
-                                                  const double *ui)
-{
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-    const int r0 = j0 + nb;
-    for (int R = r0; R < m; R += 64) {
-        for (int C = cb; C < cb + ncb; C += 64) {
-            double cr[4][4], ci[4][4];
-            for (int i = 0; i < 4; ++i)
-                for (int j = 0; j < 4; ++j) {
-                    const int row = R + ty + 16 * i, col = C + tx + 16 * j;
-                    const bool ok = row < m && col < cb + ncb;
-                    cr[i][j] = ok ? Ar[(long long)row * ld + col] : 0.0;
-                    ci[i][j] = ok ? Ai[(long long)row * ld + col] : 0.0;
-                }
-            for (int k = 0; k < nb; ++k) {
-                double ar[4], ai[4], br[4], bi[4];
-                for (int i = 0; i < 4; ++i) {
-                    const int row = R + ty + 16 * i;
-                    ar[i] = row < m ? pr[(row - j0) * NBP + k] : 0.0;
-                    ai[i] = row < m ? pi[(row - j0) * NBP + k] : 0.0;
-                }
-                for (int j = 0; j < 4; ++j) {
-                    br[j] = ur[k * LU_CB + (C - cb) + tx + 16 * j];
-                    bi[j] = ui[k * LU_CB + (C - cb) + tx + 16 * j];
-                }
-                for (int i = 0; i < 4; ++i)
-                    for (int j = 0; j < 4; ++j) {
-                        cr[i][j] -= ar[i] * br[j] - ai[i] * bi[j];
-                        ci[i][j] -= ar[i] * bi[j] + ai[i] * br[j];
-                    }
-            }
-            for (int i = 0; i < 4; ++i)
-                for (int j = 0; j < 4; ++j) {
-                    const int row = R + ty + 16 * i, col = C + tx + 16 * j;
-                    if (row < m && col < cb + ncb) {
-                        Ar[(long long)row * ld + col] = cr[i][j];
-                        Ai[(long long)row * ld + col] = ci[i][j];
-                    }
-                }
-        }
-    }
-}
-
-// the composed interchanges of one panel (row j0 + aff_src[i] moves to row
-// j0 + aff_dst[i], i < na) on columns [c_lo, c_hi), one plane after the
-// other: one column per thread, its affected entries through registers
-// (columns are independent: no staging and no barrier between column chunks)
-template <int NB, typename T>
-__device__ __forceinline__ void swap_columns_c(T *Ar, T *Ai, int ld, int j0, int na, const int *aff_src,
-                                               const int *aff_dst, int c_lo, int c_hi)
-{
-#pragma unroll 1
-    for (int col = c_lo + (int)threadIdx.x; col < c_hi; col += LU_THREADS)
-#pragma unroll 1
-        for (int plane = 0; plane < 2; ++plane) {
-            // compiler-only barrier: keeps the row indices' LDS reads inside
-            // the loop (hoisted, 4 NB row offsets would stay in registers)
-            asm volatile("" ::: "memory");
-            T *A = plane ? Ai : Ar;
-            T v[2 * NB];
-#pragma unroll
-            for (int i = 0; i < 2 * NB; ++i)
-                if (i < na) v[i] = A[(long long)(j0 + aff_src[i]) * ld + col];
-#pragma unroll
-            for (int i = 0; i < 2 * NB; ++i)
-                if (i < na) A[(long long)(j0 + aff_dst[i]) * ld + col] = v[i];
-        }
-}
-
-// batched blocked complex LU with partial pivoting (largest modulus), planar
-// row-major storage: matrix b at Aall + b * a_stride, real plane then
-// imaginary plane; same panel / interchange / update structure as the real
-// kernel
-template <typename T, int NB>
-__global__ void __launch_bounds__(LU_THREADS) lu_kernel_c(T *__restrict__ Aall, int *__restrict__ pivall, int m,
-                                                          int ld, long long a_stride, int *info)
-{
-    constexpr int NBP = NB + 1;
-    extern __shared__ unsigned char lds_raw[];
-    const int bid = blockIdx.x;
-    T *Ar = Aall + (long long)bid * a_stride;
-    T *Ai = Ar + (long long)m * ld;
-    int *piv = pivall + (long long)bid * m;
-    T *pr = reinterpret_cast<T *>(lds_raw);           // [m][NBP] panel, real
-    T *pi = pr + (size_t)m * NBP;                      // [m][NBP] panel, imaginary
-    T *ur = pi + (size_t)m * NBP;                      // [NB][LU_CB] U12 block
-    T *ui = ur + (size_t)NB * LU_CB;
-    T *stg = ui + (size_t)NB * LU_CB;                  // [2 NB][LU_SWC] interchange staging
-    __shared__ T rv[LU_THREADS / 64];
-    __shared__ int ri[LU_THREADS / 64];
-    __shared__ int sw[NB];
-    __shared__ int aff_src[2 * NB], aff_dst[2 * NB];
-    __shared__ int n_aff;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    for (int j0 = 0; j0 < m; j0 += NB) {
-        const int nb = min(NB, m - j0), mr = m - j0;
-        for (int e = tid; e < mr * nb; e += LU_THREADS) {
-            const int r = e / nb, c = e % nb;
-            const long long g = (long long)(j0 + r) * ld + j0 + c;
-            pr[r * NBP + c] = Ar[g];
-            pi[r * NBP + c] = Ai[g];
-        }
-        __syncthreads();
-        for (int c = 0; c < nb; ++c) {
-            T best = T(-1);
-            int bi = c;
-            for (int r = c + tid; r < mr; r += LU_THREADS) {
-                const T x = pr[r * NBP + c], y = pi[r * NBP + c];
-                const T v = x * x + y * y;
-                if (v > best) { best = v; bi = r; }
-            }
-            for (int off = 32; off > 0; off >>= 1) {
-                T ov = __shfl_xor(best, off, 64);
-                int oi = __shfl_xor(bi, off, 64);
-                if (ov > best || (ov == best && oi < bi)) { best = ov; bi = oi; }
-            }
-            if (lane == 0) { rv[wv] = best; ri[wv] = bi; }
-            __syncthreads();
-            T bv = rv[0];
-            int p = ri[0];
-            for (int w = 1; w < LU_THREADS / 64; ++w)
-                if (rv[w] > bv || (rv[w] == bv && ri[w] < p)) { bv = rv[w]; p = ri[w]; }
-            if (tid == 0) {
-                piv[j0 + c] = j0 + p;
-                sw[c] = p;
-                if (bv == T(0) && info) atomicAdd(info, 1);
-            }
-            if (p != c && tid < nb) {
-                T t = pr[c * NBP + tid];
-                pr[c * NBP + tid] = pr[p * NBP + tid];
-                pr[p * NBP + tid] = t;
-                t = pi[c * NBP + tid];
-                pi[c * NBP + tid] = pi[p * NBP + tid];
-                pi[p * NBP + tid] = t;
-            }
-            __syncthreads();
-            const T dr = pr[c * NBP + c], di = pi[c * NBP + c];
-            const T den = dr * dr + di * di;
-            const T ir = den != T(0) ? dr / den : T(0), ii = den != T(0) ? -di / den : T(0);
-            for (int r = c + 1 + tid; r < mr; r += LU_THREADS) {
-                const T xr = pr[r * NBP + c], xi = pi[r * NBP + c];
-                const T lr = xr * ir - xi * ii, li = xr * ii + xi * ir;
-                pr[r * NBP + c] = lr;
-                pi[r * NBP + c] = li;
-                for (int cc = c + 1; cc < nb; ++cc) {
-                    const T vr = pr[c * NBP + cc], vi = pi[c * NBP + cc];
-                    pr[r * NBP + cc] -= lr * vr - li * vi;
-                    pi[r * NBP + cc] -= lr * vi + li * vr;
-                }
-            }
-            __syncthreads();
-        }
-        if (wv == 0) compose_panel_swaps<NB>(sw, nb, aff_dst, aff_src, &n_aff);
-        __syncthreads();
-        const int na = n_aff;
-        if constexpr (NB <= 16) {
-            if (na > 0) {
-                swap_columns_c<NB>(Ar, Ai, ld, j0, na, aff_src, aff_dst, 0, m);
-                __syncthreads();
-            }
-        } else if (na > 0) {
-            for (int plane = 0; plane < 2; ++plane) {
-                T *A = plane ? Ai : Ar;
-                for (int c0 = 0; c0 < m; c0 += LU_SWC) {
-                    const int nc = min(LU_SWC, m - c0);
-                    for (int e = tid; e < na * LU_SWC; e += LU_THREADS) {
-                        const int i = e / LU_SWC, j = e % LU_SWC;
-                        if (j < nc) stg[i * LU_SWC + j] = A[(long long)(j0 + aff_src[i]) * ld + c0 + j];
-                    }
-                    __syncthreads();
-                    for (int e = tid; e < na * LU_SWC; e += LU_THREADS) {
-                        const int i = e / LU_SWC, j = e % LU_SWC;
-                        if (j < nc) A[(long long)(j0 + aff_dst[i]) * ld + c0 + j] = stg[i * LU_SWC + j];
-                    }
-                    __syncthreads();
-                }
-            }
-        }
-        for (int e = tid; e < mr * nb; e += LU_THREADS) {
-            const int r = e / nb, c = e % nb;
-            const long long g = (long long)(j0 + r) * ld + j0 + c;
-            Ar[g] = pr[r * NBP + c];
-            Ai[g] = pi[r * NBP + c];
-        }
-        __syncthreads();
-        // U12 = L11^{-1} A12 for every column right of the panel at once (one
-        // thread per column, all waves), written back to A; each trailing
-        // update then takes its U12 block from there
-#pragma unroll 1
-        for (int col = j0 + nb + tid; col < m; col += LU_THREADS) {
-            // compiler-only barrier: keeps the L11 reads from LDS inside the
-            // loop (hoisted, they would hold NB(NB-1) values in registers)
-            asm volatile("" ::: "memory");
-            T vr[NB], vi[NB];
-            for (int c = 0; c < NB; ++c) {
-                const bool ok = c < nb;
-                vr[c] = ok ? Ar[(long long)(j0 + c) * ld + col] : T(0);
-                vi[c] = ok ? Ai[(long long)(j0 + c) * ld + col] : T(0);
-            }
-            // fully unrolled (register arrays); rows c >= nb stay zero
-#pragma unroll
-            for (int c = 1; c < NB; ++c) {
-                T sr = vr[c], si = vi[c];
-#pragma unroll
-                for (int k = 0; k < c; ++k) {
-                    const T lr = pr[c * NBP + k], li = pi[c * NBP + k];
-                    sr -= lr * vr[k] - li * vi[k];
-                    si -= lr * vi[k] + li * vr[k];
-                }
-                if (c < nb) {
-                    vr[c] = sr;
-                    vi[c] = si;
-                }
-            }
-            for (int c = 0; c < NB; ++c)
-                if (c < nb) {
-                    Ar[(long long)(j0 + c) * ld + col] = vr[c];
-                    Ai[(long long)(j0 + c) * ld + col] = vi[c];
-                }
-        }
-        __syncthreads();
-        for (int cb = j0 + nb; cb < m; cb += LU_CB) {
-            const int ncb = min(LU_CB, m - cb);
-            for (int e = tid; e < NB * LU_CB; e += LU_THREADS) {
-                const int c = e / LU_CB, j = e % LU_CB;
-                const bool ok = c < nb && j < ncb;
-                const long long g = (long long)(j0 + min(c, nb - 1)) * ld + cb + min(j, ncb - 1);
-                const T a = Ar[g], b = Ai[g];
-                ur[e] = ok ? a : T(0);
-                ui[e] = ok ? b : T(0);
-            }
-            __syncthreads();
-            trailing_update_c<NBP>(Ar, Ai, m, ld, j0, nb, cb, ncb, pr, pi, ur, ui);
-            __syncthreads();
-        }
-    }
-}
-
-// complex trailing update C -= L21 U12 of one column block (planar), FP32 on
-// MFMA, for the second blocking level: rows [r0, m), K = nb, L21 from an
-// accessor (the LDS panel or global memory), U12 from LDS with row stride ldu
-template <typename LOP>
-__device__ __forceinline__ void trailing_update_cg(float *Ar, float *Ai, int r0, int m, int ld, int nb, int cb, int ncb,
-                                                  LOP lop, const float *ur, const float *ui, int ldu)
-{
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int nrt = (m - r0 + 31) / 32, nct = (ncb + 31) / 32, ntile = nrt * nct;
-    // the next tile's C block (both planes) is loaded before the current one
-    // is computed (tiles are disjoint)
-    auto load = [&](int t, floatx4_t (&xr)[2][2], floatx4_t (&xi)[2][2]) {
-        const int R = r0 + 32 * (t / nct), C = cb + 32 * (t % nct);
-#pragma unroll
-        for (int si = 0; si < 2; ++si)
-#pragma unroll
-            for (int sj = 0; sj < 2; ++sj)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int row = R + 16 * si + 4 * (lane >> 4) + i, col = C + 16 * sj + (lane & 15);
-                    const bool ok = row < m && col < cb + ncb;
-                    xr[si][sj][i] = ok ? Ar[(long long)row * ld + col] : 0.0f;
-                    xi[si][sj][i] = ok ? Ai[(long long)row * ld + col] : 0.0f;
-                }
-    };
-    floatx4_t cr[2][2], ci[2][2], nr[2][2], ni[2][2];
-    if (wv < ntile) load(wv, cr, ci);
-    for (int t = wv; t < ntile; t += LU_THREADS / 64) {
-        const int R = r0 + 32 * (t / nct), C = cb + 32 * (t % nct);
-        const int tn = t + LU_THREADS / 64;
-        if (tn < ntile) load(tn, nr, ni);
-        // L operands of UK k-steps loaded before their products (the L of
-        // the once-per-block update comes from global memory)
-        constexpr int UK = 4;
-        for (int k0 = 0; k0 < nb; k0 += 4 * UK) {
-            float ar[UK][2], ai[UK][2];
-#pragma unroll
-            for (int u = 0; u < UK; ++u) {
-                const int k = k0 + 4 * u + (lane >> 4);
-#pragma unroll
-                for (int si = 0; si < 2; ++si) {
-                    const int row = R + 16 * si + (lane & 15);
-                    const bool ok = row < m && k < nb;
-                    float lr, li;
-                    lop(min(row, m - 1), min(k, nb - 1), lr, li);
-                    ar[u][si] = ok ? -lr : 0.0f;
-                    ai[u][si] = ok ? -li : 0.0f;
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < UK; ++u) {
-                const int k = k0 + 4 * u + (lane >> 4), kc = min(k, nb - 1);
-                float br[2], bi[2];
-#pragma unroll
-                for (int sj = 0; sj < 2; ++sj) {
-                    const int col = (C - cb) + 16 * sj + (lane & 15);
-                    br[sj] = k < nb ? ur[kc * ldu + col] : 0.0f;
-                    bi[sj] = k < nb ? ui[kc * ldu + col] : 0.0f;
-                }
-#pragma unroll
-                for (int si = 0; si < 2; ++si)
-#pragma unroll
-                    for (int sj = 0; sj < 2; ++sj) {
-                        cr[si][sj] = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[u][si], br[sj], cr[si][sj], 0, 0, 0);
-                        cr[si][sj] = __builtin_amdgcn_mfma_f32_16x16x4f32(-ai[u][si], bi[sj], cr[si][sj], 0, 0, 0);
-                        ci[si][sj] = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[u][si], bi[sj], ci[si][sj], 0, 0, 0);
-                        ci[si][sj] = __builtin_amdgcn_mfma_f32_16x16x4f32(ai[u][si], br[sj], ci[si][sj], 0, 0, 0);
-                    }
-            }
-        }
-#pragma unroll
-        for (int si = 0; si < 2; ++si)
-#pragma unroll
-            for (int sj = 0; sj < 2; ++sj)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int row = R + 16 * si + 4 * (lane >> 4) + i, col = C + 16 * sj + (lane & 15);
-                    if (row < m && col < cb + ncb) {
-                        Ar[(long long)row * ld + col] = cr[si][sj][i];
-                        Ai[(long long)row * ld + col] = ci[si][sj][i];
-                    }
-                }
-        if (tn < ntile) {
-#pragma unroll
-            for (int si = 0; si < 2; ++si)
-#pragma unroll
-                for (int sj = 0; sj < 2; ++sj) {
-                    cr[si][sj] = nr[si][sj];
-                    ci[si][sj] = ni[si][sj];
-                }
-        }
-    }
-}
-
-// FP32 complex LU on two levels (matrices larger than LU_NBO_MIN_M): the
-// panels of an outer block of LU_CB columns touch only the block's columns;
-// then the block's interchanges, U of its rows (blocked forward substitution)
-// and one update of the rows and columns behind it with K = LU_CB (LU_CBD
-// columns at a time), as in lu_one.  Storage as in lu_kernel_c.
-template <typename T, int NB>
-__global__ void __launch_bounds__(LU_THREADS) lu_kernel_c2(T *__restrict__ Aall, int *__restrict__ pivall, int m,
-                                                          int ld, long long a_stride, int *info)
-{
-    constexpr int NBP = NB + 1;
-    extern __shared__ unsigned char lds_raw[];
-    const int bid = blockIdx.x;
-    T *Ar = Aall + (long long)bid * a_stride;
-    T *Ai = Ar + (long long)m * ld;
-    int *piv = pivall + (long long)bid * m;
-    static_assert(NB < 32 && sizeof(T) == 4, "two-level complex LU: FP32, panels under 32 columns");
-    constexpr int nbo = LU_CB;
-    constexpr int ubw = lu_c_u_words(NB, nbo);
-    T *pr = reinterpret_cast<T *>(lds_raw);           // [m][NBP] panel, real
-    T *pi = pr + (size_t)m * NBP;                      // [m][NBP] panel, imaginary
-    T *ur = pi + (size_t)m * NBP;                      // U block: [NB][LU_CB] or [nbo][LU_CBD]
-    T *ui = ur + (size_t)ubw;
-    int *pa = reinterpret_cast<int *>(ui + ubw);     // [m] panel row holding each logical row
-    __shared__ T rv[2][LU_THREADS / 64];               // pivot candidates per wave, by column parity
-    __shared__ int rl[2][LU_THREADS / 64], rp[2][LU_THREADS / 64];
-    __shared__ int sw[NB];
-    __shared__ int aff_src[2 * NB], aff_dst[2 * NB];
-    __shared__ int n_aff;
-    __shared__ int bsw[LU_CB];                         // local pivots of the outer block's panels
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    auto from_panel = [&](int j0) {
-        return [=](int row, int k, T &lr, T &li) {
-            const int o = pa[row - j0] * NBP + k;
-            lr = pr[o];
-            li = pi[o];
-        };
-    };
-    // interchanges of one panel (local pivots sw[0 .. nb)) on columns [c_lo, c_hi), both planes
-    auto apply_swaps = [&](int j0, int nb, int c_lo, int c_hi) {
-        if (wv == 0) compose_panel_swaps<NB>(sw, nb, aff_dst, aff_src, &n_aff);
-        __syncthreads();
-        const int na = n_aff;
-        if (na > 0) {
-            swap_columns_c<NB>(Ar, Ai, ld, j0, na, aff_src, aff_dst, c_lo, c_hi);
-            __syncthreads();
-        }
-    };
-    // U12 = L11^{-1} A12 on columns [c_lo, c_hi) of the rows j0 .. j0+nb (L11
-    // from the panel rows in LDS; one thread per column, all waves), written
-    // back to A, then A22 -= L21 U12 on the rows [j0+nb, rend), one column
-    // block at a time (U12 block staged from A)
-    auto u12_update = [&](int j0, int nb, int c_lo, int c_hi, int rend) {
-#pragma unroll 1
-        for (int col = c_lo + tid; col < c_hi; col += LU_THREADS) {
-            // compiler-only barrier: keeps the L11 reads from LDS inside the
-            // loop (hoisted, they would hold NB(NB-1) values in registers)
-            asm volatile("" ::: "memory");
-            T vr[NB], vi[NB];
-            for (int c = 0; c < NB; ++c) {
-                const bool ok = c < nb;
-                vr[c] = ok ? Ar[(long long)(j0 + c) * ld + col] : T(0);
-                vi[c] = ok ? Ai[(long long)(j0 + c) * ld + col] : T(0);
-            }
-            // fully unrolled (register arrays); rows c >= nb stay zero
-#pragma unroll
-            for (int c = 1; c < NB; ++c) {
-                T sr = vr[c], si = vi[c];
-                const int pc = c < nb ? pa[c] * NBP : 0;
-#pragma unroll
-                for (int k = 0; k < c; ++k) {
-                    const T lr = pr[pc + k], li = pi[pc + k];
-                    sr -= lr * vr[k] - li * vi[k];
-                    si -= lr * vi[k] + li * vr[k];
-                }
-                if (c < nb) {
-                    vr[c] = sr;
-                    vi[c] = si;
-                }
-            }
-            for (int c = 0; c < NB; ++c)
-                if (c < nb) {
-                    Ar[(long long)(j0 + c) * ld + col] = vr[c];
-                    Ai[(long long)(j0 + c) * ld + col] = vi[c];
-                }
-        }
-        __syncthreads();
-        if (rend <= j0 + nb) return;
-        for (int cb = c_lo; cb < c_hi; cb += LU_CB) {
-            const int ncb = min(LU_CB, c_hi - cb);
-            for (int e = tid; e < NB * LU_CB; e += LU_THREADS) {
-                const int c = e / LU_CB, j = e % LU_CB;
-                const bool ok = c < nb && j < ncb;
-                const long long g = (long long)(j0 + min(c, nb - 1)) * ld + cb + min(j, ncb - 1);
-                const T a = Ar[g], b = Ai[g];
-                ur[e] = ok ? a : T(0);
-                ui[e] = ok ? b : T(0);
-            }
-            __syncthreads();
-            trailing_update_cg(Ar, Ai, j0 + nb, rend, ld, nb, cb, ncb, from_panel(j0), ur, ui, LU_CB);
-            __syncthreads();
-        }
-    };
-    for (int J0 = 0; J0 < m; J0 += nbo) {
-      const int jend = min(J0 + nbo, m);             // end of the outer block
-      const int cmax = jend;                         // columns the panels of the block touch
-      for (int j0 = J0; j0 < jend; j0 += NB) {
-        const int nb = min(NB, m - j0), mr = m - j0;
-        for (int e = tid; e < mr * nb; e += LU_THREADS) {
-            const int r = e / nb, c = e % nb;
-            const long long g = (long long)(j0 + r) * ld + j0 + c;
-            pr[r * NBP + c] = Ar[g];
-            pi[r * NBP + c] = Ai[g];
-        }
-        __syncthreads();
-        // The panel rows stay where they are: each thread owns the rows
-        // tid + i LU_THREADS and keeps their logical positions (lg, moved by
-        // the interchanges) and whether they are pivotal yet (dn) in
-        // registers.  A pivot row is not written while its column is
-        // eliminated, and each thread searches only the rows it updated
-        // itself, so each column takes one barrier; ties go to the smaller
-        // logical row, so the pivots and factors are those of the panel with
-        // its rows interchanged.
-        int lg[LU_C2_ROWS];
-        unsigned dn = 0;
-#pragma unroll
-        for (int i = 0; i < LU_C2_ROWS; ++i) lg[i] = tid + i * LU_THREADS;
-        for (int c = 0; c < nb; ++c) {
-            const int buf = c & 1;
-            T best = T(-1);
-            int bl = 0x7fffffff, bp = 0;
-#pragma unroll
-            for (int i = 0; i < LU_C2_ROWS; ++i) {
-                const int r = tid + i * LU_THREADS;
-                if (r < mr && !((dn >> i) & 1u)) {
-                    const T x = pr[r * NBP + c], y = pi[r * NBP + c];
-                    const T v = x * x + y * y;
-                    if (v > best || (v == best && lg[i] < bl)) { best = v; bl = lg[i]; bp = r; }
-                }
-            }
-            for (int off = 32; off > 0; off >>= 1) {
-                const T ov = __shfl_xor(best, off, 64);
-                const int ol = __shfl_xor(bl, off, 64), op = __shfl_xor(bp, off, 64);
-                if (ov > best || (ov == best && ol < bl)) { best = ov; bl = ol; bp = op; }
-            }
-            if (lane == 0) { rv[buf][wv] = best; rl[buf][wv] = bl; rp[buf][wv] = bp; }
-            __syncthreads();
-            T bv = rv[buf][0];
-            int p = rl[buf][0], P = rp[buf][0];
-            for (int w = 1; w < LU_THREADS / 64; ++w)
-                if (rv[buf][w] > bv || (rv[buf][w] == bv && rl[buf][w] < p)) { bv = rv[buf][w]; p = rl[buf][w]; P = rp[buf][w]; }
-            if (tid == 0) {
-                piv[j0 + c] = j0 + p;
-                sw[c] = p;
-                bsw[j0 - J0 + c] = p;
-                if (bv == T(0) && info) atomicAdd(info, 1);
-            }
-            const T dr = pr[P * NBP + c], di = pi[P * NBP + c];
-            const T den = dr * dr + di * di;
-            const T ir = den != T(0) ? dr / den : T(0), ii = den != T(0) ? -di / den : T(0);
-#pragma unroll
-            for (int i = 0; i < LU_C2_ROWS; ++i) {
-                const int r = tid + i * LU_THREADS;
-                if (r >= mr || ((dn >> i) & 1u)) continue;
-                if (r == P) {
-                    lg[i] = c;
-                    dn |= 1u << i;
-                    continue;
-                }
-                if (lg[i] == c) lg[i] = p;
-                const T xr = pr[r * NBP + c], xi = pi[r * NBP + c];
-                const T lr = xr * ir - xi * ii, li = xr * ii + xi * ir;
-                pr[r * NBP + c] = lr;
-                pi[r * NBP + c] = li;
-                for (int cc = c + 1; cc < nb; ++cc) {
-                    const T vr = pr[P * NBP + cc], vi = pi[P * NBP + cc];
-                    pr[r * NBP + cc] -= lr * vr - li * vi;
-                    pi[r * NBP + cc] -= lr * vi + li * vr;
-                }
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < LU_C2_ROWS; ++i) {
-            const int r = tid + i * LU_THREADS;
-            if (r < mr) pa[lg[i]] = r;
-        }
-        __syncthreads();
-        // the panel's interchanges on the columns it touches (its own columns
-        // are rewritten below)
-        apply_swaps(j0, nb, 0, cmax);
-        for (int e = tid; e < mr * nb; e += LU_THREADS) {
-            const int r = e / nb, c = e % nb;
-            const long long g = (long long)(j0 + r) * ld + j0 + c;
-            Ar[g] = pr[pa[r] * NBP + c];
-            Ai[g] = pi[pa[r] * NBP + c];
-        }
-        __syncthreads();
-        u12_update(j0, nb, j0 + nb, cmax, m);
-      }
-      if (cmax < m) {
-        // columns behind the block, untouched so far: the block's interchanges
-        // in panel order, U of the block's rows (blocked forward substitution
-        // with the block's L11), then one update of the rows and columns
-        // behind the block with K = jend - J0 (L from global memory, U staged
-        // in LDS LU_CBD columns at a time)
-        for (int j0 = J0; j0 < jend; j0 += NB) {
-            const int nb = min(NB, m - j0);
-            if (tid < nb) sw[tid] = bsw[j0 - J0 + tid];
-            __syncthreads();
-            apply_swaps(j0, nb, jend, m);
-        }
-        for (int j0 = J0; j0 < jend; j0 += NB) {
-            const int nb = min(NB, m - j0), nr = jend - j0;
-            for (int e = tid; e < nr * nb; e += LU_THREADS) {
-                const int r = e / nb, c = e % nb;
-                const long long g = (long long)(j0 + r) * ld + j0 + c;
-                pr[r * NBP + c] = Ar[g];
-                pi[r * NBP + c] = Ai[g];
-            }
-            for (int r = tid; r < nr; r += LU_THREADS) pa[r] = r;   // rows reloaded in logical order
-            __syncthreads();
-            u12_update(j0, nb, jend, m, jend);
-        }
-        // the U rows are staged in the panel and U regions (free here), in
-        // column blocks as wide as they hold: every column block reads L once
-        // more from global memory
-        const int kk = jend - J0;
-        const int cbw = max(LU_CBD, min(((2 * m * NBP + 2 * ubw) / (2 * kk)) & ~31, (m - jend + 31) & ~31));
-        T *vr = pr, *vi = pr + (size_t)kk * cbw;
-        for (int cb = jend; cb < m; cb += cbw) {
-            const int ncb = min(cbw, m - cb);
-            for (int e = tid; e < kk * cbw; e += LU_THREADS) {
-                const int c = e / cbw, j = e - c * cbw;
-                const long long g = (long long)(J0 + c) * ld + cb + min(j, ncb - 1);
-                const T a = Ar[g], b = Ai[g];
-                vr[e] = j < ncb ? a : T(0);
-                vi[e] = j < ncb ? b : T(0);
-            }
-            __syncthreads();
-            trailing_update_cg(Ar, Ai, jend, m, ld, kk, cb, ncb,
-                              [=](int row, int k, T &lr, T &li) {
-                                  const long long g = (long long)row * ld + J0 + k;
-                                  lr = Ar[g];
-                                  li = Ai[g];
-                              },
-                              vr, vi, cbw);
-            __syncthreads();
-        }
-      }
-    }
-}
-
-// sequential LAPACK-style row interchanges -> one gather permutation per
-// matrix: (P b)[i] = b[perm[i]]
-__global__ void piv_to_perm_kernel(const int *__restrict__ piv, int *__restrict__ perm, int m, long long nmat)
-{
-    const long long b = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= nmat) return;
-    const int *p = piv + b * m;
-    int *q = perm + b * m;
-    for (int i = 0; i < m; ++i) q[i] = i;
-    for (int j = 0; j < m; ++j) {
-        const int k = p[j];
-        const int t = q[j];
-        q[j] = q[k];
-        q[k] = t;
-    }
-}
-
-// triangular solves with a planar complex row-major LU (unit lower L, upper
-// U), rhs (br, bi) in LDS.  Diagonal blocks of KB rows are solved by one
-// wavefront from LDS; SB of them form a super-block whose rows are updated
-// block by block, while the rows outside the super-block are updated once
-// with all SB*KB columns (longer contiguous row segments per load, two rows
-// per 16-lane group in flight for SB = 2: the same registers as KB columns
-// and four rows).  With PF the next diagonal block is loaded into registers
-// while the current one is solved and the rows are updated, and stored into
-// the second LDS block (dr[2 KB(KB+1)] and di likewise must then hold two
-// blocks): the factors are read-only, so its load never waits for the solve.
-template <typename T, int KB = 64, int SB = 1, typename TF = T, bool PF = false>
-__device__ __forceinline__ void lu_substitute_c(const TF *__restrict__ Lr, const TF *__restrict__ Li, int m, int ld, T *br, T *bi,
-                                                T *dr, T *di)
-{
-    constexpr int SW = SB * KB, RUS = SB == 1 ? 4 : (SB == 2 ? 2 : 1);
-    constexpr int DPT = (KB * KB + SV_THREADS - 1) / SV_THREADS, DB = KB * (KB + 1);
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    T pr[DPT], pi[DPT];
-    // clamped unconditional loads of a diagonal block into registers
-    auto diag_regs = [&](int kb, int nbk) {
-#pragma unroll
-        for (int q = 0; q < DPT; ++q) {
-            const int e = tid + q * SV_THREADS, i = min(e / KB, nbk - 1), j = min(e % KB, nbk - 1);
-            const long long o = (long long)(kb + i) * ld + kb + j;
-            pr[q] = ld_factor<T>(Lr + o);
-            pi[q] = ld_factor<T>(Li + o);
-        }
-    };
-    auto diag_store = [&](int buf, int nbk) {
-#pragma unroll
-        for (int q = 0; q < DPT; ++q) {
-            const int e = tid + q * SV_THREADS, i = e / KB, j = e % KB;
-            if (e < KB * KB && i < nbk && j < nbk) {
-                dr[buf * DB + i * (KB + 1) + j] = pr[q];
-                di[buf * DB + i * (KB + 1) + j] = pi[q];
-            }
-        }
-    };
-    auto load_diag = [&](int kb, int nbk) {
-        for (int e = tid; e < nbk * KB; e += SV_THREADS) {
-            const int i = e / KB, j = e % KB;
-            if (j < nbk) {
-                dr[i * (KB + 1) + j] = ld_factor<T>(Lr + (long long)(kb + i) * ld + kb + j);
-                di[i * (KB + 1) + j] = ld_factor<T>(Li + (long long)(kb + i) * ld + kb + j);
-            }
-        }
-    };
-    // forward: unit lower
-    int cur = 0;
-    if constexpr (PF) {
-        diag_regs(0, min(KB, m));
-        diag_store(0, min(KB, m));
-    }
-    for (int sb = 0; sb < m; sb += SW) {
-        const int se = min(sb + SW, m);
-        for (int kb = sb; kb < se; kb += KB) {
-            const int nbk = min(KB, se - kb), kn = kb + KB;
-            if constexpr (PF) {
-                if (kn < m) diag_regs(kn, min(KB, m - kn));
-            } else {
-                load_diag(kb, nbk);
-            }
-            __syncthreads();
-            if (wv == 0) {
-                const T *cr_ = dr + cur * DB, *ci_ = di + cur * DB;
-                T yr = lane < nbk ? br[kb + lane] : T(0), yi = lane < nbk ? bi[kb + lane] : T(0);
-                for (int c = 0; c < nbk; ++c) {
-                    const T cr = __shfl(yr, c, 64), ci = __shfl(yi, c, 64);
-                    if (lane > c && lane < nbk) {
-                        const T lr = cr_[lane * (KB + 1) + c], li = ci_[lane * (KB + 1) + c];
-                        yr -= lr * cr - li * ci;
-                        yi -= lr * ci + li * cr;
-                    }
-                }
-                if (lane < nbk) {
-                    br[kb + lane] = yr;
-                    bi[kb + lane] = yi;
-                }
-            }
-            __syncthreads();
-            if (kb + nbk < se) {
-                block_gemv_update<T, true, KB, 4, TF>(Lr, Li, ld, kb, nbk, kb + nbk, se, br, bi);
-            }
-            if constexpr (PF) {
-                if (kn < m) diag_store(cur ^ 1, min(KB, m - kn));
-                cur ^= 1;
-            }
-            __syncthreads();
-        }
-        block_gemv_update<T, true, SW, RUS, TF>(Lr, Li, ld, sb, se - sb, se, m, br, bi);
-        __syncthreads();
-    }
-    // backward: upper with diagonal
-    const int nsb = (m + SW - 1) / SW;
-    const int nblk = (m + KB - 1) / KB;
-    if constexpr (PF) {
-        const int kl = (nblk - 1) * KB;
-        diag_regs(kl, m - kl);
-        diag_store(cur, m - kl);
-    }
-    for (int bs = nsb - 1; bs >= 0; --bs) {
-        const int sb = bs * SW, se = min(sb + SW, m);
-        const int nin = (se - sb + KB - 1) / KB;
-        for (int j = nin - 1; j >= 0; --j) {
-            const int kb = sb + j * KB, nbk = min(KB, se - kb), kn = kb - KB;
-            if constexpr (PF) {
-                if (kn >= 0) diag_regs(kn, KB);
-            } else {
-                load_diag(kb, nbk);
-            }
-            __syncthreads();
-            if (wv == 0) {
-                const T *cr_ = dr + cur * DB, *ci_ = di + cur * DB;
-                T xr = lane < nbk ? br[kb + lane] : T(0), xi = lane < nbk ? bi[kb + lane] : T(0);
-                for (int c = nbk - 1; c >= 0; --c) {
-                    const T vr = __shfl(xr, c, 64), vi = __shfl(xi, c, 64);
-                    const T ur = cr_[c * (KB + 1) + c], ui = ci_[c * (KB + 1) + c];
-                    const T den = ur * ur + ui * ui;
-                    const T qr = (vr * ur + vi * ui) / den, qi = (vi * ur - vr * ui) / den;
-                    if (lane == c) {
-                        xr = qr;
-                        xi = qi;
-                    }
-                    if (lane < c) {
-                        const T lr = cr_[lane * (KB + 1) + c], li = ci_[lane * (KB + 1) + c];
-                        xr -= lr * qr - li * qi;
-                        xi -= lr * qi + li * qr;
-                    }
-                }
-                if (lane < nbk) {
-                    br[kb + lane] = xr;
-                    bi[kb + lane] = xi;
-                }
-            }
-            __syncthreads();
-            if (kb > sb) {
-                block_gemv_update<T, true, KB, 4, TF>(Lr, Li, ld, kb, nbk, sb, kb, br, bi);
-            }
-            if constexpr (PF) {
-                if (kn >= 0) diag_store(cur ^ 1, KB);
-                cur ^= 1;
-            }
-            __syncthreads();
-        }
-        block_gemv_update<T, true, SW, RUS, TF>(Lr, Li, ld, sb, se - sb, 0, sb, br, bi);
-        __syncthreads();
-    }
-}
-
-// one time-decoupled patch solve per cell: gather the patch defect of all
-// time nodes, per eigen-system transform (with the LU row permutation),
-// substitute, transform back; velocity to the cell buffer E, pressure
-// updated in place (pressure unknowns belong to one cell)
-template <int DIM, int R, typename T, typename TP, typename TF = TP>
-__global__ void __launch_bounds__(SV_THREADS) solve_td_kernel(SolveTdArgs<T, TP, TF> A)
-{
-    using Z = VS<DIM, R>;
-    constexpr int N1 = Z::N1, NL = Z::NL, NPM = Z::NPM;
-    constexpr int NV = DIM * NL, MS = NV + NPM, MSP = (MS + 1) & ~1;
-    constexpr int LDM = td_ld(MS);
-    constexpr long long MAT = (long long)MS * LDM;
-    extern __shared__ unsigned char lds_raw[];
-    const int nt = A.nt;
-    TP *rl = reinterpret_cast<TP *>(lds_raw);   // [nt][MS] patch defect
-    TP *out = rl + nt * MSP;                    // [nt][MS] patch correction
-    TP *br = out + nt * MSP;
-    TP *bi = br + MSP;
-    TP *dr = bi + MSP;
-    // diagonal-block width of the substitutions: 32 keeps the LDS at a size
-    // that lets several workgroups share a CU (32^3, r = 3, k = 1, finest
-    // level: FP64 four instead of one, FP32 six instead of three); the
-    // complex substitution updates the rows outside pairs of blocks with 64
-    // columns at once (4 % faster sweeps than 32)
-    constexpr int KBT = 32;
-    // FP32, patches above 128 unknowns: two diagonal blocks per plane (the
-    // next one is prefetched)
-    constexpr bool PFD = sizeof(TP) == 4 && MS > 128;
-    TP *di = dr + (PFD ? 2 : 1) * KBT * (KBT + 1);
-    const int cell = xcd_cell(blockIdx.x, gridDim.x), tid = threadIdx.x;
-    const int c0 = cell % A.n0, c1 = (cell / A.n0) % A.n1, c2 = DIM == 3 ? cell / (A.n0 * A.n1) : 0;
-    const long long N0 = (long long)(R + 1) * A.n0 + 1, N1g = (long long)(R + 1) * A.n1 + 1;
-    const long long pbase = (long long)nt * A.Nv1;
-    for (int e = tid; e < nt * MS; e += SV_THREADS) {
-        const int a = e / MS, j = e - (e / MS) * MS;
-        long long g;
-        if (j < NV) {
-            const int l = j % NL, c = j / NL;
-            const int i0 = l % N1, i1 = (l / N1) % N1, i2 = DIM == 3 ? l / (N1 * N1) : 0;
-            g = a * A.Nv1 + c * A.Nn +
-                (((long long)(R + 1) * c0 + i0) + N0 * (((long long)(R + 1) * c1 + i1) + N1g * ((long long)(R + 1) * c2 + i2)));
-        } else {
-            g = pbase + a * A.Np1 + (long long)cell * NPM + (j - NV);
-        }
-        rl[a * MSP + j] = (TP)A.defect[g];
-        out[a * MSP + j] = TP(0);
-    }
-    __syncthreads();
-    for (int s = 0; s < A.nsys; ++s) {
-        const bool cx = A.cplx[s] != 0;
-        const int *perm = A.perm[s] + (long long)cell * MS;
-        for (int i = tid; i < MS; i += SV_THREADS) {
-            const int src = perm[i];
-            TP sr = 0, si = 0;
-            for (int a = 0; a < nt; ++a) {
-                sr += A.Tre[s * 4 + a] * rl[a * MSP + src];
-                si += A.Tim[s * 4 + a] * rl[a * MSP + src];
-            }
-            br[i] = sr;
-            bi[i] = si;
-        }
-        __syncthreads();
-        const TF *LU = A.sys[s] + (long long)cell * (cx ? 2 : 1) * MAT;
-        if (cx) lu_substitute_c<TP, KBT, 2, TF, PFD>(LU, LU + MAT, MS, LDM, br, bi, dr, di);
-        else lu_substitute<TP, KBT, TF>(LU, MS, LDM, br, dr);
-        for (int e = tid; e < nt * MS; e += SV_THREADS) {
-            const int a = e / MS, j = e - (e / MS) * MS;
-            TP v = A.Fre[a * 4 + s] * br[j];
-            if (cx) v -= A.Fim[a * 4 + s] * bi[j];
-            out[a * MSP + j] += v;
-        }
-        __syncthreads();
-    }
-    T *Ec = A.E + (long long)cell * nt * NV;
-    for (int e = tid; e < nt * MS; e += SV_THREADS) {
-        const int a = e / MS, j = e - (e / MS) * MS;
-        if (j < NV) Ec[a * NV + j] = (T)out[a * MSP + j];
-        else A.d[pbase + a * A.Np1 + (long long)cell * NPM + (j - NV)] += A.omega * (T)out[a * MSP + j];
     }
 }
 
@@ -3149,17 +2196,6 @@ template <int NB, typename T> size_t lu_lds_bytes(int m)
     return ((size_t)m * (NB + 1) + (size_t)lu_outer_block(m, NB) * LU_CB + (size_t)2 * NB * LU_SWC) * sizeof(T);
 }
 
-template <int NB, typename T> size_t lu_c_lds_bytes(int m)
-{
-    return ((size_t)2 * m * (NB + 1) + (size_t)2 * NB * LU_CB + (size_t)2 * NB * LU_SWC) * sizeof(T);
-}
-
-// LDS of lu_kernel_c2 (panel, U block, logical-to-panel row map)
-template <int NB> size_t lu_c2_lds_bytes(int m)
-{
-    return ((size_t)2 * m * (NB + 1) + (size_t)2 * lu_c_u_words(NB, LU_CB) + (size_t)m) * sizeof(float);
-}
-
 } // namespace
 
 // ---------------------------------------------------------------------------
@@ -3213,9 +2249,7 @@ hipError_t launch_patch(int dim, int r, const PatchArgs<TE, TP> &a, int ncell, h
     return hipErrorInvalidValue;
 }
 
-// dynamic-LDS limit of a kernel, raised only when a launch needs more than
-// any earlier one (keeps driver calls out of replayed or captured launches)
-static hipError_t lds_attr(const void *kern, size_t bytes)
+hipError_t lds_attr(const void *kern, size_t bytes)
 {
     static std::mutex mu;
     static std::unordered_map<const void *, size_t> set;
@@ -3345,101 +2379,6 @@ hipError_t launch_patch_td(int dim, int r, const PatchTdArgs<TE, TP> &a, int nce
     }
     PC(2, 1) PC(2, 2) PC(2, 3) PC(3, 1) PC(3, 2) PC(3, 3)
 #undef PC
-    return hipErrorInvalidValue;
-}
-
-template <typename T>
-hipError_t launch_lu_c(T *A, int *piv, int m, int ld, long long a_stride, int batch, int *info, size_t max_lds,
-                       hipStream_t s)
-{
-    if constexpr (std::is_same<T, float>::value) {
-        if (m > LU_NBO_MIN_M && m <= LU_C2_ROWS * LU_THREADS) {
-            // two blocking levels: the widest panel (16 or 8, within the
-            // STMG_LU_NB cap) with two workgroups per CU, else the widest that fits
-            int cap2 = std::min(lu_nb_cap(), 16);
-            for (int nb = cap2; nb >= 8; nb /= 2) {
-                const size_t b = nb == 16 ? lu_c2_lds_bytes<16>(m) : lu_c2_lds_bytes<8>(m);
-                if (2 * b <= CU_LDS && b <= max_lds) { cap2 = nb; break; }
-            }
-#define LUC2(NBV)                                                                                                      \
-    if (NBV <= cap2 && lu_c2_lds_bytes<NBV>(m) <= max_lds) {                                                           \
-        size_t bytes = lu_c2_lds_bytes<NBV>(m);                                                                        \
-        hipError_t e = lds_attr((const void *)lu_kernel_c2<float, NBV>, bytes);                                        \
-        if (e != hipSuccess) return e;                                                                                 \
-        hipLaunchKernelGGL((lu_kernel_c2<float, NBV>), dim3(batch), dim3(LU_THREADS), bytes, s, A, piv, m, ld, a_stride, \
-                           info);                                                                                      \
-        return hipGetLastError();                                                                                      \
-    }
-            LUC2(16) LUC2(8) LUC2(4)
-#undef LUC2
-        }
-    }
-    int cap = lu_nb_cap();
-    for (int nb = cap; nb >= 16; nb /= 2) {
-        const size_t b = nb == 32 ? lu_c_lds_bytes<32, T>(m) : nb == 16 ? lu_c_lds_bytes<16, T>(m)
-                       : nb == 8 ? lu_c_lds_bytes<8, T>(m) : lu_c_lds_bytes<4, T>(m);
-        if (2 * b <= CU_LDS && b <= max_lds) { cap = nb; break; }
-    }
-#define LUC(NBV)                                                                                                       \
-    if (NBV <= cap && lu_c_lds_bytes<NBV, T>(m) <= max_lds) {                                                          \
-        size_t bytes = lu_c_lds_bytes<NBV, T>(m);                                                                      \
-        hipError_t e = lds_attr((const void *)lu_kernel_c<T, NBV>, bytes);                    \
-        if (e != hipSuccess) return e;                                                                                 \
-        hipLaunchKernelGGL((lu_kernel_c<T, NBV>), dim3(batch), dim3(LU_THREADS), bytes, s, A, piv, m, ld, a_stride, info); \
-        return hipGetLastError();                                                                                      \
-    }
-    LUC(32) LUC(16) LUC(8) LUC(4)
-#undef LUC
-    return hipErrorInvalidConfiguration;
-}
-
-hipError_t launch_piv_to_perm(const int *piv, int *perm, int m, long long nmat, hipStream_t s)
-{
-    if (nmat <= 0) return hipSuccess;
-    const int th = 256;
-    hipLaunchKernelGGL(piv_to_perm_kernel, dim3((unsigned)((nmat + th - 1) / th)), dim3(th), 0, s, piv, perm, m, nmat);
-    return hipGetLastError();
-}
-
-size_t solve_td_lds_bytes(int ms, int nt, size_t word)
-{
-    const size_t msp = (size_t)((ms + 1) & ~1);
-    const size_t kb = 32;   // diagonal-block width of solve_td_kernel
-    const size_t nd = word == 4 && ms > 128 ? 4 : 2;   // FP32 (ms > 128): the next block is prefetched
-    return (2 * nt * msp + 2 * msp + nd * kb * (kb + 1)) * word;
-}
-
-template <typename T, typename TP>
-hipError_t launch_solve_td(int dim, int r, const SolveTdArgs<T, TP> &a, int ncell, int ms, hipStream_t s)
-{
-    size_t bytes = solve_td_lds_bytes(ms, a.nt, sizeof(TP));
-#define SC(D, RR)                                                                                                      \
-    if (dim == D && r == RR) {                                                                                         \
-        hipError_t e = lds_attr((const void *)solve_td_kernel<D, RR, T, TP>, bytes);                    \
-        if (e != hipSuccess) return e;                                                                                 \
-        hipLaunchKernelGGL((solve_td_kernel<D, RR, T, TP>), dim3(ncell), dim3(SV_THREADS), bytes, s, a);              \
-        return hipGetLastError();                                                                                      \
-    }
-    SC(2, 1) SC(2, 2) SC(2, 3) SC(3, 1) SC(3, 2) SC(3, 3)
-#undef SC
-    return hipErrorInvalidValue;
-}
-
-hipError_t launch_solve_td_bf16(int dim, int r, const SolveTdArgs<float, float, unsigned short> &a, int ncell, int ms,
-                                hipStream_t s)
-{
-    using T = float;
-    using TP = float;
-    size_t bytes = solve_td_lds_bytes(ms, a.nt, sizeof(TP));
-#define SC(D, RR)                                                                                                      \
-    if (dim == D && r == RR) {                                                                                         \
-        hipError_t e = lds_attr((const void *)solve_td_kernel<D, RR, T, TP, unsigned short>, bytes);                    \
-        if (e != hipSuccess) return e;                                                                                 \
-        hipLaunchKernelGGL((solve_td_kernel<D, RR, T, TP, unsigned short>), dim3(ncell), dim3(SV_THREADS), bytes, s, a);              \
-        return hipGetLastError();                                                                                      \
-    }
-    SC(2, 1) SC(2, 2) SC(2, 3) SC(3, 1) SC(3, 2) SC(3, 3)
-#undef SC
     return hipErrorInvalidValue;
 }
 
@@ -3749,11 +2688,6 @@ template hipError_t launch_solve<float, float>(int, int, const SolveArgs<float, 
 template hipError_t launch_solve<double, float>(int, int, const SolveArgs<double, float> &, int, int, hipStream_t);
 template hipError_t launch_patch_td<double, double>(int, int, const PatchTdArgs<double, double> &, int, hipStream_t);
 template hipError_t launch_patch_td<float, float>(int, int, const PatchTdArgs<float, float> &, int, hipStream_t);
-template hipError_t launch_lu_c<double>(double *, int *, int, int, long long, int, int *, size_t, hipStream_t);
-template hipError_t launch_lu_c<float>(float *, int *, int, int, long long, int, int *, size_t, hipStream_t);
-template hipError_t launch_solve_td<double, double>(int, int, const SolveTdArgs<double, double> &, int, int,
-                                                    hipStream_t);
-template hipError_t launch_solve_td<float, float>(int, int, const SolveTdArgs<float, float> &, int, int, hipStream_t);
 template hipError_t launch_midpoint<double>(const double *, long long, int, const double *, double *, hipStream_t);
 template hipError_t launch_midpoint<float>(const float *, long long, int, const double *, float *, hipStream_t);
 
