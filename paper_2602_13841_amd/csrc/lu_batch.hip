@@ -185,6 +185,22 @@ int batched_lu_run(int prec, void *A, const long long *a_off, const int *m_of, i
             e = launch_batched_solve<double>((const double *)A, piv, maxm, batch, vb, db, (double *)b, s);
         else
             e = launch_batched_solve<float>((const float *)A, piv, maxm, batch, vb, db, (float *)b, s);
+    } else if (!cfg && op == 0) {
+        // left-looking factorization; FP64 matrices too large for its
+        // accumulators (first in the order) by the persistent kernel
+        int nq = 0;
+        while (nq < batch && ms[nq] > lu_std_max_m(f64)) ++nq;
+        if (nq > 0) {
+            LuQueue q{nq, dm, da, dp, dnb, dcounter};
+            const int grid = std::min(nq, device_cus() * std::max(1, (int)(CU_LDS_BYTES / (budget + 1024))));
+            if (f64) e = launch_lu_queue<double>((double *)A, piv, q, budget, grid, tune.threads, info, s);
+            else e = launch_lu_queue<float>((float *)A, piv, q, budget, grid, tune.threads, info, s, op);
+        }
+        if (e == hipSuccess && nq < batch) {
+            const LuBatch vl{0, dm + nq, da + nq, dp + nq, 0};
+            if (f64) e = launch_lu_std<double>((double *)A, piv, vl, ms + nq, batch - nq, info, s);
+            else e = launch_lu_std<float>((float *)A, piv, vl, ms + nq, batch - nq, info, s);
+        }
     } else if (!per_class) {
         // one persistent launch for the whole batch, largest matrices first
         LuQueue q{batch, dm, da, dp, dnb, dcounter};

@@ -35,9 +35,16 @@
 #include <type_traits>
 #include <utility>
 
+// every multiply-add below is written out: the results do not depend on which
+// products the compiler would fuse in which instantiation
+#pragma clang fp contract(off)
+
 namespace stmg {
 
 namespace {
+
+__device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
 typedef float floatx4_t __attribute__((ext_vector_type(4)));
 typedef double doublex4_t __attribute__((ext_vector_type(4)));
@@ -181,8 +188,8 @@ __device__ __forceinline__ void tri_inverse16(F coef, T rdr, T rdi, T (&yr)[4], 
             // column k divided by its diagonal entry: the rows are scaled last
             const T dr = dpp<BC, 0xf>(rdr);
             if constexpr (CX) {
-                const T di = dpp<BC, 0xf>(rdi), t = ar * dr - ai * di;
-                ai = ar * di + ai * dr;
+                const T di = dpp<BC, 0xf>(rdi), t = fma_(ar, dr, -(ai * di));
+                ai = fma_(ar, di, ai * dr);
                 ar = t;
             } else {
                 ar *= dr;
@@ -193,12 +200,10 @@ __device__ __forceinline__ void tri_inverse16(F coef, T rdr, T rdi, T (&yr)[4], 
             const T br = dpp<BC, 0xf>(yr[q]);
             if constexpr (CX) {
                 const T bi = dpp<BC, 0xf>(yi[q]);
-                yr[q] -= ar * br;
-                yr[q] += ai * bi;
-                yi[q] -= ar * bi;
-                yi[q] -= ai * br;
+                yr[q] = fma_(ai, bi, fma_(-ar, br, yr[q]));
+                yi[q] = fma_(-ai, br, fma_(-ar, bi, yi[q]));
             } else {
-                yr[q] -= ar * br;
+                yr[q] = fma_(-ar, br, yr[q]);
             }
         }
     });
@@ -206,8 +211,8 @@ __device__ __forceinline__ void tri_inverse16(F coef, T rdr, T rdi, T (&yr)[4], 
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             if constexpr (CX) {
-                const T t = yr[q] * rdr - yi[q] * rdi;
-                yi[q] = yr[q] * rdi + yi[q] * rdr;
+                const T t = fma_(yr[q], rdr, -(yi[q] * rdi));
+                yi[q] = fma_(yr[q], rdi, yi[q] * rdr);
                 yr[q] = t;
             } else {
                 yr[q] *= rdr;
@@ -219,9 +224,10 @@ __device__ __forceinline__ void tri_inverse16(F coef, T rdr, T rdi, T (&yr)[4], 
 template <typename T, bool CX> __device__ __forceinline__ void reciprocal(T dr, T di, T &ir, T &ii)
 {
     if constexpr (CX) {
-        const T den = dr * dr + di * di;
-        ir = den != T(0) ? dr / den : T(0);
-        ii = den != T(0) ? -di / den : T(0);
+        const T den = fma_(dr, dr, di * di);
+        const T inv = T(1) / den;
+        ir = den != T(0) ? dr * inv : T(0);
+        ii = den != T(0) ? -di * inv : T(0);
     } else {
         const T inv = T(1) / dr;
         ir = dr != T(0) ? inv : T(0);
@@ -229,37 +235,45 @@ template <typename T, bool CX> __device__ __forceinline__ void reciprocal(T dr, 
     }
 }
 
-// LDS words of T and of int for one factorization
-template <typename T, bool CX> constexpr size_t td_lu_lds_bytes(int m)
+// LDS bytes of one factorization: panel, U blocks (and L of a diagonal block:
+// STD), positions and ranks
+template <typename T, bool CX, int PW, bool STD> constexpr size_t left_lu_lds_bytes(int m)
 {
     constexpr int P = CX ? 2 : 1;
-    const size_t pan = (size_t)m * TD_LS * P, ub = (size_t)P * TD_BW * Vec<T>::LDU;
-    return (pan + 2 * ub) * sizeof(T) + (size_t)(2 * ((m + 31) & ~31) + TD_BW) * sizeof(int);
+    const size_t pan = (size_t)m * (PW + 1) * P, ub = (size_t)P * TD_BW * Vec<T>::LDU;
+    return (pan + 2 * ub + (STD ? TD_BW * (TD_BW + 1) : 0)) * sizeof(T) +
+           (size_t)(2 * ((m + 31) & ~31) + TD_BW) * sizeof(int);
 }
 
 // ---------------------------------------------------------------------------
-// the factorization: NW wavefronts, SLOTS row tiles per wavefront (32 NW SLOTS
-// >= m), RPT panel rows per thread (64 NW RPT >= m)
+// the factorization of one matrix by the workgroup: NW wavefronts, SLOTS row
+// tiles per wavefront (32 NW SLOTS >= m), RPT panel rows per thread (64 NW RPT
+// >= m), panels of PW columns.  STD = false: the format of the time-decoupled
+// systems (ip: the permutation); STD = true (real only): LAPACK's, L and U of
+// the row-permuted matrix (ip: the interchanges), at the price of one more
+// pass that permutes the rows, and with each U block by substitution.
 // ---------------------------------------------------------------------------
-template <typename T, bool CX, int NW, int SLOTS, int RPT>
-__global__ void __launch_bounds__(64 * NW, 2) lu_td_kernel(T *__restrict__ Aall, int *__restrict__ permall, int m, int ld,
-                                                        long long a_stride, int *info)
+template <typename T, bool CX, int NW, int SLOTS, int RPT, int PW, bool STD>
+__device__ __forceinline__ void lu_left(T *__restrict__ Ar, int m, int ld, int *__restrict__ ip, int *info,
+                                        unsigned char *lds_raw)
 {
+    static_assert(!(STD && CX), "the LAPACK format is real");
     using V = Vec<T>;
     using acc_t = typename V::acc;
     using seg_t = typename V::seg;
     constexpr int P = CX ? 2 : 1, W = V::W, LDU = V::LDU, NTH = 64 * NW;
     constexpr int NH = TD_BW / (4 * W);   // 16-byte segments per lane along K = 32
-    extern __shared__ unsigned char lds_raw[];
-    T *pan = reinterpret_cast<T *>(lds_raw);                  // [rows from the block on][TD_LS][P]
-    T *ub1 = pan + (size_t)m * TD_LS * P;                      // [P][32][LDU]
+    constexpr int LS = PW + 1;            // row stride of the panel
+    T *pan = reinterpret_cast<T *>(lds_raw);                  // [rows from the block on][LS][P]
+    T *ub1 = pan + (size_t)m * LS * P;                         // [P][32][LDU]
     T *ub2 = ub1 + P * TD_BW * LDU;                            // [P][32][LDU] (negated U)
     // 16 x 16 blocks of the panel phase, in the U blocks: A12 (then L21), a
     // product and V2 in the first, U12, I1, V1 and I2 in the second
     constexpr int SB = 16 * TD_LS * P;
     static_assert(4 * SB <= P * TD_BW * LDU, "four small blocks fit a U block");
     T *sV2 = ub1 + 2 * SB, *sI1 = ub2 + SB, *sV1 = ub2 + 2 * SB, *sI2 = ub2 + 3 * SB;
-    int *cur = reinterpret_cast<int *>(ub2 + P * TD_BW * LDU);   // stored row at each position
+    T *lkk = ub2 + P * TD_BW * LDU;                            // [32][33] columns of L_KK (STD)
+    int *cur = reinterpret_cast<int *>(lkk + (STD ? TD_BW * (TD_BW + 1) : 0));   // stored row at each position
     int *rk = cur + ((m + 31) & ~31);                          // rank of a panel row among the block's pivots, or -1
     int *pl = rk + ((m + 31) & ~31);                           // panel row of each pivot of the block
     // pivot candidates of the wavefronts, by column parity: value, panel row |
@@ -269,9 +283,7 @@ __global__ void __launch_bounds__(64 * NW, 2) lu_td_kernel(T *__restrict__ Aall,
     __shared__ alignas(16) T pub[2][NW][16 * P];
 
     const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    T *Ar = Aall + (long long)blockIdx.x * a_stride;
     T *Ai = Ar + (CX ? (long long)m * ld : 0);
-    int *perm = permall + (long long)blockIdx.x * m;
     // entries of A by byte offset (32-bit offsets from a uniform base)
     const unsigned ldb = ld * sizeof(T);
     auto at = [](T *base, unsigned o) { return reinterpret_cast<T *>(reinterpret_cast<char *>(base) + o); };
@@ -317,21 +329,32 @@ __global__ void __launch_bounds__(64 * NW, 2) lu_td_kernel(T *__restrict__ Aall,
         // U = L_KK^{-1} (tile K), its four 16 x 16 tiles spread over the
         // wavefronts (tile q: rows 16 (q / 2), columns 16 (q % 2)); the rows
         // of L_KK^{-1} are loaded one block ahead
-        constexpr int UT = NW >= 4 ? 1 : 4 / NW;
-        seg_t fr[UT][NH], fi[CX ? UT : 1][NH];
+        // (STD: L_KK itself, transposed into LDS, and one substitution per
+        // wavefront, lane = row)
+        constexpr int UT = NW >= 4 ? 1 : 4 / NW, LE = TD_BW * TD_BW / NTH;
+        seg_t fr[STD ? 1 : UT][NH], fi[CX ? UT : 1][NH];
+        T le[STD ? LE : 1];
         auto load_inverse = [&](int K) {
+            if constexpr (STD) {
 #pragma unroll
-            for (int u = 0; u < UT; ++u) {
-                const int si0 = ((wv + NW * u) >> 1) & 1;
-                const unsigned o = cur[32 * K + 16 * si0 + l16] * ldb + 32 * K * sizeof(T) + 16 * g;
+                for (int u = 0; u < LE; ++u) {
+                    const int e = tid + u * NTH;
+                    le[u] = *at(Ar, cur[32 * K + (e >> 5)] * ldb + (32 * K + (e & 31)) * sizeof(T));
+                }
+            } else {
 #pragma unroll
-                for (int h = 0; h < NH; ++h) {
-                    fr[u][h] = *(const seg_t *)at(Ar, o + 64 * h);
-                    if constexpr (CX) fi[u][h] = *(const seg_t *)at(Ai, o + 64 * h);
+                for (int u = 0; u < UT; ++u) {
+                    const int si0 = ((wv + NW * u) >> 1) & 1;
+                    const unsigned o = cur[32 * K + 16 * si0 + l16] * ldb + 32 * K * sizeof(T) + 16 * g;
+#pragma unroll
+                    for (int h = 0; h < NH; ++h) {
+                        fr[u][h] = *(const seg_t *)at(Ar, o + 64 * h);
+                        if constexpr (CX) fi[u][h] = *(const seg_t *)at(Ai, o + 64 * h);
+                    }
                 }
             }
         };
-        if (J > 0 && wv < 4) load_inverse(0);
+        if (J > 0 && (STD || wv < 4)) load_inverse(0);
 #pragma unroll 1
         for (int K = 0; K < J; ++K) {
             // tile K: the pivot rows of block K
@@ -349,8 +372,32 @@ __global__ void __launch_bounds__(64 * NW, 2) lu_td_kernel(T *__restrict__ Aall,
                                 if constexpr (CX) ub1[TD_BW * LDU + o] = ai[s][si][sj][i];
                             }
                 }
+            if constexpr (STD) {
+#pragma unroll
+                for (int u = 0; u < LE; ++u) {
+                    const int e = tid + u * NTH, i = e >> 5, k = e & 31;
+                    lkk[k * (TD_BW + 1) + i] = k < i ? le[u] : T(0);
+                }
+            }
             __syncthreads();
-            if (wv < 4) {
+            if constexpr (STD) {
+                constexpr int CW = TD_BW / NW;   // columns of this wavefront
+                const int i = lane & 31, cw = wv * CW;
+                T y[CW];
+#pragma unroll
+                for (int q = 0; q < CW; ++q) y[q] = ub1[i * LDU + cw + q];
+#pragma unroll
+                for (int k = 0; k < TD_BW - 1; ++k) {
+                    const T c = lkk[k * (TD_BW + 1) + i];
+#pragma unroll
+                    for (int q = 0; q < CW; ++q) y[q] = fma_(-c, lane_value(y[q], k), y[q]);
+                }
+                if (lane < 32) {
+#pragma unroll
+                    for (int q = 0; q < CW; ++q) ub2[i * LDU + cw + q] = -y[q];
+                }
+                if (K + 1 < J) load_inverse(K + 1);
+            } else if (wv < 4) {
 #pragma unroll
                 for (int u = 0; u < UT; ++u) {
                     const int si0 = ((wv + NW * u) >> 1) & 1, sj0 = (wv + NW * u) & 1;
@@ -386,46 +433,62 @@ __global__ void __launch_bounds__(64 * NW, 2) lu_td_kernel(T *__restrict__ Aall,
                 if (K + 1 < J) load_inverse(K + 1);
             }
             __syncthreads();
-            // tiles behind K: C -= L U
-            T br[NH][W][2], bi[CX ? NH : 1][W][2];
+            if constexpr (STD) {
 #pragma unroll
-            for (int h = 0; h < NH; ++h)
+                for (int u = 0; u < LE; ++u) {
+                    const int e = tid + u * NTH, r = e >> 5, c = e & 31;
+                    if (c < nbj) *at(Ar, cur[32 * K + r] * ldb + jb + c * sizeof(T)) = -ub2[r * LDU + c];
+                }
+            }
+            // tiles behind K: C -= L U, HB segments of 16 bytes of each operand
+            // per lane at a time: all of them where accumulators and operands
+            // leave registers (all at once, 4096 complex FP32 matrices of 395
+            // spill and take 16.5 instead of 14.5 ms, 1024 complex FP64 9.1
+            // instead of 8.3)
+            constexpr int SZ = sizeof(T) / 4;
+            constexpr int HB = (16 * SLOTS + 2 * 16) * P * SZ >= 192 ? 1 : NH;
 #pragma unroll
-                for (int s = 0; s < W; ++s)
+            for (int hb = 0; hb < NH; hb += HB) {
+                T br[HB][W][2], bi[HB][W][2];
 #pragma unroll
-                    for (int sj = 0; sj < 2; ++sj) {
-                        const int o = (4 * W * h + W * g + s) * LDU + 16 * sj + l16;
-                        br[h][s][sj] = ub2[o];
-                        if constexpr (CX) bi[h][s][sj] = ub2[TD_BW * LDU + o];
-                    }
+                for (int h = 0; h < HB; ++h)
 #pragma unroll
-            for (int s = 0; s < SLOTS; ++s) {
-                const int t = wv + NW * s;
-                if (t > K && t < nt) {
-                    seg_t lr[2][NH], li[CX ? 2 : 1][CX ? NH : 1];
+                    for (int u = 0; u < W; ++u)
 #pragma unroll
-                    for (int si = 0; si < 2; ++si)
-#pragma unroll
-                        for (int h = 0; h < NH; ++h) {
-                            const unsigned o = ro[s][si] + 32 * K * sizeof(T) + 64 * h;
-                            lr[si][h] = *(const seg_t *)at(Ar, o);
-                            if constexpr (CX) li[si][h] = *(const seg_t *)at(Ai, o);
+                        for (int sj = 0; sj < 2; ++sj) {
+                            const int o = (4 * W * (hb + h) + W * g + u) * LDU + 16 * sj + l16;
+                            br[h][u][sj] = ub2[o];
+                            bi[h][u][sj] = CX ? ub2[CX ? TD_BW * LDU + o : 0] : T(0);
                         }
 #pragma unroll
-                    for (int h = 0; h < NH; ++h)
+                for (int s = 0; s < SLOTS; ++s) {
+                    const int t = wv + NW * s;
+                    if (t > K && t < nt) {
+                        seg_t lr[2][HB], li[2][HB];
 #pragma unroll
-                        for (int u = 0; u < W; ++u)
+                        for (int si = 0; si < 2; ++si)
 #pragma unroll
-                            for (int si = 0; si < 2; ++si)
+                            for (int h = 0; h < HB; ++h) {
+                                const unsigned o = ro[s][si] + 32 * K * sizeof(T) + 64 * (hb + h);
+                                lr[si][h] = *(const seg_t *)at(Ar, o);
+                                if constexpr (CX) li[si][h] = *(const seg_t *)at(Ai, o);
+                            }
 #pragma unroll
-                                for (int sj = 0; sj < 2; ++sj) {
-                                    ar[s][si][sj] = V::mfma(lr[si][h][u], br[h][u][sj], ar[s][si][sj]);
-                                    if constexpr (CX) {
-                                        ar[s][si][sj] = V::mfma(-li[si][h][u], bi[h][u][sj], ar[s][si][sj]);
-                                        ai[s][si][sj] = V::mfma(lr[si][h][u], bi[h][u][sj], ai[s][si][sj]);
-                                        ai[s][si][sj] = V::mfma(li[si][h][u], br[h][u][sj], ai[s][si][sj]);
+                        for (int h = 0; h < HB; ++h)
+#pragma unroll
+                            for (int u = 0; u < W; ++u)
+#pragma unroll
+                                for (int si = 0; si < 2; ++si)
+#pragma unroll
+                                    for (int sj = 0; sj < 2; ++sj) {
+                                        ar[s][si][sj] = V::mfma(lr[si][h][u], br[h][u][sj], ar[s][si][sj]);
+                                        if constexpr (CX) {
+                                            ar[s][si][sj] = V::mfma(-li[si][h][u], bi[h][u][sj], ar[s][si][sj]);
+                                            ai[s][si][sj] = V::mfma(lr[si][h][u], bi[h][u][sj], ai[s][si][sj]);
+                                            ai[s][si][sj] = V::mfma(li[si][h][u], br[h][u][sj], ai[s][si][sj]);
+                                        }
                                     }
-                                }
+                    }
                 }
             }
         }
@@ -441,10 +504,11 @@ __global__ void __launch_bounds__(64 * NW, 2) lu_td_kernel(T *__restrict__ Aall,
                 rk[r] = -1;
             }
         }
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int c0 = 16 * h, nb = min(16, nbj - c0);
-            if (nb <= 0) break;
+        static_for(std::make_integer_sequence<int, TD_BW / PW>{}, [&](auto hc) {
+            constexpr int h = decltype(hc)::value, c0 = PW * h;
+            constexpr int sjh = c0 / 16, cs = c0 % 16;   // the panel's accumulator tile and its first column there
+            const int nb = min(PW, nbj - c0);
+            if (nb <= 0) return;
             __syncthreads();   // the panel region is free
 #pragma unroll
             for (int s = 0; s < SLOTS; ++s) {
@@ -455,29 +519,29 @@ __global__ void __launch_bounds__(64 * NW, 2) lu_td_kernel(T *__restrict__ Aall,
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {
                             const int r = 32 * (t - J) + 16 * si + V::row(g, i);
-                            if (r < mr) {
-                                T *q = pan + (r * TD_LS + l16) * P;
-                                q[0] = ar[s][si][h][i];
-                                if constexpr (CX) q[1] = ai[s][si][h][i];
+                            if (r < mr && (PW == 16 || (l16 >= cs && l16 < cs + PW))) {
+                                T *q = pan + (r * LS + l16 - cs) * P;
+                                q[0] = ar[s][si][sjh][i];
+                                if constexpr (CX) q[1] = ai[s][si][sjh][i];
                             }
                         }
                 }
             }
             __syncthreads();
             {
-                T xr[RPT][16], xi[CX ? RPT : 1][16];
+                T xr[RPT][PW], xi[CX ? RPT : 1][PW];
 #pragma unroll
                 for (int i = 0; i < RPT; ++i) {
-                    const T *q = pan + min(tid + i * NTH, mr - 1) * TD_LS * P;
+                    const T *q = pan + min(tid + i * NTH, mr - 1) * LS * P;
 #pragma unroll
-                    for (int k = 0; k < 16; ++k) {
+                    for (int k = 0; k < PW; ++k) {
                         xr[i][k] = q[k * P];
                         if constexpr (CX) xi[i][k] = q[k * P + 1];
                     }
                 }
                 // columns c .. of a row are x[.][0 ..]: every step shifts by one as it updates.
                 // One barrier per column; no branches but the publishing ones.
-                T *urow = ub1;   // [16][16] pivot rows from their own column on
+                T *urow = ub1;   // [PW][PW] pivot rows from their own column on
                 auto columns = [&](auto width, int cb) {
                     constexpr int WD = decltype(width)::value;
                     const int ce = min(cb + 4, nb);
@@ -485,18 +549,26 @@ __global__ void __launch_bounds__(64 * NW, 2) lu_td_kernel(T *__restrict__ Aall,
                     for (int c = cb; c < ce; ++c) {
                         const int par = c & 1;
                         T best = T(-1);
-                        int bi_ = 0;
+                        int bi_ = 0, bl = 0x7fffffff;
 #pragma unroll
                         for (int i = 0; i < RPT; ++i) {
-                            T v = CX ? xr[i][0] * xr[i][0] + xi[CX ? i : 0][0] * xi[CX ? i : 0][0]
+                            T v = CX ? fma_(xr[i][0], xr[i][0], xi[CX ? i : 0][0] * xi[CX ? i : 0][0])
                                      : (xr[i][0] < 0 ? -xr[i][0] : xr[i][0]);
                             v = v >= T(0) ? v : T(0);   // NaN
-                            const bool better = ((open >> i) & 1u) && v > best;
+                            const bool better = ((open >> i) & 1u) && (v > best || (STD && v == best && lg[i] < bl));
                             best = better ? v : best;
+                            bl = better ? lg[i] : bl;
                             bi_ = better ? i : bi_;
                         }
                         const T wm = wave_max(best);
-                        const bool cand = lane == __builtin_ctzll(__ballot(best == wm));
+                        unsigned long long hit = __ballot(best == wm);
+                        if (STD && __popcll(hit) > 1) {
+                            // LAPACK: ties go to the smallest position
+                            int low = best == wm ? bl : 0x7fffffff;
+                            for (int off = 32; off > 0; off >>= 1) low = min(low, __shfl_xor(low, off, 64));
+                            hit = __ballot(best == wm && bl == low);
+                        }
+                        const bool cand = lane == __builtin_ctzll(hit);
                         // the wavefront's candidate publishes its row
                         auto publish = [&](T *q, int i) {
 #pragma unroll
@@ -524,7 +596,8 @@ __global__ void __launch_bounds__(64 * NW, 2) lu_td_kernel(T *__restrict__ Aall,
                         for (int hh = NW / 2; hh > 0; hh /= 2)
 #pragma unroll
                             for (int w = 0; w < hh; ++w) {
-                                const bool better = bv[w + hh] > bv[w];
+                                const bool better =
+                                    bv[w + hh] > bv[w] || (STD && bv[w + hh] == bv[w] && bk[w + hh] >> 16 < bk[w] >> 16);
                                 bv[w] = better ? bv[w + hh] : bv[w];
                                 bk[w] = better ? bk[w + hh] : bk[w];
                             }
@@ -542,6 +615,7 @@ __global__ void __launch_bounds__(64 * NW, 2) lu_td_kernel(T *__restrict__ Aall,
                         if (tid == 0) {
                             pl[c0 + c] = R;
                             rk[R] = c0 + c;
+                            if constexpr (STD) ip[j0 + c0 + c] = j0 + p;
                             if (info && bv[0] == T(0)) atomicAdd(info, 1);
                         }
                         T ir, ii;
@@ -553,8 +627,8 @@ __global__ void __launch_bounds__(64 * NW, 2) lu_td_kernel(T *__restrict__ Aall,
                             const bool op = (open >> i) & 1u, me = op && r == R, upd = op && !me;
                             T tr, ti;
                             if constexpr (CX) {
-                                tr = xr[i][0] * ir - xi[i][0] * ii;
-                                ti = xr[i][0] * ii + xi[i][0] * ir;
+                                tr = fma_(xr[i][0], ir, -(xi[i][0] * ii));
+                                ti = fma_(xr[i][0], ii, xi[i][0] * ir);
                             } else {
                                 tr = xr[i][0] * ir;
                                 ti = T(0);
@@ -562,10 +636,10 @@ __global__ void __launch_bounds__(64 * NW, 2) lu_td_kernel(T *__restrict__ Aall,
                             lr[i] = upd ? tr : T(0);
                             li[i] = upd ? ti : T(0);
                             // (other rows write their padding entry)
-                            T *q = pan + (min(r, m - 1) * TD_LS + (upd ? c : 16)) * P;
+                            T *q = pan + (min(r, m - 1) * LS + (upd ? c : PW)) * P;
                             q[0] = lr[i];
                             if constexpr (CX) q[1] = li[i];
-                            if (me) publish(urow + c * 16 * P, i);
+                            if (me) publish(urow + c * PW * P, i);
                             lg[i] = me ? c0 + c : (op && lg[i] == c0 + c ? p : lg[i]);
                             open = me ? open & ~(1u << i) : open;
                         }
@@ -576,49 +650,49 @@ __global__ void __launch_bounds__(64 * NW, 2) lu_td_kernel(T *__restrict__ Aall,
                             if (64 * wv + i * NTH >= mr) continue;
 #pragma unroll
                             for (int k = 1; k < WD; ++k) {
-                                T vr = xr[i][k] - lr[i] * ur[k];
+                                T vr = fma_(-lr[i], ur[k], xr[i][k]);
                                 if constexpr (CX) {
-                                    T vi = xi[i][k] - lr[i] * ui[k];
-                                    vr += li[i] * ui[k];
-                                    vi -= li[i] * ur[k];
-                                    xi[i][k - 1] = vi;
+                                    vr = fma_(li[i], ui[k], vr);
+                                    xi[i][k - 1] = fma_(-li[i], ur[k], fma_(-lr[i], ui[k], xi[i][k]));
                                 }
                                 xr[i][k - 1] = vr;
                             }
                         }
                     }
                 };
-                columns(std::integral_constant<int, 16>{}, 0);
-                if (nb > 4) columns(std::integral_constant<int, 12>{}, 4);
-                if (nb > 8) columns(std::integral_constant<int, 8>{}, 8);
-                if (nb > 12) columns(std::integral_constant<int, 4>{}, 12);
+                static_for(std::make_integer_sequence<int, PW / 4>{}, [&](auto q) {
+                    constexpr int cb = 4 * decltype(q)::value;
+                    if (cb < nb) columns(std::integral_constant<int, PW - cb>{}, cb);
+                });
                 __syncthreads();
-                for (int e = tid; e < 256; e += NTH) {
-                    const int c = e >> 4, k = e & 15;
-                    if (c < nb && c + k < 16) {
-                        T *q = pan + (pl[c0 + c] * TD_LS + c + k) * P;
-                        q[0] = urow[(c * 16 + k) * P];
-                        if constexpr (CX) q[1] = urow[(c * 16 + k) * P + 1];
+                for (int e = tid; e < PW * PW; e += NTH) {
+                    const int c = e / PW, k = e % PW;
+                    if (c < nb && c + k < PW) {
+                        T *q = pan + (pl[c0 + c] * LS + c + k) * P;
+                        q[0] = urow[(c * PW + k) * P];
+                        if constexpr (CX) q[1] = urow[(c * PW + k) * P + 1];
                     }
                 }
             }
             __syncthreads();
             // the panel to A (rows that became pivots in the first panel hold U here already)
 #pragma unroll 4
-            for (int r = tid >> 4; r < mr; r += NTH / 16) {
-                const int c = tid & 15;
-                if (c < nb && !(h == 1 && rk[r] >= 0 && rk[r] < 16)) {
+            for (int r = tid / PW; r < mr; r += NTH / PW) {
+                const int c = tid % PW;
+                if (c < nb && !(h > 0 && rk[r] >= 0 && rk[r] < c0)) {
                     const unsigned o = cur[j0 + r] * ldb + jb + (c0 + c) * sizeof(T);
-                    *at(Ar, o) = pan[(r * TD_LS + c) * P];
-                    if constexpr (CX) *at(Ai, o) = pan[(r * TD_LS + c) * P + 1];
+                    *at(Ar, o) = pan[(r * LS + c) * P];
+                    if constexpr (CX) *at(Ai, o) = pan[(r * LS + c) * P + 1];
                 }
             }
             // inverses of the panel's triangles (identity beyond nb)
-            if (wv < 2) {
+            // (STD: only L's, and only for the rest of the block)
+            if (wv < (STD ? 1 : 2) && (!STD || c0 + PW < nbj)) {
                 T yr[4], yi[4];
-                const T *prow = pan + pl[c0 + min(l16, nb - 1)] * TD_LS * P;
+                const T *prow = pan + pl[c0 + min(l16, nb - 1)] * LS * P;
                 auto entry = [&](int i, int k, bool in, T &cr, T &ci) {
-                    const T vr = prow[k * P], vi = CX ? prow[k * P + 1] : T(0);
+                    const int kc = min(k, PW - 1);
+                    const T vr = prow[kc * P], vi = CX ? prow[kc * P + 1] : T(0);
                     cr = in && i < nb && k < nb ? vr : T(0);
                     ci = in && i < nb && k < nb ? vi : T(0);
                 };
@@ -626,13 +700,13 @@ __global__ void __launch_bounds__(64 * NW, 2) lu_td_kernel(T *__restrict__ Aall,
                 if (wv == 0) {
                     tri_inverse16<T, CX, false>([&](int i, int k, T &cr, T &ci) { entry(i, k, k < i, cr, ci); }, T(1),
                                                 T(0), yr, yi);
-                    dst = h == 0 ? sI1 : sI2;
+                    dst = STD || h == 0 ? sI1 : sI2;
                 } else {
                     T dr, di, rr = T(1), ri = T(0);
                     entry(l16, l16, true, dr, di);
                     if (l16 < nb) {
                         if constexpr (CX) {
-                            const T den = dr * dr + di * di;
+                            const T den = fma_(dr, dr, di * di);
                             rr = dr / den;
                             ri = -di / den;
                         } else {
@@ -650,82 +724,93 @@ __global__ void __launch_bounds__(64 * NW, 2) lu_td_kernel(T *__restrict__ Aall,
                     if constexpr (CX) d[1] = yi[q];
                 }
             }
-            if (h == 0 && nbj > 16) {
-                // the rest of the block: U12 = L11^{-1} A12, then C -= L21 U12
+            if (c0 + PW < nbj) {
+                // the rest of the block, one tile of 16 columns at a time (those
+                // of finished panels in it get garbage): U12 = L11^{-1} A12, then
+                // C -= L21 U12
                 T *u0 = ub1, *u12 = ub2;   // 16 x 16 blocks of row stride TD_LS
 #pragma unroll
-                for (int s = 0; s < SLOTS; ++s) {
-                    const int t = wv + NW * s;
-                    if (t >= J && t < nt) {
-#pragma unroll
-                        for (int si = 0; si < 2; ++si)
-#pragma unroll
-                            for (int i = 0; i < 4; ++i) {
-                                const int r = 32 * (t - J) + 16 * si + V::row(g, i);
-                                const int q = r < mr ? rk[r] : -1;
-                                if (q >= 0) {
-                                    u0[(q * TD_LS + l16) * P] = ar[s][si][1][i];
-                                    if constexpr (CX) u0[(q * TD_LS + l16) * P + 1] = ai[s][si][1][i];
-                                }
-                            }
-                    }
-                }
-                __syncthreads();
-                if (wv == 0) {
-                    acc_t dr = {0, 0, 0, 0}, di = {0, 0, 0, 0};
-                    mm16<T, CX>(sI1, u0, dr, di);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int r = V::row(g, i);
-                        u12[(r * TD_LS + l16) * P] = dr[i];
-                        if constexpr (CX) u12[(r * TD_LS + l16) * P + 1] = di[i];
-                        if (16 + l16 < nbj) {
-                            const unsigned o = cur[j0 + pl[r]] * ldb + jb + (16 + l16) * sizeof(T);
-                            *at(Ar, o) = dr[i];
-                            if constexpr (CX) *at(Ai, o) = di[i];
-                        }
-                    }
-                }
-                __syncthreads();
-                T br[16 / (4 * W)][W], bi[16 / (4 * W)][W];
-#pragma unroll
-                for (int hh = 0; hh < 16 / (4 * W); ++hh)
-#pragma unroll
-                    for (int s = 0; s < W; ++s) {
-                        const T *q = u12 + ((4 * W * hh + W * g + s) * TD_LS + l16) * P;
-                        br[hh][s] = -q[0];
-                        bi[hh][s] = CX ? -q[CX ? 1 : 0] : T(0);
+                for (int sj = 0; sj < 2; ++sj) {
+                    if (16 * sj + 16 <= c0 + PW) continue;
+                    if constexpr (PW < 16) {
+                        __syncthreads();   // the previous tile's U blocks are read
+                        for (int e = tid; e < 16 * (16 - PW); e += NTH) u0[(PW + e / 16) * TD_LS + e % 16] = T(0);
                     }
 #pragma unroll
-                for (int s = 0; s < SLOTS; ++s) {
-                    const int t = wv + NW * s;
-                    if (t >= J && t < nt) {
+                    for (int s = 0; s < SLOTS; ++s) {
+                        const int t = wv + NW * s;
+                        if (t >= J && t < nt) {
 #pragma unroll
-                        for (int si = 0; si < 2; ++si) {
-                            const T *q = pan + min(32 * (t - J) + 16 * si + l16, mr - 1) * TD_LS * P;
+                            for (int si = 0; si < 2; ++si)
 #pragma unroll
-                            for (int hh = 0; hh < 16 / (4 * W); ++hh)
-#pragma unroll
-                                for (int u = 0; u < W; ++u) {
-                                    const int k = 4 * W * hh + W * g + u;
-                                    const T lr = q[k * P];
-                                    ar[s][si][1] = V::mfma(lr, br[hh][u], ar[s][si][1]);
-                                    if constexpr (CX) {
-                                        const T li = q[k * P + 1];
-                                        ar[s][si][1] = V::mfma(-li, bi[hh][u], ar[s][si][1]);
-                                        ai[s][si][1] = V::mfma(lr, bi[hh][u], ai[s][si][1]);
-                                        ai[s][si][1] = V::mfma(li, br[hh][u], ai[s][si][1]);
+                                for (int i = 0; i < 4; ++i) {
+                                    const int r = 32 * (t - J) + 16 * si + V::row(g, i);
+                                    const int q = r < mr ? rk[r] - c0 : -1;
+                                    if (q >= 0) {
+                                        u0[(q * TD_LS + l16) * P] = ar[s][si][sj][i];
+                                        if constexpr (CX) u0[(q * TD_LS + l16) * P + 1] = ai[s][si][sj][i];
                                     }
                                 }
                         }
                     }
+                    __syncthreads();
+                    if (wv == 0) {
+                        acc_t dr = {0, 0, 0, 0}, di = {0, 0, 0, 0};
+                        mm16<T, CX>(sI1, u0, dr, di);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const int r = V::row(g, i), c = 16 * sj + l16;
+                            u12[(r * TD_LS + l16) * P] = dr[i];
+                            if constexpr (CX) u12[(r * TD_LS + l16) * P + 1] = di[i];
+                            if (r < PW && c >= c0 + PW && c < nbj) {
+                                const unsigned o = cur[j0 + pl[c0 + r]] * ldb + jb + c * sizeof(T);
+                                *at(Ar, o) = dr[i];
+                                if constexpr (CX) *at(Ai, o) = di[i];
+                            }
+                        }
+                    }
+                    __syncthreads();
+                    constexpr int HP = PW / (4 * W);
+                    T br[HP][W], bi[HP][W];
+#pragma unroll
+                    for (int hh = 0; hh < HP; ++hh)
+#pragma unroll
+                        for (int s = 0; s < W; ++s) {
+                            const T *q = u12 + ((4 * W * hh + W * g + s) * TD_LS + l16) * P;
+                            br[hh][s] = -q[0];
+                            bi[hh][s] = CX ? -q[CX ? 1 : 0] : T(0);
+                        }
+#pragma unroll
+                    for (int s = 0; s < SLOTS; ++s) {
+                        const int t = wv + NW * s;
+                        if (t >= J && t < nt) {
+#pragma unroll
+                            for (int si = 0; si < 2; ++si) {
+                                const T *q = pan + min(32 * (t - J) + 16 * si + l16, mr - 1) * LS * P;
+#pragma unroll
+                                for (int hh = 0; hh < HP; ++hh)
+#pragma unroll
+                                    for (int u = 0; u < W; ++u) {
+                                        const int k = 4 * W * hh + W * g + u;
+                                        const T lr = q[k * P];
+                                        ar[s][si][sj] = V::mfma(lr, br[hh][u], ar[s][si][sj]);
+                                        if constexpr (CX) {
+                                            const T li = q[k * P + 1];
+                                            ar[s][si][sj] = V::mfma(-li, bi[hh][u], ar[s][si][sj]);
+                                            ai[s][si][sj] = V::mfma(lr, bi[hh][u], ai[s][si][sj]);
+                                            ai[s][si][sj] = V::mfma(li, br[hh][u], ai[s][si][sj]);
+                                        }
+                                    }
+                            }
+                        }
+                    }
                 }
             }
-        }
+        });
         __syncthreads();
         // ---- the diagonal block: L_JJ^{-1} = [I1; -I2 L21 I1, I2], U_JJ^{-1} =
         //      [V1, -V1 U12 V2; V2] -------------------------------------------------------
-        if (wv < 2) {
+        if (!STD && wv < 2) {
             // scratch blocks: L21, product of the lower part, product of the upper part
             T *l21 = ub1, *p1 = ub1 + SB, *p2 = pan;
             acc_t dr = {0, 0, 0, 0}, di = {0, 0, 0, 0};
@@ -794,7 +879,68 @@ __global__ void __launch_bounds__(64 * NW, 2) lu_td_kernel(T *__restrict__ Aall,
             if (tid + i * NTH < mr) cur[j0 + lg[i]] = row[i];
         __syncthreads();
     }
-    for (int p = tid; p < m; p += NTH) perm[p] = cur[p];
+    if constexpr (!STD) {
+        for (int p = tid; p < m; p += NTH) ip[p] = cur[p];
+    } else {
+        // rows to their positions, 32 columns at a time through registers
+#pragma unroll 1
+        for (int J = 0; J < nt; ++J) {
+            int lane = tid & 63;
+            asm volatile("" : "+v"(lane));
+            const int c = 32 * J + (lane & 31);
+            const unsigned cb = min(c, m - 1) * sizeof(T);
+            T v[SLOTS][16];
+#pragma unroll
+            for (int s = 0; s < SLOTS; ++s)
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    v[s][i] = *at(Ar, cur[min(32 * (wv + NW * s) + 2 * i + (lane >> 5), m - 1)] * ldb + cb);
+            __syncthreads();
+#pragma unroll
+            for (int s = 0; s < SLOTS; ++s)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const int p = 32 * (wv + NW * s) + 2 * i + (lane >> 5);
+                    if (p < m && c < m) *at(Ar, p * ldb + cb) = v[s][i];
+                }
+            __syncthreads();
+        }
+    }
+}
+
+template <typename T, bool CX, int NW, int SLOTS, int RPT>
+__global__ void __launch_bounds__(64 * NW, 2) lu_td_kernel(T *__restrict__ A, int *__restrict__ perm, int m, int ld,
+                                                        long long a_stride, int *info)
+{
+    extern __shared__ unsigned char lds_raw[];
+    lu_left<T, CX, NW, SLOTS, RPT, TD_PW, false>(A + (long long)blockIdx.x * a_stride, m, ld,
+                                                 perm + (long long)blockIdx.x * m, info, lds_raw);
+}
+
+// a batch of real matrices of mixed sizes in LAPACK's format, one workgroup per
+// matrix (block b: entry b of the metadata).  LARGE: above 512 rows.
+constexpr int STD_SMALL_M = 512;
+template <typename T, bool LARGE>
+__global__ void __launch_bounds__(LARGE ? 512 : 256, 2) lu_std_kernel(T *__restrict__ A, int *__restrict__ piv, LuBatch B,
+                                                                   int *info)
+{
+    extern __shared__ unsigned char lds_raw[];
+    const int m = __builtin_amdgcn_readfirstlane(B.m_of[blockIdx.x]);
+    T *a = A + B.a_off[blockIdx.x];
+    int *ip = piv + B.p_off[blockIdx.x];
+    if constexpr (LARGE) {
+        constexpr int PW = sizeof(T) == 8 ? 8 : 16;
+        if constexpr (sizeof(T) == 4) {
+            if (m > 1280) {
+                lu_left<T, false, 8, 8, 4, PW, true>(a, m, m, ip, info, lds_raw);
+                return;
+            }
+        }
+        lu_left<T, false, 8, 5, 3, PW, true>(a, m, m, ip, info, lds_raw);
+    } else {
+        if (m <= 256) lu_left<T, false, 4, 2, 1, 16, true>(a, m, m, ip, info, lds_raw);
+        else lu_left<T, false, 4, 4, 2, 16, true>(a, m, m, ip, info, lds_raw);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -872,12 +1018,10 @@ __device__ __forceinline__ void td_substitute(const TF *__restrict__ Lr, const T
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             if constexpr (CX) {
-                sr += ar.v[e] * xr[e];
-                sr -= ai.v[e] * xi[e];
-                si += ar.v[e] * xi[e];
-                si += ai.v[e] * xr[e];
+                sr = fma_(-ai.v[e], xi[e], fma_(ar.v[e], xr[e], sr));
+                si = fma_(ai.v[e], xr[e], fma_(ar.v[e], xi[e], si));
             } else {
-                sr += ar.v[e] * xr[e];
+                sr = fma_(ar.v[e], xr[e], sr);
             }
         }
     };
@@ -1038,8 +1182,8 @@ __global__ void __launch_bounds__(TDS_THREADS, sizeof(TP) == 8 ? 2 : 4) solve_td
             if (i < MS) {
                 const int src = perm[i];
                 for (int a = 0; a < nt; ++a) {
-                    sr += A.Tre[s * 4 + a] * rl[a * MSP + src];
-                    si += A.Tim[s * 4 + a] * rl[a * MSP + src];
+                    sr = fma_(A.Tre[s * 4 + a], rl[a * MSP + src], sr);
+                    si = fma_(A.Tim[s * 4 + a], rl[a * MSP + src], si);
                 }
             }
             br[i] = sr;
@@ -1052,7 +1196,7 @@ __global__ void __launch_bounds__(TDS_THREADS, sizeof(TP) == 8 ? 2 : 4) solve_td
         for (int j = tid; j < MS; j += TDS_THREADS)
             for (int a = 0; a < nt; ++a) {
                 TP v = A.Fre[a * 4 + s] * br[j];
-                if (cx) v -= A.Fim[a * 4 + s] * bi[j];
+                if (cx) v = fma_(-A.Fim[a * 4 + s], bi[j], v);
                 out[a * MSP + j] += v;
             }
         __syncthreads();
@@ -1061,7 +1205,10 @@ __global__ void __launch_bounds__(TDS_THREADS, sizeof(TP) == 8 ? 2 : 4) solve_td
     for (int j = tid; j < MS; j += TDS_THREADS)
         for (int a = 0; a < nt; ++a) {
             if (j < NV) Ec[a * NV + j] = (T)out[a * MSP + j];
-            else A.d[pbase + a * A.Np1 + (long long)cell * NPM + (j - NV)] += A.omega * (T)out[a * MSP + j];
+            else {
+                T &d = A.d[pbase + a * A.Np1 + (long long)cell * NPM + (j - NV)];
+                d = fma_(A.omega, (T)out[a * MSP + j], d);
+            }
         }
 }
 
@@ -1081,7 +1228,7 @@ hipError_t launch_lu_td(T *A, int *perm, int m, int ld, bool cplx, int batch, in
 #define LTD(CX, NW, SLOTS, RPT)                                                                                        \
     {                                                                                                                  \
         static_assert(SLOTS <= 2 * RPT, "panel rows cover the tiles");                                                 \
-        const size_t bytes = td_lu_lds_bytes<T, CX>(m);                                                                \
+        const size_t bytes = left_lu_lds_bytes<T, CX, TD_PW, false>(m);                                                                \
         hipError_t e = lds_attr((const void *)lu_td_kernel<T, CX, NW, SLOTS, RPT>, bytes);                             \
         if (e != hipSuccess) return e;                                                                                 \
         hipLaunchKernelGGL((lu_td_kernel<T, CX, NW, SLOTS, RPT>), dim3(batch), dim3(64 * NW), bytes, s, A, perm, m,    \
@@ -1124,6 +1271,38 @@ hipError_t launch_solve_td(int dim, int r, const SolveTdArgs<T, TP, TF> &a, int 
     return hipErrorInvalidValue;
 }
 
+// Large matrices first (the batch is sorted by decreasing size): one launch of
+// 8 wavefronts per matrix and one or two matrices per CU above 512 rows, one
+// of 4 wavefronts and two to four matrices per CU for the rest.
+template <typename T>
+hipError_t launch_lu_std(T *A, int *piv, const LuBatch &b, const int *m_host, int batch, int *info, hipStream_t s)
+{
+    int nl = 0;
+    while (nl < batch && m_host[nl] > STD_SMALL_M) ++nl;
+#define LSTD(LARGE, NTH, PW, M, N, MB)                                                                                 \
+    {                                                                                                                  \
+        const size_t bytes = left_lu_lds_bytes<T, false, PW, true>(M);                                                 \
+        hipError_t e = lds_attr((const void *)lu_std_kernel<T, LARGE>, bytes);                                         \
+        if (e != hipSuccess) return e;                                                                                 \
+        hipLaunchKernelGGL((lu_std_kernel<T, LARGE>), dim3(N), dim3(NTH), bytes, s, A, piv, MB, info);                 \
+        e = hipGetLastError();                                                                                         \
+        if (e != hipSuccess) return e;                                                                                 \
+    }
+    if (nl > 0 && m_host[0] > lu_std_max_m(sizeof(T) == 8)) return hipErrorInvalidValue;
+    if (nl > 0) LSTD(true, 512, (sizeof(T) == 8 ? 8 : 16), m_host[0], nl, b)
+    if (nl < batch) {
+        LuBatch r = b;
+        r.m_of += nl;
+        r.a_off += nl;
+        r.p_off += nl;
+        LSTD(false, 256, 16, m_host[nl], batch - nl, r)
+    }
+#undef LSTD
+    return hipSuccess;
+}
+
+template hipError_t launch_lu_std<double>(double *, int *, const LuBatch &, const int *, int, int *, hipStream_t);
+template hipError_t launch_lu_std<float>(float *, int *, const LuBatch &, const int *, int, int *, hipStream_t);
 template hipError_t launch_lu_td<double>(double *, int *, int, int, bool, int, int *, hipStream_t);
 template hipError_t launch_lu_td<float>(float *, int *, int, int, bool, int, int *, hipStream_t);
 template hipError_t launch_solve_td(int, int, const SolveTdArgs<double, double, double> &, int, hipStream_t);

@@ -133,6 +133,12 @@ hipError_t launch_patch_td(int dim, int r, const PatchTdArgs<TE, TP> &a, int nce
 // triangles (strict lower part: L^{-1}, upper triangle: U^{-1}).
 template <typename T>
 hipError_t launch_lu_td(T *A, int *perm, int m, int ld, bool cplx, int batch, int *info, hipStream_t s);
+// the same left-looking factorization of real matrices of mixed sizes (sorted
+// by decreasing size; b: device metadata, m_host: the sizes), LAPACK's format
+// as launch_lu_queue leaves it; sizes up to lu_std_max_m
+constexpr int lu_std_max_m(bool f64) { return f64 ? 1280 : 1856; }
+template <typename T>
+hipError_t launch_lu_std(T *A, int *piv, const LuBatch &b, const int *m_host, int batch, int *info, hipStream_t s);
 // one sweep's patch solves with those factors
 template <typename T, typename TP, typename TF>
 hipError_t launch_solve_td(int dim, int r, const SolveTdArgs<T, TP, TF> &a, int ncell, hipStream_t s);
