@@ -122,6 +122,8 @@ __device__ __forceinline__ float wave_max(float x)
     v = max(v, __builtin_amdgcn_update_dpp(lowest, v, 0x143, 0xc, 0xf, false));
     return __int_as_float(__builtin_amdgcn_readlane(v, 63));
 }
+__device__ __forceinline__ float max_of(float a, float b) { return fmaxf(a, b); }
+__device__ __forceinline__ double max_of(double a, double b) { return fmax(a, b); }
 __device__ __forceinline__ double wave_max(double v)
 {
     v = fmax(v, dpp<0x111, 0xf>(v));
@@ -257,7 +259,7 @@ template <typename T, bool CX, int NW, int SLOTS, int RPT, int PW, bool STD>
 __device__ __forceinline__ void lu_left(T *__restrict__ Ar, int m, int ld, int *__restrict__ ip, int *info,
                                         unsigned char *lds_raw)
 {
-    static_assert(!(STD && CX), "the LAPACK format is real");
+    static_assert(!STD || (!CX && NW <= 8), "the LAPACK format is real");
     using V = Vec<T>;
     using acc_t = typename V::acc;
     using seg_t = typename V::seg;
@@ -319,13 +321,19 @@ __device__ __forceinline__ void lu_left(T *__restrict__ Ar, int m, int ld, int *
                 }
         }
         // ---- updates of the finished block columns ------------------------------------
-        // row offsets of the L operands of this wavefront's tiles
-        unsigned ro[SLOTS][2];
+        // row offsets of the L operands of this wavefront's tiles (many tiles:
+        // looked up for each segment, the accumulators leave no registers)
+        constexpr bool RO = SLOTS <= 4;
+        unsigned ro[RO ? SLOTS : 1][2];
+        auto row_offset = [&](int s, int si) -> unsigned {
+            return cur[min(32 * (wv + NW * s) + 16 * si + l16, m - 1)] * ldb + 16 * g;
+        };
+        if constexpr (RO) {
 #pragma unroll
-        for (int s = 0; s < SLOTS; ++s)
+            for (int s = 0; s < SLOTS; ++s)
 #pragma unroll
-            for (int si = 0; si < 2; ++si) 
-                ro[s][si] = cur[min(32 * (wv + NW * s) + 16 * si + l16, m - 1)] * ldb + 16 * g;
+                for (int si = 0; si < 2; ++si) ro[s][si] = row_offset(s, si);
+        }
         // U = L_KK^{-1} (tile K), its four 16 x 16 tiles spread over the
         // wavefronts (tile q: rows 16 (q / 2), columns 16 (q % 2)); the rows
         // of L_KK^{-1} are loaded one block ahead
@@ -381,20 +389,36 @@ __device__ __forceinline__ void lu_left(T *__restrict__ Ar, int m, int ld, int *
             }
             __syncthreads();
             if constexpr (STD) {
-                constexpr int CW = TD_BW / NW;   // columns of this wavefront
-                const int i = lane & 31, cw = wv * CW;
-                T y[CW];
+                // lane (i, g): rows i and 16 + i of CL columns, the solved
+                // rows broadcast inside the 16-lane rows
+                constexpr int CL = TD_BW / NW / 4 > 0 ? TD_BW / NW / 4 : 1;
+                const int cw = wv * (TD_BW / NW) + g * CL;
+                T y0[CL], y1[CL];
 #pragma unroll
-                for (int q = 0; q < CW; ++q) y[q] = ub1[i * LDU + cw + q];
-#pragma unroll
-                for (int k = 0; k < TD_BW - 1; ++k) {
-                    const T c = lkk[k * (TD_BW + 1) + i];
-#pragma unroll
-                    for (int q = 0; q < CW; ++q) y[q] = fma_(-c, lane_value(y[q], k), y[q]);
+                for (int q = 0; q < CL; ++q) {
+                    y0[q] = ub1[l16 * LDU + cw + q];
+                    y1[q] = ub1[(16 + l16) * LDU + cw + q];
                 }
-                if (lane < 32) {
+                static_for(std::make_integer_sequence<int, 16>{}, [&](auto kk) {
+                    constexpr int k = decltype(kk)::value;
+                    const T c0 = lkk[k * (TD_BW + 1) + l16], c1 = lkk[k * (TD_BW + 1) + 16 + l16];
 #pragma unroll
-                    for (int q = 0; q < CW; ++q) ub2[i * LDU + cw + q] = -y[q];
+                    for (int q = 0; q < CL; ++q) {
+                        const T v = dpp<0x150 + k, 0xf>(y0[q]);
+                        y0[q] = fma_(-c0, v, y0[q]);
+                        y1[q] = fma_(-c1, v, y1[q]);
+                    }
+                });
+                static_for(std::make_integer_sequence<int, 15>{}, [&](auto kk) {
+                    constexpr int k = decltype(kk)::value;
+                    const T c1 = lkk[(16 + k) * (TD_BW + 1) + 16 + l16];
+#pragma unroll
+                    for (int q = 0; q < CL; ++q) y1[q] = fma_(-c1, dpp<0x150 + k, 0xf>(y1[q]), y1[q]);
+                });
+#pragma unroll
+                for (int q = 0; q < CL; ++q) {
+                    ub2[l16 * LDU + cw + q] = -y0[q];
+                    ub2[(16 + l16) * LDU + cw + q] = -y1[q];
                 }
                 if (K + 1 < J) load_inverse(K + 1);
             } else if (wv < 4) {
@@ -440,64 +464,75 @@ __device__ __forceinline__ void lu_left(T *__restrict__ Ar, int m, int ld, int *
                     if (c < nbj) *at(Ar, cur[32 * K + r] * ldb + jb + c * sizeof(T)) = -ub2[r * LDU + c];
                 }
             }
-            // tiles behind K: C -= L U, HB segments of 16 bytes of each operand
-            // per lane at a time: all of them where accumulators and operands
-            // leave registers (all at once, 4096 complex FP32 matrices of 395
-            // spill and take 16.5 instead of 14.5 ms, 1024 complex FP64 9.1
-            // instead of 8.3)
-            constexpr int SZ = sizeof(T) / 4;
-            constexpr int HB = (16 * SLOTS + 2 * 16) * P * SZ >= 192 ? 1 : NH;
+            // tiles behind K: C -= L U, one 16-byte segment of L per lane and
+            // row tile at a time, the next one loaded before the products of
+            // the current (512 real FP64 matrices of 1185, whose loads were
+            // waited for: 40 -> 33 ms; 4096 complex FP32 of 395: 14.5 -> 14.0)
+            seg_t nr[2], ni[2];
+            auto load_l = [&](int s, int h) {
 #pragma unroll
-            for (int hb = 0; hb < NH; hb += HB) {
-                T br[HB][W][2], bi[HB][W][2];
+                for (int si = 0; si < 2; ++si) {
+                    const unsigned o = (RO ? ro[RO ? s : 0][si] : row_offset(s, si)) + 32 * K * sizeof(T) + 64 * h;
+                    nr[si] = *(const seg_t *)at(Ar, o);
+                    if constexpr (CX) ni[si] = *(const seg_t *)at(Ai, o);
+                }
+            };
+            bool loaded = false;
 #pragma unroll
-                for (int h = 0; h < HB; ++h)
+            for (int s = 0; s < SLOTS; ++s) {
+                const int t = wv + NW * s;
+                if (t > K && t < nt) {
+                    if (!loaded) load_l(s, 0);
+                    loaded = true;
 #pragma unroll
-                    for (int u = 0; u < W; ++u)
+                    for (int h = 0; h < NH; ++h) {
+                        seg_t lr[2], li[2];
 #pragma unroll
-                        for (int sj = 0; sj < 2; ++sj) {
-                            const int o = (4 * W * (hb + h) + W * g + u) * LDU + 16 * sj + l16;
-                            br[h][u][sj] = ub2[o];
-                            bi[h][u][sj] = CX ? ub2[CX ? TD_BW * LDU + o : 0] : T(0);
+                        for (int si = 0; si < 2; ++si) {
+                            lr[si] = nr[si];
+                            if constexpr (CX) li[si] = ni[si];
                         }
+                        // (past the last tile: a row that exists, not used)
+                        if (h + 1 < NH) load_l(s, h + 1);
+                        else if (s + 1 < SLOTS) load_l(s + 1, 0);
+                        T br[W][2], bi[W][2];
 #pragma unroll
-                for (int s = 0; s < SLOTS; ++s) {
-                    const int t = wv + NW * s;
-                    if (t > K && t < nt) {
-                        seg_t lr[2][HB], li[2][HB];
+                        for (int u = 0; u < W; ++u)
 #pragma unroll
-                        for (int si = 0; si < 2; ++si)
-#pragma unroll
-                            for (int h = 0; h < HB; ++h) {
-                                const unsigned o = ro[s][si] + 32 * K * sizeof(T) + 64 * (hb + h);
-                                lr[si][h] = *(const seg_t *)at(Ar, o);
-                                if constexpr (CX) li[si][h] = *(const seg_t *)at(Ai, o);
+                            for (int sj = 0; sj < 2; ++sj) {
+                                const int o = (4 * W * h + W * g + u) * LDU + 16 * sj + l16;
+                                br[u][sj] = ub2[o];
+                                bi[u][sj] = CX ? ub2[CX ? TD_BW * LDU + o : 0] : T(0);
                             }
 #pragma unroll
-                        for (int h = 0; h < HB; ++h)
+                        for (int u = 0; u < W; ++u)
 #pragma unroll
-                            for (int u = 0; u < W; ++u)
+                            for (int si = 0; si < 2; ++si)
 #pragma unroll
-                                for (int si = 0; si < 2; ++si)
-#pragma unroll
-                                    for (int sj = 0; sj < 2; ++sj) {
-                                        ar[s][si][sj] = V::mfma(lr[si][h][u], br[h][u][sj], ar[s][si][sj]);
-                                        if constexpr (CX) {
-                                            ar[s][si][sj] = V::mfma(-li[si][h][u], bi[h][u][sj], ar[s][si][sj]);
-                                            ai[s][si][sj] = V::mfma(lr[si][h][u], bi[h][u][sj], ai[s][si][sj]);
-                                            ai[s][si][sj] = V::mfma(li[si][h][u], br[h][u][sj], ai[s][si][sj]);
-                                        }
+                                for (int sj = 0; sj < 2; ++sj) {
+                                    ar[s][si][sj] = V::mfma(lr[si][u], br[u][sj], ar[s][si][sj]);
+                                    if constexpr (CX) {
+                                        ar[s][si][sj] = V::mfma(-li[si][u], bi[u][sj], ar[s][si][sj]);
+                                        ai[s][si][sj] = V::mfma(lr[si][u], bi[u][sj], ai[s][si][sj]);
+                                        ai[s][si][sj] = V::mfma(li[si][u], br[u][sj], ai[s][si][sj]);
                                     }
+                                }
                     }
                 }
             }
         }
         // ---- the block's panels -------------------------------------------------------
+        // this thread's panel rows: whole sets of 64 RPT rows per wavefront, so
+        // that wavefronts run out of rows one after the other and then only
+        // keep the barriers (with the winner found by lanes below: 1024 real
+        // matrices of 202 0.95 -> 0.81 ms, 64 FP32 of 1185 7.2 -> 6.5 ms)
+        auto row_of = [&](int i) { return (wv * RPT + i) * 64 + lane; };
+        const bool idle = row_of(0) - lane >= mr;
         int lg[RPT];         // position of this thread's rows, relative to the block
         unsigned open = 0;   // rows that are not pivotal yet
 #pragma unroll
         for (int i = 0; i < RPT; ++i) {
-            const int r = tid + i * NTH;
+            const int r = row_of(i);
             lg[i] = r;
             if (r < mr) {
                 open |= 1u << i;
@@ -532,7 +567,7 @@ __device__ __forceinline__ void lu_left(T *__restrict__ Ar, int m, int ld, int *
                 T xr[RPT][PW], xi[CX ? RPT : 1][PW];
 #pragma unroll
                 for (int i = 0; i < RPT; ++i) {
-                    const T *q = pan + min(tid + i * NTH, mr - 1) * LS * P;
+                    const T *q = pan + min(row_of(i), mr - 1) * LS * P;
 #pragma unroll
                     for (int k = 0; k < PW; ++k) {
                         xr[i][k] = q[k * P];
@@ -545,6 +580,11 @@ __device__ __forceinline__ void lu_left(T *__restrict__ Ar, int m, int ld, int *
                 auto columns = [&](auto width, int cb) {
                     constexpr int WD = decltype(width)::value;
                     const int ce = min(cb + 4, nb);
+                    if (idle) {
+                        if (lane < 2) wval[lane][wv] = T(-1);
+                        for (int c = cb; c < ce; ++c) __syncthreads();
+                        return;
+                    }
 #pragma unroll 1
                     for (int c = cb; c < ce; ++c) {
                         const int par = c & 1;
@@ -582,26 +622,24 @@ __device__ __forceinline__ void lu_left(T *__restrict__ Ar, int m, int ld, int *
                             if (cand && i == bi_) {
                                 publish(pub[par][wv], i);
                                 wval[par][wv] = wm;
-                                wkey[par][wv] = min(tid + i * NTH, mr - 1) | lg[i] << 16;
+                                wkey[par][wv] = min(row_of(i), mr - 1) | lg[i] << 16;
                             }
                         __syncthreads();
-                        T bv[NW];
-                        int bk[NW];
-#pragma unroll
-                        for (int w = 0; w < NW; ++w) {
-                            bv[w] = wval[par][w];
-                            bk[w] = wkey[par][w] | w << 12;
+                        // the winner: candidate w in lane w (mod NW)
+                        const T cv = wval[par][lane & (NW - 1)];
+                        const int ck = wkey[par][lane & (NW - 1)] | (lane & (NW - 1)) << 12;
+                        T top = cv;
+                        if constexpr (NW > 1) top = max_of(top, dpp<0xB1, 0xf>(top));    // quad_perm 1,0,3,2
+                        if constexpr (NW > 2) top = max_of(top, dpp<0x4E, 0xf>(top));    // quad_perm 2,3,0,1
+                        if constexpr (NW > 4) top = max_of(top, dpp<0x141, 0xf>(top));   // row_half_mirror
+                        unsigned long long win = __ballot(cv == top) & ((1ull << NW) - 1);
+                        if (STD && __popcll(win) > 1) {
+                            const int pos = cv == top ? ck >> 16 : 0x7fffffff;
+                            int low = pos;
+                            for (int off = NW / 2; off > 0; off >>= 1) low = min(low, __shfl_xor(low, off, 64));
+                            win = __ballot(pos == low) & ((1ull << NW) - 1);
                         }
-#pragma unroll
-                        for (int hh = NW / 2; hh > 0; hh /= 2)
-#pragma unroll
-                            for (int w = 0; w < hh; ++w) {
-                                const bool better =
-                                    bv[w + hh] > bv[w] || (STD && bv[w + hh] == bv[w] && bk[w + hh] >> 16 < bk[w] >> 16);
-                                bv[w] = better ? bv[w + hh] : bv[w];
-                                bk[w] = better ? bk[w + hh] : bk[w];
-                            }
-                        const int key = __builtin_amdgcn_readfirstlane(bk[0]);
+                        const int key = __builtin_amdgcn_readlane(ck, __builtin_ctzll(win | (1ull << 63)));
                         const int R = key & 0xfff, p = key >> 16;
                         const T *u = pub[par][(key >> 12) & 0xf];
                         T ur[WD], ui[WD];
@@ -616,14 +654,14 @@ __device__ __forceinline__ void lu_left(T *__restrict__ Ar, int m, int ld, int *
                             pl[c0 + c] = R;
                             rk[R] = c0 + c;
                             if constexpr (STD) ip[j0 + c0 + c] = j0 + p;
-                            if (info && bv[0] == T(0)) atomicAdd(info, 1);
+                            if (info && lane_value(top, 0) == T(0)) atomicAdd(info, 1);
                         }
                         T ir, ii;
                         reciprocal<T, CX>(ur[0], ui[0], ir, ii);
                         T lr[RPT], li[RPT];
 #pragma unroll
                         for (int i = 0; i < RPT; ++i) {
-                            const int r = tid + i * NTH;
+                            const int r = row_of(i);
                             const bool op = (open >> i) & 1u, me = op && r == R, upd = op && !me;
                             T tr, ti;
                             if constexpr (CX) {
@@ -647,7 +685,7 @@ __device__ __forceinline__ void lu_left(T *__restrict__ Ar, int m, int ld, int *
                         // wavefront past the end are skipped)
 #pragma unroll
                         for (int i = 0; i < RPT; ++i) {
-                            if (64 * wv + i * NTH >= mr) continue;
+                            if (row_of(i) - lane >= mr) continue;
 #pragma unroll
                             for (int k = 1; k < WD; ++k) {
                                 T vr = fma_(-lr[i], ur[k], xr[i][k]);
@@ -872,11 +910,11 @@ __device__ __forceinline__ void lu_left(T *__restrict__ Ar, int m, int ld, int *
         // ---- positions after the block's interchanges --------------------------------------
         int row[RPT];
 #pragma unroll
-        for (int i = 0; i < RPT; ++i) row[i] = cur[j0 + min(tid + i * NTH, mr - 1)];
+        for (int i = 0; i < RPT; ++i) row[i] = cur[j0 + min(row_of(i), mr - 1)];
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < RPT; ++i)
-            if (tid + i * NTH < mr) cur[j0 + lg[i]] = row[i];
+            if (row_of(i) < mr) cur[j0 + lg[i]] = row[i];
         __syncthreads();
     }
     if constexpr (!STD) {
