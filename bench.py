@@ -91,16 +91,17 @@ def vmult_flops(dim, n, r, k, nq):
 
 def vmult_flops_performed(n, r, k, nq):
     """Operations the 3D Jacobian volume kernel performs per application (FMA
-    = 2): z sweep (x by S and D, state and mixed field by S, time mixing,
-    pressure), y sweep (three x variants, state, mixed field, pressure), x
-    sweep per quadrature point, point physics, and the transposed x, y, z
-    sweeps."""
+    = 2): z sweep (x by S and D, state by S, pressure), y sweep (three x
+    variants, state, pressure), row stage (time mixing, x sweep and point
+    physics; for r <= 2 each of a row's three threads interpolates all values
+    of x and the state and the pressure), and the transposed x, y, z sweeps."""
     n1, rp1, nt = r + 2, r + 1, k + 1
     ncell = int(np.prod(n))
-    z = 3 * n1 ** 3 * nq * 4 + 3 * n1 ** 3 * nt + rp1 ** 3 * nq
-    y = 15 * nq ** 2 * n1 ** 2 + nq ** 2 * rp1 ** 2
-    xp = nq ** 3 * (18 * n1 + rp1)
-    bx = 12 * nq ** 3 * n1 + nq ** 3 * rp1
+    threads = 1 if r == 3 else 3
+    z = 3 * n1 ** 3 * nq * 3 + rp1 ** 3 * nq
+    y = 12 * nq ** 2 * n1 ** 2 + nq ** 2 * rp1 ** 2
+    xp = 3 * nt * nq ** 2 * n1 + nq ** 3 * (12 * n1 + threads * (6 * n1 + rp1))
+    bx = 12 * nq ** 3 * n1 + threads * nq ** 3 * rp1
     by = 9 * nq ** 2 * n1 ** 2 + nq ** 2 * rp1 ** 2
     bz = 6 * nq * n1 ** 3 + nq * rp1 ** 3
     qp = nq ** 3 * (2 * 27 + 5 * 9 + 2 * 27 + 4 * 3 + 4)
@@ -570,7 +571,7 @@ def main():
         "roofline": {"bound": "alu", "achieved": achieved / 1e12, "peak": PEAK_FP64_VALU / 1e12,
                      "unit": "TFLOP/s", "frac": achieved / PEAK_FP64_VALU, "traffic": traffic,
                      "traffic_source": traffic_note,
-                     "kernel": "jac_cell_kernel<2,5,192,f64> (3D Jacobian volume terms)",
+                     "kernel": "vol_kernel<2,5,3,f64,Jac> (3D Jacobian volume terms)",
                      "flops_per_launch": flops,
                      "flops_per_launch_performed": vmult_flops_performed(w["n"], w["r"], w["k"], nq),
                      "kernel_ms": cell64},
