@@ -1570,7 +1570,8 @@ __global__ void __launch_bounds__(256) patch_td_kernel(PatchTdArgs<TE, TP> A)
     const int cc[3] = {cell % A.n0, (cell / A.n0) % A.n1, DIM == 3 ? cell / (A.n0 * A.n1) : 0};
     const int nn[3] = {A.n0, A.n1, A.n2};
     const long long rw = A.rec_words;
-    const TE *own = A.elem + (long long)cell * rw + DIM * DIM * NL * NL + NL * NL;
+    const TE *own = A.elem + (long long)cell * rw;
+    const TE *ownB = own + DIM * DIM * NL * NL + NL * NL;
     // velocity index -> component, node and the node's per-axis positions,
     // packed (bits 0-3, 4-7, 8-11: positions; 12-19: node; 20-21: component)
     static_assert(N1 <= 16 && NL <= 256, "patch index packing");
@@ -1580,49 +1581,94 @@ __global__ void __launch_bounds__(256) patch_td_kernel(PatchTdArgs<TE, TP> A)
         dec[t] = (i % N1) | (((i / N1) % N1) << 4) | ((DIM == 3 ? i / (N1 * N1) : 0) << 8) | (i << 12) | (c << 20);
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < MS * MS; e += blockDim.x) {
-        const int row = e / MS, col = e - (e / MS) * MS;
-        double mv = 0, lv = 0;
-        if (row < NV && col < NV) {
-            const int dr = dec[row], dc = dec[col];
-            const int i = (dr >> 12) & 255, c = dr >> 20, j = (dc >> 12) & 255, e2 = dc >> 20;
-            const bool need_m = c == e2;
-            int li[3] = {dr & 15, (dr >> 4) & 15, (dr >> 8) & 15};
-            int lj[3] = {dc & 15, (dc >> 4) & 15, (dc >> 8) & 15};
-            // neighbour offsets per axis that hold both nodes
-            int opts[3][3], nopt[3];
-            for (int ax = 0; ax < 3; ++ax) {
-                nopt[ax] = 0;
-                opts[ax][nopt[ax]++] = 0;
-                if (ax >= DIM) continue;
-                if (li[ax] == 0 && lj[ax] == 0 && cc[ax] > 0) opts[ax][nopt[ax]++] = -1;
-                if (li[ax] == R + 1 && lj[ax] == R + 1 && cc[ax] < nn[ax] - 1) opts[ax][nopt[ax]++] = 1;
-            }
-            for (int o2 = 0; o2 < nopt[2]; ++o2)
-                for (int o1 = 0; o1 < nopt[1]; ++o1)
-                    for (int o0 = 0; o0 < nopt[0]; ++o0) {
-                        const int dd[3] = {opts[0][o0], opts[1][o1], opts[2][o2]};
-                        const long long nb = (cc[0] + dd[0]) +
-                                             (long long)A.n0 * ((cc[1] + dd[1]) + (long long)A.n1 * (cc[2] + dd[2]));
-                        int ip = 0, jp = 0, st = 1;
-                        for (int ax = 0; ax < DIM; ++ax) {
-                            ip += st * (li[ax] - dd[ax] * (R + 1));
-                            jp += st * (lj[ax] - dd[ax] * (R + 1));
-                            st *= N1;
-                        }
-                        const TE *rec = A.elem + nb * rw;
-                        if (need_m) mv += (double)rec[DIM * DIM * NL * NL + (long long)ip * NL + jp];
-                        lv += (double)rec[((long long)(c * DIM + e2) * NL + ip) * NL + jp];
-                    }
-        } else if (row < NV) {
-            lv = (double)own[(long long)row * NPM + (col - NV)];     // row = c * NL + i
-        } else if (col < NV) {
-            lv = (double)own[(long long)col * NPM + (row - NV)];
+    // from the entry of a node pair in this cell's record to its entry in the
+    // record of the neighbour behind the lower [0] / upper [1] face of an axis:
+    // neighbour cell, and node positions shifted by R + 1
+    long long hop[3][2];
+    {
+        long long cs = 1;
+        int st = 1;
+        for (int ax = 0; ax < DIM; ++ax) {
+            const long long sh = (long long)(R + 1) * st * (NL + 1);
+            hop[ax][0] = -cs * rw + sh;
+            hop[ax][1] = cs * rw - sh;
+            cs *= nn[ax];
+            st *= N1;
         }
-        for (int s = 0; s < A.nsys; ++s) {
-            TP *o = A.sys[s] + (long long)cell * (A.cplx[s] ? 2 : 1) * MAT + (long long)row * LDM + col;
-            o[0] = (TP)(A.lre[s] * mv + lv);
-            if (A.cplx[s]) o[MAT] = (TP)(A.lim[s] * mv);
+    }
+    // entries of four rounds at once: their loads from this cell's record are in
+    // flight together, and so are the up to seven from neighbours of each.  One
+    // entry at a time with its neighbours in a loop, latency bound it: 13824
+    // patches of 395 in FP32, 17.3 GB written: 14.6 -> 11.6 ms
+    constexpr int U = 4;
+    const int nth = blockDim.x;
+    for (int e0 = threadIdx.x; e0 < MS * MS; e0 += U * nth) {
+        const TE *pl[U], *pm[U];   // this cell's entries (nullptr: none)
+        int up[U];                 // per axis: 1 lower, 2 upper neighbour also holds both nodes
+        TE l0[U], m0[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int e = e0 + u * nth, row = e / MS, col = e - row * MS;
+            pl[u] = pm[u] = nullptr;
+            up[u] = 0;
+            if (row < NV && col < NV) {
+                const int dr = dec[row], dc = dec[col];
+                const int i = (dr >> 12) & 255, c = dr >> 20, j = (dc >> 12) & 255, e2 = dc >> 20;
+                pl[u] = own + ((long long)(c * DIM + e2) * NL + i) * NL + j;
+                if (c == e2) pm[u] = own + DIM * DIM * NL * NL + (long long)i * NL + j;
+#pragma unroll
+                for (int ax = 0; ax < DIM; ++ax) {
+                    const int li = (dr >> (4 * ax)) & 15, lj = (dc >> (4 * ax)) & 15;
+                    if (li == 0 && lj == 0 && cc[ax] > 0) up[u] |= 1 << (2 * ax);
+                    if (li == R + 1 && lj == R + 1 && cc[ax] < nn[ax] - 1) up[u] |= 2 << (2 * ax);
+                }
+            } else if (row < NV) {
+                pl[u] = ownB + (long long)row * NPM + (col - NV);     // row = c * NL + i
+            } else if (col < NV && row < MS) {
+                pl[u] = ownB + (long long)col * NPM + (row - NV);
+            }
+            l0[u] = pl[u] ? *pl[u] : TE(0);
+            m0[u] = pm[u] ? *pm[u] : TE(0);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int e = e0 + u * nth, row = e / MS, col = e - row * MS;
+            double mv = (double)m0[u], lv = (double)l0[u];
+            if (__any(up[u] != 0)) {
+                long long h[DIM];
+                int mask = 0;
+#pragma unroll
+                for (int ax = 0; ax < DIM; ++ax) {
+                    const int b = (up[u] >> (2 * ax)) & 3;
+                    h[ax] = b == 1 ? hop[ax][0] : hop[ax][1];
+                    if (b) mask |= 1 << ax;
+                }
+                TE ln[1 << DIM], mn[1 << DIM];
+#pragma unroll
+                for (int k = 1; k < (1 << DIM); ++k) {
+                    ln[k] = mn[k] = TE(0);
+                    if ((mask & k) == k) {
+                        long long o = 0;
+#pragma unroll
+                        for (int ax = 0; ax < DIM; ++ax)
+                            if ((k >> ax) & 1) o += h[ax];
+                        ln[k] = pl[u][o];
+                        if (pm[u]) mn[k] = pm[u][o];
+                    }
+                }
+                // summed in a fixed order (z outer, x inner; this cell first)
+#pragma unroll
+                for (int k = 1; k < (1 << DIM); ++k) {
+                    mv += (double)mn[k];
+                    lv += (double)ln[k];
+                }
+            }
+            if (e >= MS * MS) continue;
+            for (int s = 0; s < A.nsys; ++s) {
+                TP *o = A.sys[s] + (long long)cell * (A.cplx[s] ? 2 : 1) * MAT + (long long)row * LDM + col;
+                o[0] = (TP)(A.lre[s] * mv + lv);
+                if (A.cplx[s]) o[MAT] = (TP)(A.lim[s] * mv);
+            }
         }
     }
 }
