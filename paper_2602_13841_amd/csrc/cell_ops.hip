@@ -3,8 +3,9 @@
 // One workgroup handles one spatial cell and all k+1 time nodes of the slab
 // (the Kronecker evaluation of Sec. "Matrix-free operator evaluation": the
 // spatial operator once per temporal node, then the small dense time
-// mixing).  3D Jacobian and residual: vol_kernel (below).  2D, and the mass
-// operator, per cell and time node (cell_kernel):
+// mixing).  3D Jacobian and residual with two or three time nodes: vol_kernel
+// (below; vol_takes says for which).  Otherwise per cell and time node (3D
+// Jacobian: jac_cell_kernel; the rest: cell_kernel):
 //
 //   1. coalesced gather of the nodal values (velocity, pressure modes, state)
 //      into LDS,
@@ -324,43 +325,69 @@ __device__ __forceinline__ void pencil_fwd(const T *__restrict__ inA, const T *_
     }
 }
 
-// 2D: reference derivatives along y of NF fields at the Gauss points by
-// collocation (Dq, NQ x NQ): field f at U + f * NQ^2, derivative to
-// G + (f * 2 + 1) * NQ^2
-template <int NQ, int NF, int NTH, typename T, typename MP>
+// reference derivatives along y (and z) of NF fields at the Gauss points by
+// collocation (Dq, NQ x NQ): field f at U + f * NQ^DIM, derivative along axis
+// d (1 <= d < DIM) to G + (f * DIM + d) * NQ^DIM
+template <int DIM, int NQ, int NF, int NTH, typename T, typename MP>
 __device__ __forceinline__ void colloc_fwd(const T *__restrict__ U, T *__restrict__ G, MP Dq)
 {
-    constexpr int NQV = NQ * NQ;
-    for (int w = threadIdx.x; w < NF * NQ; w += NTH) {
-        const int f = w / NQ, p = w - f * NQ;
-        pencil_apply<NQ, NQ>(U + f * NQV + p, NQ, G + (f * 2 + 1) * NQV + p, NQ, Dq);
+    constexpr int NQV = DIM == 3 ? NQ * NQ * NQ : NQ * NQ;
+    constexpr int NP = DIM == 3 ? NQ * NQ : NQ;      // pencils per field and axis
+    const int tid = threadIdx.x;
+    for (int w = tid; w < NF * (DIM - 1) * NP; w += NTH) {
+        const int f = w / ((DIM - 1) * NP), rr = w - f * (DIM - 1) * NP, d = 1 + rr / NP, p = rr - (d - 1) * NP;
+        int base, st;
+        if (d == 1) {                 // pencil along y through (qz, qx), p = qz * NQ + qx
+            const int qz = DIM == 3 ? p / NQ : 0, qxx = DIM == 3 ? p - qz * NQ : p;
+            base = qz * NQ * NQ + qxx;
+            st = NQ;
+        } else {                      // pencil along z through (qy, qx), p = qy * NQ + qx
+            base = p;
+            st = NQ * NQ;
+        }
+        pencil_apply<NQ, NQ>(U + f * NQV + base, st, G + (f * DIM + d) * NQV + base, st, Dq);
     }
     __syncthreads();
 }
 
-// 2D: transposed collocation of the test-function gradients along y, in place:
-// Y_c += Dq^T F[c][1] (F at F0 + (c * 2 + 1) * NQ^2, Y_c at Y0 + c * NQ^2); the x
-// part is applied by pencil_bwd with the nodal derivative table
-template <int NQ, int NTH, typename T, typename MP>
+// transposed collocation of the test-function gradients along z and y, in
+// place: Y_c += Dq_d^T F[c][d] for d = DIM-1 .. 1 (F at F0 + (c * DIM + d) *
+// NQ^DIM, Y_c at Y0 + c * NQ^DIM); the x part is applied by pencil_bwd with
+// the nodal derivative table
+template <int DIM, int NQ, int NTH, typename T, typename MP>
 __device__ __forceinline__ void colloc_bwd(const T *__restrict__ F0, T *__restrict__ Y0, MP Dq)
 {
-    constexpr int NQV = NQ * NQ;
-    for (int w = threadIdx.x; w < 2 * NQ; w += NTH) {
-        const int c = w / NQ, p = w - c * NQ;
-        const T *f = F0 + (c * 2 + 1) * NQV + p;
-        T *y = Y0 + c * NQV + p;
-        T u[NQ];
+    constexpr int NQV = DIM == 3 ? NQ * NQ * NQ : NQ * NQ;
+    constexpr int NP = DIM == 3 ? NQ * NQ : NQ;
+    const int tid = threadIdx.x;
+#pragma unroll 1
+    for (int d = DIM - 1; d >= 1; --d) {
+        for (int w = tid; w < DIM * NP; w += NTH) {
+            const int c = w / NP, p = w - c * NP;
+            int base, st;
+            if (d == 1) {
+                const int qz = DIM == 3 ? p / NQ : 0, qxx = DIM == 3 ? p - qz * NQ : p;
+                base = qz * NQ * NQ + qxx;
+                st = NQ;
+            } else {
+                base = p;
+                st = NQ * NQ;
+            }
+            const T *f = F0 + (c * DIM + d) * NQV + base;
+            T *y = Y0 + c * NQV + base;
+            T u[NQ];
 #pragma unroll
-        for (int m = 0; m < NQ; ++m) u[m] = f[m * NQ];
+            for (int m = 0; m < NQ; ++m) u[m] = f[m * st];
 #pragma unroll
-        for (int o = 0; o < NQ; ++o) {
-            T s = y[o * NQ];
+            for (int o = 0; o < NQ; ++o) {
+                T s = y[o * st];
 #pragma unroll
-            for (int m = 0; m < NQ; ++m) s += Dq[m * NQ + o] * u[m];
-            y[o * NQ] = s;
+                for (int m = 0; m < NQ; ++m) s += Dq[m * NQ + o] * u[m];
+                y[o * st] = s;
+            }
         }
+        __syncthreads();
     }
-    __syncthreads();
 }
 
 // Gauss points -> nodes (transposed interpolation) of group A (NFA fields at
@@ -689,7 +716,7 @@ __global__ void __launch_bounds__(NTH) cell_kernel(CellArgs<T> A)
         constexpr int NG = MODE == Mode::Mass ? 0 : DIM;
         T *G = Q + LY::DQ0 * NQV;
         pencil_fwd<DIM, NQ, NFA, N1, 1, RP1, NG, NTH, T>(cur, xpf + a * NPF, Q, Q + NFA * NQV, G, t1, t2, S, D, Lp);
-        if constexpr (MODE != Mode::Mass) colloc_fwd<NQ, DIM, NTH, T>(Q, G, Dq);
+        if constexpr (MODE != Mode::Mass) colloc_fwd<DIM, NQ, DIM, NTH, T>(Q, G, Dq);
 
         // ---- quadrature-point physics, in place at each point ----------------------
         const T wa = A.w[a];
@@ -768,9 +795,9 @@ __global__ void __launch_bounds__(NTH) cell_kernel(CellArgs<T> A)
         }
         __syncthreads();
 
-        // ---- transposed collocation along y (into the value fields), then Gauss
+        // ---- transposed collocation along y, z (into the value fields), then Gauss
         //      points -> nodes with the x part of the test gradient
-        if constexpr (MODE != Mode::Mass) colloc_bwd<NQ, NTH, T>(G, Q, Dq);
+        if constexpr (MODE != Mode::Mass) colloc_bwd<DIM, NQ, NTH, T>(G, Q, Dq);
         pencil_bwd<DIM, NQ, DIM, N1, 1, RP1, MODE != Mode::Mass, NTH, T>(Q, G, DIM * NQV, Q + NFA * NQV, ys, ypf, t1,
                                                                         t2, S, D, Lp);
 
@@ -787,6 +814,546 @@ __global__ void __launch_bounds__(NTH) cell_kernel(CellArgs<T> A)
         }
         __syncthreads();
     }
+}
+
+// ---------------------------------------------------------------------------
+// 3D Jacobian volume kernel (eq. JacobianLocal, convective part eq. Defcp), where
+// vol_kernel below is not the faster one (vol_takes).
+//
+// Same cell / time-node decomposition as cell_kernel, different contraction
+// order: the reference gradient of the direction field is obtained by
+// contracting with the nodal derivative table D along the axis in question
+// (z and y during the first two sweeps, x in the last), not by collocation at
+// the Gauss points.  The last forward contraction then needs only rows that
+// the earlier sweeps left in LDS, so one thread per quadrature point finishes
+// the interpolation, evaluates the point physics and writes its 13
+// coefficients; three sweeps take them back to the nodes and the last one
+// writes E and the pressure rows from registers.  Per time node that is six
+// barrier-separated stages (z, y, x + physics, x^T, y^T, z^T).  The
+// time-mixed field sum_b K_ab x^b is formed while loading the z columns.
+// Every item type of a stage starts on a wavefront boundary so that no
+// wavefront executes two item types.
+// ---------------------------------------------------------------------------
+constexpr int al64(int v) { return (v + 63) & ~63; }
+constexpr int al4(int v) { return (v + 3) & ~3; }
+
+template <int R, int NQ> struct JacLds {
+    static constexpr int N1 = R + 2, RP1 = R + 1, NL = N1 * N1 * N1, NQV = NQ * NQ * NQ;
+    static constexpr int QN2 = NQ * N1 * N1;     // one field after the z sweep [qz][j][i]
+    static constexpr int QQN = NQ * NQ * N1;     // one field after the y sweep [qz][qy][i]
+    // 1D tables (rows per quadrature point for the thread-per-point stage)
+    static constexpr int TS = 0, TD = TS + NQ * N1, TL = TD + NQ * N1, QW = TL + NQ * RP1, QX = QW + NQ;
+    static constexpr int GEO = al4(QX + NQ);     // [8][3] vertices (mapped cells)
+    // region P: z-sweep results (xhat along z by S and by D, state, mixed field,
+    // pressure), then the point record [13][NQV], then the y^T results; the
+    // nodal state of the next time node sits behind the z-sweep results
+    static constexpr int ZXS = 0, ZXD = 3 * QN2, ZS = 6 * QN2, ZM = 9 * QN2, ZP = 12 * QN2;
+    static constexpr int NSO = al4(ZP + NQ * RP1 * RP1);
+    static constexpr int WA = 0, WC = 3 * QN2, WP = 6 * QN2;
+    static constexpr int RPW = al4(NSO + 3 * NL > 13 * NQV ? NSO + 3 * NL : 13 * NQV);
+    // region Y: y-sweep results (xhat: S_y S_z, D_y S_z, S_y D_z; state; mixed;
+    // pressure), then the x^T results (value + x-gradient, y-gradient,
+    // z-gradient coefficients; pressure)
+    static constexpr int YSS = 0, YDS = 3 * QQN, YSD = 6 * QQN, YS = 9 * QQN, YM = 12 * QQN, YP = 15 * QQN;
+    static constexpr int BA = 0, BB = 3 * QQN, BC = 6 * QQN, BP = 9 * QQN;
+    static constexpr int RYW = al4(15 * QQN + NQ * NQ * RP1);
+    static constexpr int RP = GEO + 24, RY = RP + RPW;
+    // then [nt][NPF] pressure modes and [nt][3][NL] nodal x of all time nodes
+    static constexpr int XP0 = RY + RYW;
+    static_assert(WP + NQ * RP1 * RP1 <= NSO, "y^T results stay clear of the nodal state");
+};
+
+template <int R, int NQ, typename T>
+__host__ __device__ constexpr int jac_lds_words(int nt)
+{
+    using LY = JacLds<R, NQ>;
+    return LY::XP0 + nt * ((R + 1) * (R + 1) * (R + 1) + 3 * LY::NL);
+}
+
+// position of the pressure multi-index (i0, i1, i2) in the admissible
+// ordering of pmode_full (first index fastest), or -1 if its degree exceeds R
+template <int R>
+__device__ __forceinline__ int pmode_compact(int i0, int i1, int i2)
+{
+    if (i0 + i1 + i2 > R) return -1;
+    int cnt = 0;
+    for (int a2 = 0; a2 < i2; ++a2) cnt += (R - a2 + 1) * (R - a2 + 2) / 2;
+    for (int a1 = 0; a1 < i1; ++a1) cnt += R - i2 - a1 + 1;
+    return cnt + i0;
+}
+
+// FUSED: the boundary-face items run in the same launch and add onto this
+// cell's E entries and pressure rows; for cells on the domain boundary the
+// volume result is then added atomically too (onto entries zeroed before the
+// launch)
+template <int R, int NQ, int NTH, typename T, bool MAPPED, bool FUSED>
+__device__ __forceinline__ void jac_cell_body(const CellArgs<T> &A, const int cell, const int vec, T *sm,
+                                              const int tid)
+{
+    using LY = JacLds<R, NQ>;
+    constexpr int N1 = R + 2, RP1 = R + 1, NL = LY::NL, NPF = RP1 * RP1 * RP1, NPM = Sizes<3, R>::NPM;
+    constexpr int NQV = LY::NQV, QN2 = LY::QN2, QQN = LY::QQN, N2 = N1 * N1, RP2 = RP1 * RP1;
+
+    T *tS = sm + LY::TS, *tD = sm + LY::TD, *tL = sm + LY::TL, *qw = sm + LY::QW, *qxs = sm + LY::QX;
+    T *geo = sm + LY::GEO;
+    T *P = sm + LY::RP, *Y = sm + LY::RY;
+    T *NS = P + LY::NSO;
+    const int nt = A.nt;
+    T *XP = sm + LY::XP0;                 // [nt][NPF]
+    T *XS = XP + nt * NPF;                // [nt][3][NL]
+
+    const T *__restrict__ x = A.x + vec * A.xstride;
+    T *__restrict__ y = A.y + vec * A.ystride;
+    T *__restrict__ E = A.E + (long long)vec * A.ncell * nt * 3 * NL;
+
+    TableLayout lay;
+    lay.init(R, NQ);
+    // matrices indexed by compile-time row/column in the sweeps: scalar path
+    using CP = const __attribute__((address_space(4))) T *;
+    const CP S = (CP)(A.tab + lay.S), D = (CP)(A.tab + lay.D), L = (CP)(A.tab + lay.L);
+    // rows selected by the point's own x index: from LDS
+    for (int i = tid; i < NQ * N1; i += NTH) {
+        tS[i] = A.tab[lay.S + i];
+        tD[i] = A.tab[lay.D + i];
+    }
+    for (int i = tid; i < NQ * RP1; i += NTH) tL[i] = A.tab[lay.L + i];
+    for (int i = tid; i < NQ; i += NTH) {
+        qw[i] = A.tab[lay.qw + i];
+        qxs[i] = A.tab[lay.qx + i];
+    }
+
+    const int c0 = cell % A.n0;
+    const int c1 = (cell / A.n0) % A.n1;
+    const int c2 = cell / (A.n0 * A.n1);
+    const bool atomic_out =
+        FUSED && (c0 == 0 || c0 == A.n0 - 1 || c1 == 0 || c1 == A.n1 - 1 || c2 == 0 || c2 == A.n2 - 1);
+    const long long N0 = (long long)(R + 1) * A.n0 + 1;
+    const long long N1g = (long long)(R + 1) * A.n1 + 1;
+    auto gnode = [&](int l) -> long long {
+        int i0 = l % N1, i1 = (l / N1) % N1, i2 = l / N2;
+        long long g0 = (long long)(R + 1) * c0 + i0, g1 = (long long)(R + 1) * c1 + i1;
+        long long g2 = (long long)(R + 1) * c2 + i2;
+        return g0 + N0 * (g1 + N1g * g2);
+    };
+
+    // state of a time node into registers (element e = tid + j * NTH)
+    constexpr int PF = (3 * NL + NTH - 1) / NTH;
+    T spre[PF];
+    const T *st = A.state + vec * A.sstride;
+    auto load_state = [&](int a) {
+#pragma unroll
+        for (int j = 0; j < PF; ++j) {
+            const int e = tid + j * NTH;
+            if (e < 3 * NL) {
+                const int l = e % NL, c = e / NL;
+                spre[j] = st[a * A.Nv1 + c * A.Nn + gnode(l)];
+            }
+        }
+    };
+    auto store_state = [&]() {
+#pragma unroll
+        for (int j = 0; j < PF; ++j) {
+            const int e = tid + j * NTH;
+            if (e < 3 * NL) NS[e] = spre[j];
+        }
+    };
+    load_state(0);
+    for (int e = tid; e < nt * 3 * NL; e += NTH) {
+        const int l = e % NL, c = (e / NL) % 3, a = e / (3 * NL);
+        XS[e] = x[a * A.Nv1 + c * A.Nn + gnode(l)];
+    }
+    const long long pbase = (long long)nt * A.Nv1;
+    constexpr int PP = (MAX_NT * NPM + NTH - 1) / NTH;
+    T ppre[PP];
+#pragma unroll
+    for (int j = 0; j < PP; ++j) {
+        const int e = tid + j * NTH;
+        if (e < nt * NPM) ppre[j] = x[pbase + (e / NPM) * A.Np1 + (long long)cell * NPM + e % NPM];
+    }
+    for (int e = tid; e < nt * NPF; e += NTH) XP[e] = 0;
+    const T hcar[3] = {T(1) / A.n0, T(1) / A.n1, T(1) / A.n2};
+    const T hinv[3] = {T(1) / hcar[0], T(1) / hcar[1], T(1) / hcar[2]};
+    const T det_c = hcar[0] * hcar[1] * hcar[2];
+    if (MAPPED && tid < 8) {
+        const int v = tid, o0 = v & 1, o1 = (v >> 1) & 1, o2 = (v >> 2) & 1;
+        const long long vi = (c0 + o0) + (long long)(A.n0 + 1) * ((c1 + o1) + (long long)(A.n1 + 1) * (c2 + o2));
+        for (int k = 0; k < 3; ++k) geo[v * 3 + k] = T(A.vert[vi * 3 + k]);
+    }
+    store_state();
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < PP; ++j) {
+        const int e = tid + j * NTH;
+        if (e < nt * NPM) XP[(e / NPM) * NPF + pmode_full<3, R>(e % NPM)] = ppre[j];
+    }
+    if (nt > 1) load_state(1);
+    __syncthreads();
+
+    for (int a = 0; a < nt; ++a) {
+        // ---- z sweep: xhat by S and D, state and mixed field by S, pressure by L
+        {
+            constexpr int NX = 3 * N2, O1 = al64(NX), O2 = O1 + al64(3 * N2), TOT = O2 + RP2;
+            for (int w = tid; w < TOT; w += NTH) {
+                if (w < NX) {
+                    const int c = w / N2, ji = w - c * N2;
+                    const T *src = XS + (a * 3 + c) * NL + ji;
+                    T u[N1];
+#pragma unroll
+                    for (int k = 0; k < N1; ++k) u[k] = src[k * N2];
+                    T *oS = P + LY::ZXS + c * QN2 + ji, *oD = P + LY::ZXD + c * QN2 + ji;
+#pragma unroll
+                    for (int qz = 0; qz < NQ; ++qz) {
+                        T s = 0, d = 0;
+#pragma unroll
+                        for (int k = 0; k < N1; ++k) {
+                            s += S[qz * N1 + k] * u[k];
+                            d += D[qz * N1 + k] * u[k];
+                        }
+                        oS[qz * N2] = s;
+                        oD[qz * N2] = d;
+                    }
+                } else if (w >= O1 && w < O1 + 3 * N2) {
+                    const int ww = w - O1, c = ww / N2, ji = ww - c * N2;
+                    T u[N1], m[N1];
+#pragma unroll
+                    for (int k = 0; k < N1; ++k) {
+                        u[k] = NS[c * NL + k * N2 + ji];
+                        m[k] = 0;
+                    }
+                    for (int b = 0; b < nt; ++b) {
+                        const T kab = A.K[a * nt + b];
+                        const T *src = XS + (b * 3 + c) * NL + ji;
+#pragma unroll
+                        for (int k = 0; k < N1; ++k) m[k] += kab * src[k * N2];
+                    }
+                    T *os = P + LY::ZS + c * QN2 + ji, *om = P + LY::ZM + c * QN2 + ji;
+#pragma unroll
+                    for (int qz = 0; qz < NQ; ++qz) {
+                        T s = 0, mm = 0;
+#pragma unroll
+                        for (int k = 0; k < N1; ++k) {
+                            s += S[qz * N1 + k] * u[k];
+                            mm += S[qz * N1 + k] * m[k];
+                        }
+                        os[qz * N2] = s;
+                        om[qz * N2] = mm;
+                    }
+                } else if (w >= O2) {
+                    const int ji = w - O2;
+                    const T *src = XP + a * NPF + ji;
+                    T u[RP1];
+#pragma unroll
+                    for (int k = 0; k < RP1; ++k) u[k] = src[k * RP2];
+                    T *op = P + LY::ZP + ji;
+#pragma unroll
+                    for (int qz = 0; qz < NQ; ++qz) {
+                        T s = 0;
+#pragma unroll
+                        for (int k = 0; k < RP1; ++k) s += L[qz * RP1 + k] * u[k];
+                        op[qz * RP2] = s;
+                    }
+                }
+            }
+            __syncthreads();
+        }
+        // ---- y sweep: xhat -> S_y S_z, D_y S_z, S_y D_z; state, mixed -> S_y; pressure -> L
+        {
+            constexpr int NX = 3 * NQ * N1, O1 = al64(NX), O2 = O1 + al64(3 * NQ * N1), TOT = O2 + NQ * RP1;
+            for (int w = tid; w < TOT; w += NTH) {
+                if (w < NX) {
+                    const int c = w / (NQ * N1), rr = w - c * NQ * N1, qz = rr / N1, i = rr - qz * N1;
+                    const T *sS = P + LY::ZXS + c * QN2 + qz * N2 + i, *sD = P + LY::ZXD + c * QN2 + qz * N2 + i;
+                    T u[N1], v[N1];
+#pragma unroll
+                    for (int j = 0; j < N1; ++j) {
+                        u[j] = sS[j * N1];
+                        v[j] = sD[j * N1];
+                    }
+                    const int ob = c * QQN + qz * NQ * N1 + i;
+#pragma unroll
+                    for (int qy = 0; qy < NQ; ++qy) {
+                        T ss = 0, ds = 0, sd = 0;
+#pragma unroll
+                        for (int j = 0; j < N1; ++j) {
+                            ss += S[qy * N1 + j] * u[j];
+                            ds += D[qy * N1 + j] * u[j];
+                            sd += S[qy * N1 + j] * v[j];
+                        }
+                        Y[LY::YSS + ob + qy * N1] = ss;
+                        Y[LY::YDS + ob + qy * N1] = ds;
+                        Y[LY::YSD + ob + qy * N1] = sd;
+                    }
+                } else if (w >= O1 && w < O1 + 3 * NQ * N1) {
+                    const int ww = w - O1, c = ww / (NQ * N1), rr = ww - c * NQ * N1, qz = rr / N1, i = rr - qz * N1;
+                    const T *sS = P + LY::ZS + c * QN2 + qz * N2 + i, *sM = P + LY::ZM + c * QN2 + qz * N2 + i;
+                    T u[N1], m[N1];
+#pragma unroll
+                    for (int j = 0; j < N1; ++j) {
+                        u[j] = sS[j * N1];
+                        m[j] = sM[j * N1];
+                    }
+                    const int ob = c * QQN + qz * NQ * N1 + i;
+#pragma unroll
+                    for (int qy = 0; qy < NQ; ++qy) {
+                        T s = 0, mm = 0;
+#pragma unroll
+                        for (int j = 0; j < N1; ++j) {
+                            s += S[qy * N1 + j] * u[j];
+                            mm += S[qy * N1 + j] * m[j];
+                        }
+                        Y[LY::YS + ob + qy * N1] = s;
+                        Y[LY::YM + ob + qy * N1] = mm;
+                    }
+                } else if (w >= O2) {
+                    const int ww = w - O2, qz = ww / RP1, ip = ww - qz * RP1;
+                    const T *src = P + LY::ZP + qz * RP2 + ip;
+                    T u[RP1];
+#pragma unroll
+                    for (int j = 0; j < RP1; ++j) u[j] = src[j * RP1];
+                    T *op = Y + LY::YP + qz * NQ * RP1 + ip;
+#pragma unroll
+                    for (int qy = 0; qy < NQ; ++qy) {
+                        T s = 0;
+#pragma unroll
+                        for (int j = 0; j < RP1; ++j) s += L[qy * RP1 + j] * u[j];
+                        op[qy * RP1] = s;
+                    }
+                }
+            }
+            __syncthreads();
+        }
+        // ---- x sweep and point physics: one thread per quadrature point ---------------
+        {
+            const T wa = A.w[a];
+            for (int q = tid; q < NQV; q += NTH) {
+                const int qx = q % NQ, qy = (q / NQ) % NQ, qz = q / (NQ * NQ);
+                const int row = qz * NQ + qy;
+                T sx[N1], dx[N1], lx[RP1];
+#pragma unroll
+                for (int i = 0; i < N1; ++i) {
+                    sx[i] = tS[qx * N1 + i];
+                    dx[i] = tD[qx * N1 + i];
+                }
+#pragma unroll
+                for (int i = 0; i < RP1; ++i) lx[i] = tL[qx * RP1 + i];
+                T xh[3], gref[3][3], v[3], xm[3];
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    const int rb = c * QQN + row * N1;
+                    T a0 = 0, a1 = 0, a2 = 0, a3 = 0, a4 = 0, a5 = 0;
+#pragma unroll
+                    for (int i = 0; i < N1; ++i) {
+                        const T u = Y[LY::YSS + rb + i];
+                        a0 += sx[i] * u;
+                        a1 += dx[i] * u;
+                        a2 += sx[i] * Y[LY::YDS + rb + i];
+                        a3 += sx[i] * Y[LY::YSD + rb + i];
+                        a4 += sx[i] * Y[LY::YS + rb + i];
+                        a5 += sx[i] * Y[LY::YM + rb + i];
+                    }
+                    xh[c] = a0;
+                    gref[c][0] = a1;
+                    gref[c][1] = a2;
+                    gref[c][2] = a3;
+                    v[c] = a4;
+                    xm[c] = a5;
+                }
+                T ph = 0;
+#pragma unroll
+                for (int i = 0; i < RP1; ++i) ph += lx[i] * Y[LY::YP + row * RP1 + i];
+                T det, Jit[3][3];
+                if constexpr (MAPPED) {
+                    const T xi[3] = {qxs[qx], qxs[qy], qxs[qz]};
+                    det = geometry<3>(true, geo, xi, hcar, Jit);
+                } else {
+                    det = det_c;
+                }
+                const T jxw = det * qw[qx] * qw[qy] * qw[qz];
+                const T sc = wa * jxw;
+                T divx = 0;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    T Fc[3];
+#pragma unroll
+                    for (int d = 0; d < 3; ++d) {
+                        T g = 0;
+                        if constexpr (MAPPED) {
+#pragma unroll
+                            for (int jd = 0; jd < 3; ++jd) g += Jit[d][jd] * gref[c][jd];
+                        } else {
+                            g = hinv[d] * gref[c][d];
+                        }
+                        if (d == c) divx += g;
+                        // nu grad x - x (x) v - v (x) x - p I
+                        Fc[d] = A.nu * g - xh[c] * v[d] - v[c] * xh[d];
+                        if (d == c) Fc[d] -= ph;
+                    }
+#pragma unroll
+                    for (int jd = 0; jd < 3; ++jd) {
+                        T s = 0;
+                        if constexpr (MAPPED) {
+#pragma unroll
+                            for (int d = 0; d < 3; ++d) s += Fc[d] * Jit[d][jd];
+                        } else {
+                            s = Fc[jd] * hinv[jd];
+                        }
+                        P[(3 + c * 3 + jd) * NQV + q] = s * sc;
+                    }
+                    P[c * NQV + q] = jxw * xm[c];
+                }
+                P[12 * NQV + q] = -sc * divx;
+            }
+            __syncthreads();
+        }
+        // ---- x^T: per (component, qz, qy) pencil, value + x-gradient (S, D), y- and
+        //      z-gradient coefficients (S); pressure by L
+        {
+            constexpr int NI = 3 * NQ * NQ, O1 = al64(NI), TOT = O1 + NQ * NQ;
+            for (int w = tid; w < TOT; w += NTH) {
+                if (w < NI) {
+                    const int c = w / (NQ * NQ), row = w - c * NQ * NQ;
+                    const T *pv = P + c * NQV + row * NQ, *pg = P + (3 + c * 3) * NQV + row * NQ;
+                    T u[NQ], g0[NQ], g1[NQ], g2[NQ];
+#pragma unroll
+                    for (int o = 0; o < NQ; ++o) {
+                        u[o] = pv[o];
+                        g0[o] = pg[o];
+                        g1[o] = pg[NQV + o];
+                        g2[o] = pg[2 * NQV + o];
+                    }
+                    const int ob = c * QQN + row * N1;
+#pragma unroll
+                    for (int i = 0; i < N1; ++i) {
+                        T sa = 0, sb = 0, scc = 0;
+#pragma unroll
+                        for (int o = 0; o < NQ; ++o) {
+                            sa += S[o * N1 + i] * u[o];
+                            sa += D[o * N1 + i] * g0[o];
+                            sb += S[o * N1 + i] * g1[o];
+                            scc += S[o * N1 + i] * g2[o];
+                        }
+                        Y[LY::BA + ob + i] = sa;
+                        Y[LY::BB + ob + i] = sb;
+                        Y[LY::BC + ob + i] = scc;
+                    }
+                } else if (w >= O1) {
+                    const int row = w - O1;
+                    const T *pp = P + 12 * NQV + row * NQ;
+                    T u[NQ];
+#pragma unroll
+                    for (int o = 0; o < NQ; ++o) u[o] = pp[o];
+#pragma unroll
+                    for (int i = 0; i < RP1; ++i) {
+                        T s = 0;
+#pragma unroll
+                        for (int o = 0; o < NQ; ++o) s += L[o * RP1 + i] * u[o];
+                        Y[LY::BP + row * RP1 + i] = s;
+                    }
+                }
+            }
+            __syncthreads();
+        }
+        // ---- y^T: per (component, qz, i) pencil; pressure by L
+        {
+            constexpr int NI = 3 * NQ * N1, O1 = al64(NI), TOT = O1 + NQ * RP1;
+            for (int w = tid; w < TOT; w += NTH) {
+                if (w < NI) {
+                    const int c = w / (NQ * N1), rr = w - c * NQ * N1, qz = rr / N1, i = rr - qz * N1;
+                    const int sb = c * QQN + qz * NQ * N1 + i;
+                    T ua[NQ], ub[NQ], uc[NQ];
+#pragma unroll
+                    for (int o = 0; o < NQ; ++o) {
+                        ua[o] = Y[LY::BA + sb + o * N1];
+                        ub[o] = Y[LY::BB + sb + o * N1];
+                        uc[o] = Y[LY::BC + sb + o * N1];
+                    }
+                    const int ob = c * QN2 + qz * N2 + i;
+#pragma unroll
+                    for (int j = 0; j < N1; ++j) {
+                        T sa = 0, scc = 0;
+#pragma unroll
+                        for (int o = 0; o < NQ; ++o) {
+                            sa += S[o * N1 + j] * ua[o];
+                            sa += D[o * N1 + j] * ub[o];
+                            scc += S[o * N1 + j] * uc[o];
+                        }
+                        P[LY::WA + ob + j * N1] = sa;
+                        P[LY::WC + ob + j * N1] = scc;
+                    }
+                } else if (w >= O1) {
+                    const int ww = w - O1, qz = ww / RP1, ip = ww - qz * RP1;
+                    T u[NQ];
+#pragma unroll
+                    for (int o = 0; o < NQ; ++o) u[o] = Y[LY::BP + qz * NQ * RP1 + o * RP1 + ip];
+#pragma unroll
+                    for (int j = 0; j < RP1; ++j) {
+                        T s = 0;
+#pragma unroll
+                        for (int o = 0; o < NQ; ++o) s += L[o * RP1 + j] * u[o];
+                        P[LY::WP + qz * RP2 + j * RP1 + ip] = s;
+                    }
+                }
+            }
+            __syncthreads();
+        }
+        // ---- z^T: per (component, j, i) column, straight to E; pressure rows; the
+        //      next time node's state into LDS (clear of the y^T results)
+        {
+            constexpr int NI = 3 * N2, O1 = al64(NI), TOT = O1 + RP2;
+            T *Ec = E + ((long long)cell * nt + a) * 3 * NL;
+            for (int w = tid; w < TOT; w += NTH) {
+                if (w < NI) {
+                    const int c = w / N2, ji = w - c * N2;
+                    T ua[NQ], uc[NQ];
+#pragma unroll
+                    for (int o = 0; o < NQ; ++o) {
+                        ua[o] = P[LY::WA + c * QN2 + o * N2 + ji];
+                        uc[o] = P[LY::WC + c * QN2 + o * N2 + ji];
+                    }
+#pragma unroll
+                    for (int k = 0; k < N1; ++k) {
+                        T s = 0;
+#pragma unroll
+                        for (int o = 0; o < NQ; ++o) {
+                            s += S[o * N1 + k] * ua[o];
+                            s += D[o * N1 + k] * uc[o];
+                        }
+                        if (atomic_out) unsafeAtomicAdd(Ec + c * NL + k * N2 + ji, s);
+                        else Ec[c * NL + k * N2 + ji] = s;
+                    }
+                } else if (w >= O1) {
+                    const int ji = w - O1, jp = ji / RP1, ip = ji - jp * RP1;
+                    T u[NQ];
+#pragma unroll
+                    for (int o = 0; o < NQ; ++o) u[o] = P[LY::WP + o * RP2 + ji];
+#pragma unroll
+                    for (int kp = 0; kp < RP1; ++kp) {
+                        const int e = pmode_compact<R>(ip, jp, kp);
+                        if (e >= 0) {
+                            T s = 0;
+#pragma unroll
+                            for (int o = 0; o < NQ; ++o) s += L[o * RP1 + kp] * u[o];
+                            if (atomic_out) unsafeAtomicAdd(y + pbase + a * A.Np1 + (long long)cell * NPM + e, s);
+                            else y[pbase + a * A.Np1 + (long long)cell * NPM + e] = s;
+                        }
+                    }
+                }
+            }
+            if (a + 1 < nt) {
+                store_state();
+                if (a + 2 < nt) load_state(a + 2);
+            }
+            __syncthreads();
+        }
+    }
+}
+
+template <int R, int NQ, int NTH, typename T, bool MAPPED>
+__global__ void __launch_bounds__(NTH) jac_cell_kernel(CellArgs<T> A)
+{
+    extern __shared__ unsigned char smem_raw[];
+    jac_cell_body<R, NQ, NTH, T, MAPPED, false>(A, xcd_cell(blockIdx.x, gridDim.x), blockIdx.y,
+                                                reinterpret_cast<T *>(smem_raw), threadIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -822,9 +1389,6 @@ __global__ void __launch_bounds__(NTH) cell_kernel(CellArgs<T> A)
 // device is no longer balanced between the workgroups: 82 us either way).
 // Item types start on wavefront boundaries: no wavefront executes two types.
 // ---------------------------------------------------------------------------
-constexpr int al64(int v) { return (v + 63) & ~63; }
-constexpr int al4(int v) { return (v + 3) & ~3; }
-
 // smallest stride >= n of rows [i][.. qz][qy] for which the N1 x NQ addresses
 // i * stride + qz * NQ of a y pencil's lanes fall on the fewest of 32 banks twice
 constexpr int bank_stride(int n, int n1, int nq)
@@ -897,27 +1461,7 @@ template <int R, int NQ, Mode MODE> struct VolLds {
     // items of the z stage
     __host__ __device__ static constexpr int zitems(int nt) { return al64(3 * nt * N2) + nt * RP2; }
     __host__ __device__ static constexpr int zslots(int nt) { return (zitems(nt) + threads(nt) - 1) / threads(nt); }
-    // NT = 0: any number of time nodes
-    __host__ __device__ static constexpr int zslots_of(int NT)
-    {
-        int m = NT ? zslots(NT) : 1;
-        for (int n = 1; n <= MAX_NT && !NT; ++n) m = zslots(n) > m ? zslots(n) : m;
-        return m;
-    }
-    __host__ __device__ static constexpr int max_threads(int NT) { return threads(NT ? NT : MAX_NT); }
 };
-
-// position of the pressure multi-index (i0, i1, i2) in the admissible
-// ordering of pmode_full (first index fastest), or -1 if its degree exceeds R
-template <int R>
-__device__ __forceinline__ int pmode_compact(int i0, int i1, int i2)
-{
-    if (i0 + i1 + i2 > R) return -1;
-    int cnt = 0;
-    for (int a2 = 0; a2 < i2; ++a2) cnt += (R - a2 + 1) * (R - a2 + 2) / 2;
-    for (int a1 = 0; a1 < i1; ++a1) cnt += R - i2 - a1 + 1;
-    return cnt + i0;
-}
 
 // geometry along a row of Gauss points and the flux of one component at a point
 template <typename T, bool MAPPED> struct RowGeometry {
@@ -1011,7 +1555,7 @@ template <typename T> __device__ __forceinline__ T pick(int c, T v0, T v1, T v2)
 // FUSED: the boundary-face items run in the same launch and add onto this
 // cell's E entries and pressure rows; for cells on the domain boundary the
 // volume result is then added atomically too (onto entries zeroed before the
-// launch).  NT: number of time nodes, 0 any; VolLds::threads(nt) threads
+// launch).  NT time nodes, VolLds::threads(NT) threads
 template <int R, int NQ, int NT, typename T, Mode MODE, bool MAPPED, bool FUSED>
 __device__ __forceinline__ void vol_body(const CellArgs<T> &A, const int cell, const int vec, T *sm, const int tid)
 {
@@ -1020,7 +1564,7 @@ __device__ __forceinline__ void vol_body(const CellArgs<T> &A, const int cell, c
     constexpr int N1 = R + 2, RP1 = R + 1, NL = N1 * N1 * N1, NPM = Sizes<3, R>::NPM;
     constexpr int NR = LY::NR, QN2 = LY::QN2, N2 = LY::N2, RP2 = LY::RP2, QN = NQ * N1;
 
-    const int nt = NT ? NT : A.nt, nth = LY::threads(nt);
+    constexpr int nt = NT, nth = LY::threads(nt);
     T *Z = sm + LY::RZ, *Y = sm + LY::ry(nt);
     const int PX = LY::px(nt), PS = LY::ps(nt), PP = LY::pp(nt);
     T *tK = sm + LY::TK, *tw = sm + LY::TW, *tphi = sm + LY::TPHI, *qw = sm + LY::QW, *qxs = sm + LY::QX;
@@ -1038,7 +1582,7 @@ __device__ __forceinline__ void vol_body(const CellArgs<T> &A, const int cell, c
     const int NX = 3 * nt * N2, O1 = al64(NX), TOT = O1 + nt * RP2;
 
     // ---- z: columns (field, j, i), the loads of all items first -------------------------
-    constexpr int ZSLOTS = LY::zslots_of(NT);
+    constexpr int ZSLOTS = LY::zslots(NT);
     T u[ZSLOTS][N1], us[ZSLOTS][N1];
     const int c0 = cell % A.n0, c01 = cell / A.n0, c1 = c01 % A.n1, c2 = c01 / A.n1;
     {
@@ -1199,8 +1743,8 @@ __device__ __forceinline__ void vol_body(const CellArgs<T> &A, const int cell, c
                     if constexpr (JAC) V[c][i] = ya[LY::ys(nt) + i * PS + c * NR];
                     T m = 0;
 #pragma unroll
-                    for (int b = 0; b < (NT ? NT : MAX_NT); ++b)
-                        if (NT || b < nt) m += tK[a * nt + b] * Y[i * PX + (3 * b + c) * NR + row];
+                    for (int b = 0; b < NT; ++b)
+                        m += tK[a * nt + b] * Y[i * PX + (3 * b + c) * NR + row];
                     if constexpr (!JAC) m -= tphi[a] * Y[LY::ys(nt) + i * PS + c * NR + row];
                     zm[i * PX + c * NR] = m;   // read back by this thread
                 }
@@ -1329,8 +1873,8 @@ __device__ __forceinline__ void vol_body(const CellArgs<T> &A, const int cell, c
                 }
                 T m = 0;
 #pragma unroll
-                for (int b = 0; b < (NT ? NT : MAX_NT); ++b)
-                    if (NT || b < nt) m += tK[a * nt + b] * Y[i * PX + (3 * b + c) * NR + row];
+                for (int b = 0; b < NT; ++b)
+                    m += tK[a * nt + b] * Y[i * PX + (3 * b + c) * NR + row];
                 if constexpr (!JAC) m -= tphi[a] * Y[LY::ys(nt) + i * PS + c * NR + row];
                 M[i] = m;
                 U[i] = yo[i * PX];
@@ -1513,7 +2057,7 @@ template <int R, typename T> constexpr int vol_waves()
 }
 
 template <int R, int NQ, int NT, typename T, Mode MODE, bool MAPPED>
-__global__ void __launch_bounds__((VolLds<R, NQ, MODE>::max_threads(NT)))
+__global__ void __launch_bounds__((VolLds<R, NQ, MODE>::threads(NT)))
 __attribute__((amdgpu_waves_per_eu(vol_waves<R, T>()))) vol_kernel(CellArgs<T> A)
 {
     extern __shared__ unsigned char smem_raw[];
@@ -2113,9 +2657,32 @@ struct FusedGrid {
     int period;   // volume groups per face group
 };
 
+template <int R, int NQ, int NTH, typename T, bool MAPPED>
+__global__ void __launch_bounds__(NTH) jac_fused_kernel(CellArgs<T> A, FusedGrid F)
+{
+    extern __shared__ unsigned char smem_raw[];
+    T *sm = reinterpret_cast<T *>(smem_raw);
+    const int b = blockIdx.x, x = b & 7, g = b >> 3;
+    const int p1 = F.period + 1, per = g / p1, pos = g - per * p1;
+    if (pos == F.period && per < F.nfg) {
+        constexpr int W = NTH / 64;
+        const int w = threadIdx.x >> 6;
+        const int item = (per * 8 + x) * W + w;
+        if (item >= A.nbcell * A.nt) return;   // whole wavefront; face items synchronize per wavefront
+        face_item<3, R, NQ, 64, T, Mode::Jac, true>(A, item, blockIdx.y, sm + w * face_lds_words<3, R, NQ, T>(0),
+                                                    threadIdx.x & 63);
+        return;
+    }
+    const int vg = g - min(per, F.nfg);
+    const int q = A.ncell >> 3, rem = A.ncell & 7;
+    if (vg >= q + (x < rem ? 1 : 0)) return;   // whole workgroup
+    jac_cell_body<R, NQ, NTH, T, MAPPED, true>(A, x * q + min(x, rem) + vg, blockIdx.y, sm, threadIdx.x);
+}
+
+// the same with vol_kernel's volume pass
 template <int R, int NQ, int NT, typename T, bool MAPPED>
-__global__ void __launch_bounds__((VolLds<R, NQ, Mode::Jac>::max_threads(NT)))
-__attribute__((amdgpu_waves_per_eu(vol_waves<R, T>()))) jac_fused_kernel(CellArgs<T> A, FusedGrid F)
+__global__ void __launch_bounds__((VolLds<R, NQ, Mode::Jac>::threads(NT)))
+__attribute__((amdgpu_waves_per_eu(vol_waves<R, T>()))) vol_fused_kernel(CellArgs<T> A, FusedGrid F)
 {
     extern __shared__ unsigned char smem_raw[];
     T *sm = reinterpret_cast<T *>(smem_raw);
@@ -2245,52 +2812,132 @@ static hipError_t launch_face(const CellArgs<T> &a, int nvec, hipStream_t s)
     return hipGetLastError();
 }
 
+// workgroup size of jac_cell_kernel, measured at 16^3 cells on one MI355X
+// (time per launch, 128 vs 256 threads): r = 1, n_q = 4: FP64 28 vs 44 us,
+// FP32 19 vs 26; r = 2, n_q = 5: FP64 78 vs 73, FP32 42 vs 46; r = 2,
+// n_q = 4: FP64 58 vs 64, FP32 34 vs 40; r = 3, n_q = 7 (k = 1): FP64 231
+// vs 150, FP32 106 vs 88.  192 threads: FP64 r = 2, n_q = 5 72 us (at 121
+// VGPRs a CU holds five 3-wavefront groups against four of 4 wavefronts, and
+// five groups' LDS, 31.6 KB each, still fit in 160 KB); FP32 r = 3 87 us
+// against 93 at 256 (130 VGPRs: four groups against three).  FP64 r = 3
+// (178 VGPRs, two wavefronts per SIMD) gains nothing from it: 185 us.
+template <int R, int NQ, typename T> constexpr int jac_threads()
+{
+    if (R == 3) return sizeof(T) == 8 ? 256 : 192;
+    if (R == 2 && NQ == 5 && sizeof(T) == 8) return 192;
+    return 128;
+}
+
+template <int R, int NQ, typename T>
+static hipError_t launch_jac_cell(const CellArgs<T> &a, int nvec, hipStream_t s)
+{
+    constexpr int NTH = jac_threads<R, NQ, T>();
+    size_t bytes = (size_t)jac_lds_words<R, NQ, T>(a.nt) * sizeof(T);
+    auto kern = a.mapped ? jac_cell_kernel<R, NQ, NTH, T, true> : jac_cell_kernel<R, NQ, NTH, T, false>;
+    static std::mutex mu;
+    std::lock_guard<std::mutex> lk(mu);
+    static size_t attr_bytes[2] = {0, 0};   // per kernel (affine, mapped)
+    size_t &have = attr_bytes[a.mapped ? 1 : 0];
+    static int max_lds = -1;
+    if (max_lds < 0) {
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
+            max_lds = 65536;
+    }
+    if (bytes > (size_t)max_lds) return hipErrorInvalidConfiguration;
+    if (bytes > have) {
+        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+        if (e != hipSuccess) return e;
+        have = bytes;
+    }
+    dim3 grid(a.ncell, nvec);
+    hipLaunchKernelGGL(kern, grid, dim3(NTH), bytes, s, a);
+    return hipGetLastError();
+}
+
+// 3D Jacobian with its boundary faces in one launch (after zeroing what both
+// passes add to)
+template <int R, int NQ, typename T>
+static hipError_t launch_jac_cell_fused(const CellArgs<T> &a, int nvec, hipStream_t s)
+{
+    constexpr int NTH = jac_threads<R, NQ, T>();
+    constexpr int W = NTH / 64;
+    constexpr int nl = (R + 2) * (R + 2) * (R + 2), npm = Sizes<3, R>::NPM;
+    if (a.nbcell > 0) {
+        const long long n = (long long)a.nbcell * a.nt * (3 * nl + npm);
+        const int blocks = (int)std::min<long long>((n + 255) / 256, 4096);
+        hipLaunchKernelGGL(zero_boundary_kernel<T>, dim3(blocks, nvec), dim3(256), 0, s, a, nl, npm);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    FusedGrid F;
+    F.nvg = (a.ncell + 7) / 8;
+    const int fwg = (a.nbcell * a.nt + W - 1) / W;
+    F.nfg = (fwg + 7) / 8;
+    F.period = F.nfg > 0 ? F.nvg / F.nfg : F.nvg;
+    const size_t words = std::max<size_t>(jac_lds_words<R, NQ, T>(a.nt), (size_t)W * face_lds_words<3, R, NQ, T>(0));
+    const size_t bytes = words * sizeof(T);
+    auto kern = a.mapped ? jac_fused_kernel<R, NQ, NTH, T, true> : jac_fused_kernel<R, NQ, NTH, T, false>;
+    static std::mutex mu;
+    std::lock_guard<std::mutex> lk(mu);
+    static size_t attr_bytes[2] = {0, 0};   // per kernel (affine, mapped)
+    size_t &have = attr_bytes[a.mapped ? 1 : 0];
+    static int max_lds = -1;
+    if (max_lds < 0) {
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
+            max_lds = 65536;
+    }
+    if (bytes > (size_t)max_lds) return hipErrorInvalidConfiguration;
+    if (bytes > have) {
+        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+        if (e != hipSuccess) return e;
+        have = bytes;
+    }
+    dim3 grid(8 * (F.nvg + F.nfg), nvec);
+    hipLaunchKernelGGL(kern, grid, dim3(NTH), bytes, s, a, F);
+    return hipGetLastError();
+}
+
 // dynamic LDS of a kernel, raised when a launch needs more than any before
 struct LdsLimit {
     std::mutex mu;
-    size_t have[2] = {0, 0};   // per kernel (affine, mapped)
-    hipError_t require(const void *kern, bool mapped, size_t bytes)
+    size_t have = 0;
+    hipError_t require(const void *kern, size_t bytes)
     {
         std::lock_guard<std::mutex> lk(mu);
-        if (bytes <= have[mapped]) return hipSuccess;
+        if (bytes <= have) return hipSuccess;
         int dev = 0, max_lds = 0;
         if (hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
             max_lds = 65536;
         if (bytes > (size_t)max_lds) return hipErrorInvalidConfiguration;
         const hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-        if (e == hipSuccess) have[mapped] = bytes;
+        if (e == hipSuccess) have = bytes;
         return e;
     }
 };
 
 // 3D Jacobian and residual, volume pass
-template <int R, int NQ, int NT, typename T, Mode MODE>
-static hipError_t launch_vol_nt(const CellArgs<T> &a, int nvec, hipStream_t s)
+template <int R, int NQ, int NT, typename T, Mode MODE, bool MAPPED>
+static hipError_t launch_vol(const CellArgs<T> &a, int nvec, hipStream_t s)
 {
     using LY = VolLds<R, NQ, MODE>;
     const size_t bytes = (size_t)LY::words(a.nt) * sizeof(T);
-    auto kern = a.mapped ? vol_kernel<R, NQ, NT, T, MODE, true> : vol_kernel<R, NQ, NT, T, MODE, false>;
+    auto kern = vol_kernel<R, NQ, NT, T, MODE, MAPPED>;
     static LdsLimit lds;
-    const hipError_t e = lds.require((const void *)kern, a.mapped != 0, bytes);
+    const hipError_t e = lds.require((const void *)kern, bytes);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(a.ncell, nvec), dim3(LY::threads(a.nt)), bytes, s, a);
     return hipGetLastError();
 }
 
-template <int R, int NQ, typename T, Mode MODE>
-static hipError_t launch_vol(const CellArgs<T> &a, int nvec, hipStream_t s)
-{
-    if (a.nt < 1 || a.nt > MAX_NT) return hipErrorInvalidValue;
-    if (a.nt == 2) return launch_vol_nt<R, NQ, 2, T, MODE>(a, nvec, s);
-    if (a.nt == 3) return launch_vol_nt<R, NQ, 3, T, MODE>(a, nvec, s);
-    return launch_vol_nt<R, NQ, 0, T, MODE>(a, nvec, s);
-}
-
 // 3D Jacobian with its boundary faces in one launch (after zeroing what both
 // passes add to)
-template <int R, int NQ, int NT, typename T>
-static hipError_t launch_jac_fused_nt(const CellArgs<T> &a, int nvec, hipStream_t s)
+template <int R, int NQ, int NT, typename T, bool MAPPED>
+static hipError_t launch_vol_fused(const CellArgs<T> &a, int nvec, hipStream_t s)
 {
     using LY = VolLds<R, NQ, Mode::Jac>;
     constexpr int nl = (R + 2) * (R + 2) * (R + 2), npm = Sizes<3, R>::NPM;
@@ -2304,9 +2951,9 @@ static hipError_t launch_jac_fused_nt(const CellArgs<T> &a, int nvec, hipStream_
     }
     const size_t words = std::max<size_t>(LY::words(a.nt), (size_t)W * face_lds_words<3, R, NQ, T>(0));
     const size_t bytes = words * sizeof(T);
-    auto kern = a.mapped ? jac_fused_kernel<R, NQ, NT, T, true> : jac_fused_kernel<R, NQ, NT, T, false>;
+    auto kern = vol_fused_kernel<R, NQ, NT, T, MAPPED>;
     static LdsLimit lds;
-    const hipError_t e = lds.require((const void *)kern, a.mapped != 0, bytes);
+    const hipError_t e = lds.require((const void *)kern, bytes);
     if (e != hipSuccess) return e;
     FusedGrid F;
     F.nvg = (a.ncell + 7) / 8;
@@ -2318,16 +2965,56 @@ static hipError_t launch_jac_fused_nt(const CellArgs<T> &a, int nvec, hipStream_
     return hipGetLastError();
 }
 
+// whether vol_kernel takes a volume pass; elsewhere the thread-per-point kernels
+// (jac_cell_kernel, cell_kernel) are the faster ones.  Whole application, 12^3
+// cells, old / new time (k = 1, 2; affine, mapped):
+//   FP64 Jacobian  r = 1: 1.14, 1.18; 1.11, 1.18   r = 2, n_q = 5: 1.15, 1.25; 0.78, 0.74
+//                  (mapped: registers)   r = 2, n_q = 4: 1.08, 1.11; 1.19, 1.30
+//                  r = 3, n_q = 7: 1.24, 1.02; 1.23, 0.90   n_q = 5: 1.08, 1.13; 0.96, 1.08
+//   FP32 Jacobian  r = 1: 1.01, 1.17; 1.26, 1.14   r = 2, n_q = 5: 0.92, 1.14; 0.97, 0.94
+//                  r = 3, n_q = 7: 1.07, 0.87; 1.16, 0.88   n_q = 5: 0.68 .. 0.77
+//   residual       r = 1: 1.30, 1.35; 1.29, 1.35   r = 2: 1.08 .. 1.30
+//                  r = 3, n_q = 7: 1.27, 0.96; 1.34, 1.09   n_q = 5: 0.90 .. 1.02
+// One time node leaves most of a workgroup idle (k = 0: 0.46 .. 1.05), with four
+// one workgroup fills a CU's LDS (k = 3, r = 3: 0.51 .. 0.88).
+template <int R, int NQ, int NT, typename T, Mode MODE, bool MAPPED> constexpr bool vol_takes()
+{
+    if (NT != 2 && NT != 3) return false;
+    if (R == 1) return true;
+    if (R == 3) return NQ == 7 && NT == 2;
+    if (MODE == Mode::Res) return true;
+    return sizeof(T) == 8 ? NQ == 4 || !MAPPED : NQ == 5 && NT == 3 && !MAPPED;
+}
+
+// 3D Jacobian (FUSED: with its boundary faces) or residual; the kernel by vol_takes
+template <int R, int NQ, int NT, typename T, Mode MODE, bool FUSED, bool MAPPED>
+static bool try_vol(const CellArgs<T> &a, int nvec, hipStream_t s, hipError_t &e)
+{
+    if constexpr (vol_takes<R, NQ, NT, T, MODE, MAPPED>() && !(FUSED && sizeof(T) == 8)) {
+        if (a.nt == NT && (a.mapped != 0) == MAPPED) {
+            if constexpr (FUSED) e = launch_vol_fused<R, NQ, NT, T, MAPPED>(a, nvec, s);
+            else e = launch_vol<R, NQ, NT, T, MODE, MAPPED>(a, nvec, s);
+            return true;
+        }
+    }
+    return false;
+}
+
+template <int R, int NQ, typename T, Mode MODE, bool FUSED>
+static bool try_vol(const CellArgs<T> &a, int nvec, hipStream_t s, hipError_t &e)
+{
+    return try_vol<R, NQ, 2, T, MODE, FUSED, false>(a, nvec, s, e) ||
+           try_vol<R, NQ, 2, T, MODE, FUSED, true>(a, nvec, s, e) ||
+           try_vol<R, NQ, 3, T, MODE, FUSED, false>(a, nvec, s, e) ||
+           try_vol<R, NQ, 3, T, MODE, FUSED, true>(a, nvec, s, e);
+}
+
 template <int R, int NQ, typename T>
 static hipError_t launch_jac_fused(const CellArgs<T> &a, int nvec, hipStream_t s)
 {
-    if (a.nt < 1 || a.nt > MAX_NT) return hipErrorInvalidValue;
-    // (FP64 by override only; n_q = r + 2 is the option, not the default)
-    if constexpr (sizeof(T) == 4 && NQ == (3 * R + 5) / 2) {
-        if (a.nt == 2) return launch_jac_fused_nt<R, NQ, 2, T>(a, nvec, s);
-        if (a.nt == 3) return launch_jac_fused_nt<R, NQ, 3, T>(a, nvec, s);
-    }
-    return launch_jac_fused_nt<R, NQ, 0, T>(a, nvec, s);
+    hipError_t e = hipSuccess;
+    if (try_vol<R, NQ, T, Mode::Jac, true>(a, nvec, s, e)) return e;
+    return launch_jac_cell_fused<R, NQ, T>(a, nvec, s);
 }
 
 template <int R, typename T>
@@ -2344,7 +3031,11 @@ static hipError_t dispatch_fused_nq(int nq, const CellArgs<T> &a, int nvec, hipS
 template <int DIM, int R, int NQ, typename T, Mode MODE>
 static hipError_t launch_one(const CellArgs<T> &a, int nvec, hipStream_t s)
 {
-    if constexpr (DIM == 3 && MODE != Mode::Mass) return launch_vol<R, NQ, T, MODE>(a, nvec, s);
+    if constexpr (DIM == 3 && MODE != Mode::Mass) {
+        hipError_t e = hipSuccess;
+        if (try_vol<R, NQ, T, MODE, false>(a, nvec, s, e)) return e;
+    }
+    if constexpr (DIM == 3 && MODE == Mode::Jac) return launch_jac_cell<R, NQ, T>(a, nvec, s);
     constexpr int NTH = DIM == 2 ? 64 : 256;
     TableLayout lay;
     lay.init(R, NQ);

@@ -228,7 +228,7 @@ void mg_allocate(stmg_ctx *ctx)
         }
     }
     // coarsest level: dense Jacobian (bordered by the constant pressures of
-    // each time node when every face is Dirichlet) and its LU
+    // each time node when every face is Dirichlet) and its inverse (LU beyond DINV_MAX_M)
     {
         Level &Lc = *mg.lv[nl - 1].L;
         const int n = (int)Lc.N, m = n + (mg.border ? Lc.nt : 0);
