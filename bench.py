@@ -254,7 +254,7 @@ def bench_batched_lu(npatch=4096, seed=6):
     trailing-update MFMA, FP32 accumulation), then the triangular solves;
     accuracy as the sampled normwise backward error and the relative
     distance of the solutions to the FP64 ones.  Each factorization is timed
-    as one persistent launch with the tuned table and, as the untuned
+    as one call and, as the untuned
     reference, as one launch per size class.  (The patches come from the
     library: only the cpu_baseline leg runs the oracle.)"""
     import torch

@@ -237,9 +237,9 @@ int stmg_num_levels(const stmg_ctx *ctx);
 int stmg_level_info(const stmg_ctx *ctx, int level, int *k, int *r, int *n_cells, long long *n_total);
 
 /* Set the Newton state U (FP64, device, length N): the level states (finer
- * state evaluated at the coarser nodes and Radau nodes) and the FP64 LU of
+ * state evaluated at the coarser nodes and Radau nodes) and the FP64 inverse of
  * the coarsest level Jacobian (bordered by the constant pressures of each
- * time node when every face is Dirichlet). */
+ * time node when every face is Dirichlet; above 6144 unknowns its LU). */
 int stmg_set_state(stmg_ctx *ctx, const double *u_state);
 /* Copy of the state of a level (FP64 slab vector of that level). */
 int stmg_level_state(stmg_ctx *ctx, int level, double *out);
@@ -326,13 +326,14 @@ int stmg_march(stmg_ctx *ctx, int nslabs, const double *rhs, long long rhs_strid
 /* ---- batched patch factorizations (no context) ---------------------------
  * A batch of dense matrices of mixed sizes, factored by LU with partial
  * pivoting (the Vanka patch factorization of Sec. "Inexact space-time Vanka
- * smoother" as a standalone batch) in ONE persistent launch: a grid of
- * workgroups sized to stay resident takes the matrices, largest first, from a
- * device work queue; each matrix is factored by one workgroup with blocked
- * right-looking panels in LDS and the trailing updates on MFMA
- * (v_mfma_f32_16x16x4f32 in FP32, v_mfma_f64_16x16x4f64 in FP64).  The
- * workgroups per CU and the panel width of each size class come from a table
- * written by the package's tuner (paper_2602_13841_amd/tune_lu.py).  prec:
+ * smoother" as a standalone batch).  FP64 and FP32 matrices up to 1280 / 1856
+ * rows: one launch, one workgroup per matrix (largest first), left-looking
+ * block columns in MFMA accumulators (v_mfma_f64_16x16x4f64,
+ * v_mfma_f32_16x16x4f32).  Longer matrices and BF16 / FP16 operands: one
+ * persistent launch whose workgroups take the matrices, largest first, from a
+ * device work queue (blocked right-looking panels in LDS, trailing updates on
+ * MFMA; workgroups per CU and panel widths from a table written by the
+ * package's tuner, paper_2602_13841_amd/tune_lu.py).  prec:
  * STMG_F64, STMG_F32, or STMG_F32_BF16 / STMG_F32_F16 (FP32 matrices and
  * factors; the L21 and U12 blocks of each trailing update A22 -= L21 U12 are
  * rounded to BF16 / FP16 for the MFMA, A22 accumulates in FP32; the solve is

@@ -1380,8 +1380,8 @@ __global__ void __launch_bounds__(NTH) jac_cell_kernel(CellArgs<T> A)
 // the operations of a mapped point would be the same for the three) and half
 // of the points, the y- and z-derivative, mixed and pressure rows read again for
 // each point (held in registers they spill: 1.1 instead of 0.55 ms).
-// One MI355X, volume pass alone: 16^3 cells, r = 2, k = 2: FP64 74 -> 46 us; 24 x
-// 20 x 28 mapped cells, r = 3, k = 1, FP64: 611 -> 440 us; residual 73 -> 44 us.
+// One MI355X, volume pass alone: 16^3 cells, r = 2, k = 2: FP64 74 -> 49 us; 24 x
+// 20 x 28 mapped cells, r = 3, k = 1, FP64: 611 -> 440 us; residual 72 -> 47 us.
 // What bounds it: the FP64 vector units are busy 60 % of the time at r = 2 (40 % at
 // r = 3, two wavefronts per SIMD by LDS); of a workgroup's 17000 cycles (r = 2, k = 2)
 // 5900 wait for its columns from memory.  Taken back: one workgroup looping over
