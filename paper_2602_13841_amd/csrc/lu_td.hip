@@ -45,6 +45,8 @@ namespace {
 
 __device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ __forceinline__ float abs_(float x) { return __builtin_fabsf(x); }
+__device__ __forceinline__ double abs_(double x) { return __builtin_fabs(x); }
 
 typedef float floatx4_t __attribute__((ext_vector_type(4)));
 typedef double doublex4_t __attribute__((ext_vector_type(4)));
@@ -108,8 +110,8 @@ __device__ __forceinline__ double lane_value(double x, int l)
     return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 // wavefront maximum, uniform (row_shr 1, 2, 4, 8, then row_bcast 15 and 31).
-// FP32: as integers, which order like the values for v >= 0 and the sentinel
-// -1, so that each step is one instruction.
+// FP32: as integers, which order like the values for v >= +0 and the sentinel
+// -1, so that each step is one instruction (-0 would be the lowest of all).
 __device__ __forceinline__ float wave_max(float x)
 {
     int v = __float_as_int(x);
@@ -581,7 +583,10 @@ __device__ __forceinline__ void lu_left(T *__restrict__ Ar, int m, int ld, int *
                     constexpr int WD = decltype(width)::value;
                     const int ce = min(cb + 4, nb);
                     if (idle) {
-                        if (lane < 2) wval[lane][wv] = T(-1);
+                        if (lane < 2) {
+                            wval[lane][wv] = T(-1);
+                            wkey[lane][wv] = 0;
+                        }
                         for (int c = cb; c < ce; ++c) __syncthreads();
                         return;
                     }
@@ -592,8 +597,9 @@ __device__ __forceinline__ void lu_left(T *__restrict__ Ar, int m, int ld, int *
                         int bi_ = 0, bl = 0x7fffffff;
 #pragma unroll
                         for (int i = 0; i < RPT; ++i) {
+                            // (never -0: wave_max orders FP32 values by their bits)
                             T v = CX ? fma_(xr[i][0], xr[i][0], xi[CX ? i : 0][0] * xi[CX ? i : 0][0])
-                                     : (xr[i][0] < 0 ? -xr[i][0] : xr[i][0]);
+                                     : abs_(xr[i][0]);
                             v = v >= T(0) ? v : T(0);   // NaN
                             const bool better = ((open >> i) & 1u) && (v > best || (STD && v == best && lg[i] < bl));
                             best = better ? v : best;

@@ -73,3 +73,26 @@ def test_ties_and_zero_pivots():
         out, info = factor([np.zeros((35, 35)), np.eye(20)], dt)
         assert info == 35 and np.array_equal(out[0][1], np.arange(35)) and np.array_equal(out[1][1], np.arange(20))
         assert np.array_equal(out[1][0], np.eye(20))
+
+
+@pytest.mark.parametrize("m", [1, 20, 35, 64, 100, 130, 257, 513])
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+def test_negative_zero_pivots(prec, m):
+    """A column of -0 is a zero pivot like one of +0: counted, no interchange,
+    and the other columns factored as usual."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    dt = torch.float64 if prec == "f64" else torch.float32
+    out, info = factor([-np.zeros((m, m))], dt)
+    assert info == m and np.array_equal(out[0][1], np.arange(m)) and not out[0][0].any()
+    # a diagonal matrix (exact in both precisions), its last and a middle
+    # column -0, negated zeros everywhere off the diagonal
+    M = -np.zeros((m, m))
+    d = 1.0 + np.arange(m) % 5
+    d[[m // 2, m - 1]] = -0.0
+    np.fill_diagonal(M, -d)
+    for mats in ([M], [M, -M, np.eye(40)]):   # alone and beside others
+        out, info = factor(mats, dt)
+        assert info == len({m // 2, m - 1}) * min(len(mats), 2)
+        for A, (F, piv) in zip(mats, out):
+            assert np.array_equal(piv, np.arange(len(A))) and np.array_equal(F, A)
