@@ -98,10 +98,6 @@ template <int CTRL, int RM> __device__ __forceinline__ double dpp(double x)
     const int h = __builtin_amdgcn_update_dpp(hi, hi, CTRL, RM, 0xf, false);
     return __longlong_as_double(((long long)h << 32) | (unsigned)l);
 }
-__device__ __forceinline__ float lane_value(float x, int l)
-{
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l));
-}
 __device__ __forceinline__ double lane_value(double x, int l)
 {
     const long long b = __double_as_longlong(x);
@@ -109,12 +105,31 @@ __device__ __forceinline__ double lane_value(double x, int l)
     const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
     return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
-// wavefront maximum, uniform (row_shr 1, 2, 4, 8, then row_bcast 15 and 31).
-// FP32: as integers, which order like the values for v >= +0 and the sentinel
-// -1, so that each step is one instruction (-0 would be the lowest of all).
-__device__ __forceinline__ float wave_max(float x)
+// Pivot keys: order the candidates of a column like their moduli, a NaN below
+// every number and a row that is no candidate below a NaN, so that a NaN is
+// the pivot only of a column without a number (and is not a zero pivot).  FP32: the bits of the modulus (>= +0) as an integer, which has the order of
+// the values and makes each step of the maxima one instruction.
+template <typename T> struct Pivot;
+template <> struct Pivot<float> {
+    using key = int;
+    static constexpr key NONE = -2;
+    static __device__ __forceinline__ key of(float modulus) { return modulus >= 0.0f ? __float_as_int(modulus) : -1; }
+};
+template <> struct Pivot<double> {
+    using key = double;
+    static constexpr key NONE = -2.0;
+    static __device__ __forceinline__ key of(double modulus) { return modulus >= 0.0 ? modulus : -1.0; }
+};
+template <int CTRL, int RM> __device__ __forceinline__ int dpp(int x)
 {
-    int v = __float_as_int(x);
+    return __builtin_amdgcn_update_dpp(x, x, CTRL, RM, 0xf, false);
+}
+__device__ __forceinline__ int lane_value(int x, int l) { return __builtin_amdgcn_readlane(x, l); }
+__device__ __forceinline__ int max_of(int a, int b) { return max(a, b); }
+__device__ __forceinline__ double max_of(double a, double b) { return fmax(a, b); }
+// wavefront maximum, uniform (row_shr 1, 2, 4, 8, then row_bcast 15 and 31)
+__device__ __forceinline__ int wave_max(int v)
+{
     constexpr int lowest = -0x7fffffff - 1;
     v = max(v, __builtin_amdgcn_update_dpp(lowest, v, 0x111, 0xf, 0xf, false));
     v = max(v, __builtin_amdgcn_update_dpp(lowest, v, 0x112, 0xf, 0xf, false));
@@ -122,10 +137,8 @@ __device__ __forceinline__ float wave_max(float x)
     v = max(v, __builtin_amdgcn_update_dpp(lowest, v, 0x118, 0xf, 0xf, false));
     v = max(v, __builtin_amdgcn_update_dpp(lowest, v, 0x142, 0xa, 0xf, false));
     v = max(v, __builtin_amdgcn_update_dpp(lowest, v, 0x143, 0xc, 0xf, false));
-    return __int_as_float(__builtin_amdgcn_readlane(v, 63));
+    return __builtin_amdgcn_readlane(v, 63);
 }
-__device__ __forceinline__ float max_of(float a, float b) { return fmaxf(a, b); }
-__device__ __forceinline__ double max_of(double a, double b) { return fmax(a, b); }
 __device__ __forceinline__ double wave_max(double v)
 {
     v = fmax(v, dpp<0x111, 0xf>(v));
@@ -280,9 +293,11 @@ __device__ __forceinline__ void lu_left(T *__restrict__ Ar, int m, int ld, int *
     int *cur = reinterpret_cast<int *>(lkk + (STD ? TD_BW * (TD_BW + 1) : 0));   // stored row at each position
     int *rk = cur + ((m + 31) & ~31);                          // rank of a panel row among the block's pivots, or -1
     int *pl = rk + ((m + 31) & ~31);                           // panel row of each pivot of the block
-    // pivot candidates of the wavefronts, by column parity: value, panel row |
+    // pivot candidates of the wavefronts, by column parity: key, panel row |
     // position << 16, and the row from its current column on
-    __shared__ alignas(16) T wval[2][NW];
+    using PV = Pivot<T>;
+    using key_t = typename PV::key;
+    __shared__ alignas(16) key_t wval[2][NW];
     __shared__ alignas(16) int wkey[2][NW];
     __shared__ alignas(16) T pub[2][NW][16 * P];
 
@@ -584,7 +599,7 @@ __device__ __forceinline__ void lu_left(T *__restrict__ Ar, int m, int ld, int *
                     const int ce = min(cb + 4, nb);
                     if (idle) {
                         if (lane < 2) {
-                            wval[lane][wv] = T(-1);
+                            wval[lane][wv] = PV::NONE;
                             wkey[lane][wv] = 0;
                         }
                         for (int c = cb; c < ce; ++c) __syncthreads();
@@ -593,20 +608,18 @@ __device__ __forceinline__ void lu_left(T *__restrict__ Ar, int m, int ld, int *
 #pragma unroll 1
                     for (int c = cb; c < ce; ++c) {
                         const int par = c & 1;
-                        T best = T(-1);
+                        key_t best = PV::NONE;
                         int bi_ = 0, bl = 0x7fffffff;
 #pragma unroll
                         for (int i = 0; i < RPT; ++i) {
-                            // (never -0: wave_max orders FP32 values by their bits)
-                            T v = CX ? fma_(xr[i][0], xr[i][0], xi[CX ? i : 0][0] * xi[CX ? i : 0][0])
-                                     : abs_(xr[i][0]);
-                            v = v >= T(0) ? v : T(0);   // NaN
+                            const key_t v = PV::of(
+                                CX ? fma_(xr[i][0], xr[i][0], xi[CX ? i : 0][0] * xi[CX ? i : 0][0]) : abs_(xr[i][0]));
                             const bool better = ((open >> i) & 1u) && (v > best || (STD && v == best && lg[i] < bl));
                             best = better ? v : best;
                             bl = better ? lg[i] : bl;
                             bi_ = better ? i : bi_;
                         }
-                        const T wm = wave_max(best);
+                        const key_t wm = wave_max(best);
                         unsigned long long hit = __ballot(best == wm);
                         if (STD && __popcll(hit) > 1) {
                             // LAPACK: ties go to the smallest position
@@ -632,9 +645,9 @@ __device__ __forceinline__ void lu_left(T *__restrict__ Ar, int m, int ld, int *
                             }
                         __syncthreads();
                         // the winner: candidate w in lane w (mod NW)
-                        const T cv = wval[par][lane & (NW - 1)];
+                        const key_t cv = wval[par][lane & (NW - 1)];
                         const int ck = wkey[par][lane & (NW - 1)] | (lane & (NW - 1)) << 12;
-                        T top = cv;
+                        key_t top = cv;
                         if constexpr (NW > 1) top = max_of(top, dpp<0xB1, 0xf>(top));    // quad_perm 1,0,3,2
                         if constexpr (NW > 2) top = max_of(top, dpp<0x4E, 0xf>(top));    // quad_perm 2,3,0,1
                         if constexpr (NW > 4) top = max_of(top, dpp<0x141, 0xf>(top));   // row_half_mirror
@@ -660,7 +673,7 @@ __device__ __forceinline__ void lu_left(T *__restrict__ Ar, int m, int ld, int *
                             pl[c0 + c] = R;
                             rk[R] = c0 + c;
                             if constexpr (STD) ip[j0 + c0 + c] = j0 + p;
-                            if (info && lane_value(top, 0) == T(0)) atomicAdd(info, 1);
+                            if (info && lane_value(top, 0) == key_t(0)) atomicAdd(info, 1);
                         }
                         T ir, ii;
                         reciprocal<T, CX>(ur[0], ui[0], ir, ii);

@@ -1,0 +1,50 @@
+"""Left-looking batched LU (stmg_batched_lu in FP64 and FP32) on matrices with
+NaN entries, against the persistent right-looking kernel (explicit launch
+parameters) on the same matrices (GPU)."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+
+def factor(A, dt, config=None):
+    from paper_2602_13841_amd import stmg
+    m = len(A)
+    F = torch.tensor(A, dtype=dt, device="cuda")
+    piv = torch.full((m,), -1, dtype=torch.int32, device="cuda")
+    info = torch.zeros(1, dtype=torch.int32, device="cuda")
+    stmg.batched_lu(F, [0], [m], piv, [0], info, config=config)
+    return F.cpu().numpy(), piv.cpu().numpy(), int(info.item())
+
+
+@pytest.mark.parametrize("m", [3, 40, 130, 300, 600])
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+def test_nan_pivots(prec, m):
+    """NaN is below every number in the pivot search: a zero is taken before
+    it, and a column without a number keeps its row and is no zero pivot."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    dt = torch.float64 if prec == "f64" else torch.float32
+    rng = np.random.Generator(np.random.PCG64(83))
+    right_looking = (1, [16, 16, 16, 8, 4], 256)
+    # [NaN, 0, 0, ...] and zeros elsewhere: the first zero, in every column
+    A = np.zeros((m, m))
+    A[0, 0] = np.nan
+    F, piv, info = factor(A, dt)
+    _, ref, ref_info = factor(A, dt, right_looking)
+    assert piv[0] == 1 and info == m - 1
+    assert np.array_equal(piv, ref) and info == ref_info
+    # no number in column 0, hence in none
+    A = rng.uniform(-1, 1, (m, m))
+    A[:, 0] = np.nan
+    F, piv, info = factor(A, dt)
+    _, ref, ref_info = factor(A, dt, right_looking)
+    assert np.array_equal(piv, np.arange(m)) and np.array_equal(piv, ref) and info == ref_info == 0
+    # one NaN: its row is the last pivot, the others are factored without it
+    A = rng.uniform(-1, 1, (m, m))
+    A[0, 0], A[2, 0] = np.nan, 8.0
+    F, piv, info = factor(A, dt)
+    assert piv[0] == 2 and info == 0
+    assert np.all(np.isfinite(F[:-1])) and np.all(np.isnan(F[-1]))
