@@ -243,8 +243,14 @@ template <typename T, bool CX> __device__ __forceinline__ void reciprocal(T dr, 
     if constexpr (CX) {
         const T den = fma_(dr, dr, di * di);
         const T inv = T(1) / den;
-        ir = den != T(0) ? dr * inv : T(0);
-        ii = den != T(0) ? -di * inv : T(0);
+        ir = dr * inv;
+        ii = -di * inv;
+        // a pivot so small that 1 / den overflows (FP32: below 5.4e-20) still
+        // has a finite reciprocal; zero: no elimination
+        if (!(inv < T(__builtin_inf()))) {
+            ir = den != T(0) ? dr / den : T(0);
+            ii = den != T(0) ? -di / den : T(0);
+        }
     } else {
         const T inv = T(1) / dr;
         ir = dr != T(0) ? inv : T(0);

@@ -48,3 +48,21 @@ def test_nan_pivots(prec, m):
     F, piv, info = factor(A, dt)
     assert piv[0] == 2 and info == 0
     assert np.all(np.isfinite(F[:-1])) and np.all(np.isnan(F[-1]))
+
+
+@pytest.mark.parametrize("d,n,r,nu,tau", [(3, (2, 1, 1), 2, 3e-19, 1e19), (2, (2, 2), 3, 3e-20, 1e20)],
+                         ids=["3d_r2", "2d_r3"])
+def test_small_complex_pivots(d, n, r, nu, tau):
+    """Almost no viscosity and a long slab without Dirichlet faces: FP32 patch
+    systems whose velocity pivots (1e-20 and below 5.4e-20) have a squared
+    modulus with a reciprocal beyond the FP32 range.  The pivots' own
+    reciprocals are finite, and so is a sweep."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2602_13841_amd import stmg
+    ctx = stmg.Context(d, n, r, 1, nu, tau, dirichlet_faces=0, prec_mg=stmg.STMG_F32, fgmres_maxit=1)
+    ctx.smoother_rebuild(torch.zeros(ctx.N, dtype=torch.float64, device="cuda"))
+    b = 1e-10 * torch.rand(ctx.N, generator=torch.Generator().manual_seed(1), dtype=torch.float64)
+    x = torch.zeros(ctx.N, dtype=torch.float32, device="cuda")
+    ctx.vanka_smooth(0, b.to("cuda", torch.float32), x)
+    assert bool(torch.isfinite(x).all()) and bool(x.any())
