@@ -1432,8 +1432,11 @@ __device__ __forceinline__ void block_gemv_update(const T *__restrict__ L, int l
 #pragma unroll
             for (int i = 0; i < CPL; ++i) {
                 const int c = l16 + 16 * i;
+                // (formed before the load: a condition in the select itself
+                // makes the compiler branch around each load and wait for it)
+                const bool ok = r < rend && c < nbk;
                 const T v = L[o + min(c, nbk - 1)];
-                l[u][i] = r < rend && c < nbk ? v : T(0);
+                l[u][i] = ok ? v : T(0);
             }
         }
 #pragma unroll
