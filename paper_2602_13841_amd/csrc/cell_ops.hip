@@ -2986,12 +2986,28 @@ template <int R, int NQ, int NT, typename T, Mode MODE, bool MAPPED> constexpr b
     return sizeof(T) == 8 ? NQ == 4 || !MAPPED : NQ == 5 && NT == 3 && !MAPPED;
 }
 
+// and for how many cells: the FP32 Jacobian of r = 2 and 3 gains by shorter rounds
+// of workgroups, but fewer of them share a CU.  Old / new time, one application:
+//   r = 2, n_q = 5, k = 2 (256 threads instead of 128): up to 4 cells per CU one
+//     round either way, 0.93 .. 1.01; 1120 .. 1280 cells 1.02, above 1.07 .. 1.19
+//   r = 3, n_q = 7, k = 1 (affine, mapped): up to 640 cells 0.99 .. 1.06, 1.03 .. 1.10;
+//     720 .. 864 cells, one round of the old and two of the new: 0.87 .. 0.95,
+//     0.86 .. 0.89; from 960 on 0.97 .. 1.15, 1.03 .. 1.24
+// Everything else was the faster one at 1 to 7680 cells.
+template <int R, typename T> static bool vol_takes_cells(int ncell)
+{
+    constexpr int cus = 256;
+    if (sizeof(T) == 8 || R == 1) return true;
+    if (R == 2) return ncell > 4 * cus;
+    return 2 * ncell <= 5 * cus || 2 * ncell > 7 * cus;
+}
+
 // 3D Jacobian (FUSED: with its boundary faces) or residual; the kernel by vol_takes
 template <int R, int NQ, int NT, typename T, Mode MODE, bool FUSED, bool MAPPED>
 static bool try_vol(const CellArgs<T> &a, int nvec, hipStream_t s, hipError_t &e)
 {
     if constexpr (vol_takes<R, NQ, NT, T, MODE, MAPPED>() && !(FUSED && sizeof(T) == 8)) {
-        if (a.nt == NT && (a.mapped != 0) == MAPPED) {
+        if (a.nt == NT && (a.mapped != 0) == MAPPED && vol_takes_cells<R, T>(a.ncell)) {
             if constexpr (FUSED) e = launch_vol_fused<R, NQ, NT, T, MAPPED>(a, nvec, s);
             else e = launch_vol<R, NQ, NT, T, MODE, MAPPED>(a, nvec, s);
             return true;
