@@ -61,6 +61,37 @@ struct DevAlloc {
     }
 };
 
+// a second stream of one call: starts behind what the caller's stream holds,
+// and the caller's stream waits for it at the end.  Where it cannot be made,
+// its work goes to the caller's stream.
+struct SideStream {
+    hipStream_t main, side = nullptr;
+    hipEvent_t ev = nullptr;
+    explicit SideStream(hipStream_t s) : main(s) {}
+    hipStream_t fork()
+    {
+        if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) ev = nullptr;
+        else if (hipStreamCreateWithFlags(&side, hipStreamNonBlocking) != hipSuccess) side = nullptr;
+        else if (hipEventRecord(ev, main) != hipSuccess || hipStreamWaitEvent(side, ev, 0) != hipSuccess) {
+            (void)hipStreamDestroy(side);
+            side = nullptr;
+        }
+        if (!side) (void)hipGetLastError();
+        return side ? side : main;
+    }
+    hipError_t join()
+    {
+        if (!side) return hipSuccess;
+        if (hipEventRecord(ev, side) == hipSuccess && hipStreamWaitEvent(main, ev, 0) == hipSuccess) return hipSuccess;
+        return hipStreamSynchronize(side);
+    }
+    ~SideStream()
+    {
+        if (side) (void)hipStreamDestroy(side);
+        if (ev) (void)hipEventDestroy(ev);
+    }
+};
+
 } // namespace
 
 size_t batched_lu_meta_bytes(int batch) { return META_HEADER_BYTES + (size_t)batch * META_BYTES_PER_MATRIX; }
@@ -186,21 +217,27 @@ int batched_lu_run(int prec, void *A, const long long *a_off, const int *m_of, i
         else
             e = launch_batched_solve<float>((const float *)A, piv, maxm, batch, vb, db, (float *)b, s);
     } else if (!cfg && op == 0) {
-        // left-looking factorization; FP64 matrices too large for its
-        // accumulators (first in the order) by the persistent kernel
+        // left-looking factorization; matrices too large for its accumulators
+        // (first in the order) by the persistent kernel, beside the others on a
+        // stream of its own (one of 2000 rows takes 80 ms on one CU); the
+        // allocation-free call creates nothing and runs one after the other
         int nq = 0;
         while (nq < batch && ms[nq] > lu_std_max_m(f64)) ++nq;
+        SideStream fork(s);
         if (nq > 0) {
             LuQueue q{nq, dm, da, dp, dnb, dcounter};
             const int grid = std::min(nq, device_cus() * std::max(1, (int)(CU_LDS_BYTES / (budget + 1024))));
-            if (f64) e = launch_lu_queue<double>((double *)A, piv, q, budget, grid, tune.threads, info, s);
-            else e = launch_lu_queue<float>((float *)A, piv, q, budget, grid, tune.threads, info, s, op);
+            const hipStream_t sq = nq < batch && staging != MetaStaging::Fixed ? fork.fork() : s;
+            if (f64) e = launch_lu_queue<double>((double *)A, piv, q, budget, grid, tune.threads, info, sq);
+            else e = launch_lu_queue<float>((float *)A, piv, q, budget, grid, tune.threads, info, sq, op);
         }
         if (e == hipSuccess && nq < batch) {
             const LuBatch vl{0, dm + nq, da + nq, dp + nq, 0};
             if (f64) e = launch_lu_std<double>((double *)A, piv, vl, ms + nq, batch - nq, info, s);
             else e = launch_lu_std<float>((float *)A, piv, vl, ms + nq, batch - nq, info, s);
         }
+        const hipError_t ej = fork.join();
+        if (e == hipSuccess) e = ej;
     } else if (!per_class) {
         // one persistent launch for the whole batch, largest matrices first
         LuQueue q{batch, dm, da, dp, dnb, dcounter};

@@ -1,6 +1,7 @@
-"""Left-looking batched LU (stmg_batched_lu in FP64 and FP32) on matrices with
-NaN entries, against the persistent right-looking kernel (explicit launch
-parameters) on the same matrices (GPU)."""
+"""Left-looking LU (stmg_batched_lu in FP64 and FP32, patch systems) on special
+matrices and batches: NaN entries, against the persistent right-looking kernel
+(explicit launch parameters); tiny complex pivots; matrices beyond the
+left-looking kernel's limit beside others (GPU)."""
 import numpy as np
 import pytest
 
@@ -66,3 +67,33 @@ def test_small_complex_pivots(d, n, r, nu, tau):
     x = torch.zeros(ctx.N, dtype=torch.float32, device="cuda")
     ctx.vanka_smooth(0, b.to("cuda", torch.float32), x)
     assert bool(torch.isfinite(x).all()) and bool(x.any())
+
+
+@pytest.mark.parametrize("prec,big", [("f64", 1281), ("f32", 1857)])
+def test_oversized_beside_others(prec, big):
+    """Matrices above the left-looking limit run beside the rest of the batch:
+    each is factored as it is alone (bit for bit), with the fixed staging too,
+    and on a stream that still holds earlier work."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2602_13841_amd import stmg
+    dt = torch.float64 if prec == "f64" else torch.float32
+    rng = np.random.Generator(np.random.PCG64(84))
+    sizes = [40, big, 395, 600, 17]
+    mats = [rng.uniform(-1, 1, (m, m)) for m in sizes]
+    want = [factor(A, dt) for A in mats]
+    a_off = np.concatenate([[0], np.cumsum(np.square(sizes))[:-1]])
+    p_off = np.concatenate([[0], np.cumsum(sizes)[:-1]])
+    flat = torch.tensor(np.concatenate([A.ravel() for A in mats]), dtype=dt, device="cuda")
+    stream = torch.cuda.Stream()
+    for noalloc in (False, True):
+        piv = torch.full((sum(sizes),), -1, dtype=torch.int32, device="cuda")
+        torch.cuda.synchronize()
+        with torch.cuda.stream(stream):
+            F = torch.zeros_like(flat)
+            for _ in range(50):   # the matrices arrive with the last of these copies
+                F.copy_(flat)
+            stmg.batched_lu(F, a_off, sizes, piv, p_off, noalloc=noalloc)
+        F, piv = F.cpu().numpy(), piv.cpu().numpy()
+        for m, a, p, (G, q, _) in zip(sizes, a_off, p_off, want):
+            assert np.array_equal(F[a:a + m * m].reshape(m, m), G) and np.array_equal(piv[p:p + m], q)
