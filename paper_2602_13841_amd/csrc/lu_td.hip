@@ -47,6 +47,7 @@ __device__ __forceinline__ float fma_(float a, float b, float c) { return __buil
 __device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
 __device__ __forceinline__ float abs_(float x) { return __builtin_fabsf(x); }
 __device__ __forceinline__ double abs_(double x) { return __builtin_fabs(x); }
+template <typename T> __device__ __forceinline__ bool finite_(T x) { return abs_(x) < T(__builtin_inf()); }
 
 typedef float floatx4_t __attribute__((ext_vector_type(4)));
 typedef double doublex4_t __attribute__((ext_vector_type(4)));
@@ -443,6 +444,22 @@ __device__ __forceinline__ void lu_left(T *__restrict__ Ar, int m, int ld, int *
                     ub2[l16 * LDU + cw + q] = -y0[q];
                     ub2[(16 + l16) * LDU + cw + q] = -y1[q];
                 }
+                bool fin = true;
+#pragma unroll
+                for (int q = 0; q < CL; ++q) fin = fin && finite_(y0[q]) && finite_(y1[q]);
+                if (__any(!fin)) {
+                    // an infinity or NaN must not reach the rows above it (zero
+                    // times its value): plain substitution, one column per lane
+                    if (l16 < CL)
+#pragma unroll 1
+                        for (int i = 0; i < 32; ++i) {
+                            T v = -ub1[i * LDU + cw + l16];
+#pragma unroll 1
+                            for (int k = 0; k < i; ++k)
+                                v = fma_(-lkk[k * (TD_BW + 1) + i], ub2[k * LDU + cw + l16], v);
+                            ub2[i * LDU + cw + l16] = v;
+                        }
+                }
                 if (K + 1 < J) load_inverse(K + 1);
             } else if (wv < 4) {
 #pragma unroll
@@ -820,6 +837,26 @@ __device__ __forceinline__ void lu_left(T *__restrict__ Ar, int m, int ld, int *
                     if (wv == 0) {
                         acc_t dr = {0, 0, 0, 0}, di = {0, 0, 0, 0};
                         mm16<T, CX>(sI1, u0, dr, di);
+                        if constexpr (STD) {
+                            bool fin = true;
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) fin = fin && finite_(dr[i]);
+                            if (__any(!fin)) {
+                                // an infinity or NaN must not reach the rows above
+                                // it: by substitution, one column per lane
+#pragma unroll 1
+                                for (int i = 0; i < PW; ++i) {
+                                    const T *li = pan + pl[c0 + i] * LS;
+                                    T v = u0[i * TD_LS + l16];
+#pragma unroll 1
+                                    for (int k = 0; k < i; ++k) v = fma_(-li[k], u12[k * TD_LS + l16], v);
+                                    u12[i * TD_LS + l16] = v;
+                                }
+#pragma unroll
+                                for (int i = 0; i < 4; ++i)
+                                    dr[i] = V::row(g, i) < PW ? u12[V::row(g, i) * TD_LS + l16] : T(0);
+                            }
+                        }
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {
                             const int r = V::row(g, i), c = 16 * sj + l16;

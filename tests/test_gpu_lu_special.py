@@ -97,3 +97,31 @@ def test_oversized_beside_others(prec, big):
         F, piv = F.cpu().numpy(), piv.cpu().numpy()
         for m, a, p, (G, q, _) in zip(sizes, a_off, p_off, want):
             assert np.array_equal(F[a:a + m * m].reshape(m, m), G) and np.array_equal(piv[p:p + m], q)
+
+
+@pytest.mark.parametrize("m", [20, 33, 47, 64, 130, 300, 600, 700])
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+def test_nonfinite_entries_stay_where_elimination_puts_them(prec, m):
+    """NaN and infinities above the diagonal: the factors are not finite
+    exactly where the elimination l_ik u_kj reaches, and agree elsewhere with
+    the factors of the matrix without them.  (Dominant diagonal: no
+    interchanges.)"""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    dt, u = (torch.float64, 2.0 ** -53) if prec == "f64" else (torch.float32, 2.0 ** -24)
+    rng = np.random.Generator(np.random.PCG64(85))
+    A = rng.uniform(0.5, 1, (m, m)) + 4 * m * np.eye(m)
+    clean, _, _ = factor(A, dt)
+    for bad in ([(m - 3, m - 1)], [(m // 2, m - 2), (m - 2, m - 1)], [(1, m - 5), (2, m - 1)], [(m - 20, m - 4)]):
+        B, hit = A.copy(), np.zeros((m, m), dtype=bool)
+        for (i, j), v in zip(bad, (np.nan, -np.inf)):
+            B[i, j], hit[i, j] = v, True
+        for k in range(m):
+            hit[k + 1:, k] |= hit[k, k]
+            hit[k + 1:, k + 1:] |= hit[k + 1:, k, None] | hit[None, k, k + 1:]
+        for config in (None, (1, [16, 16, 16, 8, 4], 256)):
+            F, piv, info = factor(B, dt, config)
+            assert info == 0 and np.array_equal(piv, np.arange(m))
+            assert np.array_equal(~np.isfinite(F), hit), (bad, config)
+            ok = ~hit
+            assert np.all(np.abs(F[ok] - clean[ok]) <= 8 * m * u * np.abs(clean[ok]) + 8 * m * u)
