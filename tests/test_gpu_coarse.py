@@ -67,3 +67,37 @@ def test_coarse_inverse(d, n, k, mask):
             assert np.linalg.norm(x - ref) <= (tol + extra) * np.linalg.norm(ref)
         A[:N, :N] = s.jacobian(I.uniform(N, 32)).toarray()
         lu = sla.lu_factor(A)
+
+
+# both sides of the largest system that is inverted (6144 unknowns): below it
+# the tallest panels, above it the LU and its substitution
+@pytest.mark.parametrize("n,mask", [((23, 23), 0b1101), ((24, 23), None), ((24, 24), None), ((25, 23), 0b1101)],
+                         ids=["6005", "6263_border", "6531_border", "6519"])
+def test_coarse_large(n, mask):
+    """Against a sparse LU of the bordered Jacobian, with the bound of
+    test_coarse_inverse (condition number by the 1-norm estimator)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import scipy.sparse as sp
+    import scipy.sparse.linalg as spl
+    from paper_2602_13841_amd import stmg
+    prob = oracle.Problem(dim=2, n=n, r=1, k=0, nu=0.05, tau=0.1, dirichlet_mask=mask,
+                          vertices=I.perturbed_vertices(2, n, 0.2, 31))
+    slab = oracle.Slab(prob)
+    N = slab.N
+    U = I.uniform(N, 32)
+    A = slab.jacobian(U).tocsc()
+    if mask is None:
+        E = sp.csc_matrix(S.constant_pressure_vectors(slab))
+        A = sp.bmat([[A, E], [E.T, None]], format="csc")
+    lu = spl.splu(A)
+    inverse = spl.LinearOperator(A.shape, matvec=lu.solve, rmatvec=lambda v: lu.solve(v, trans="T"))
+    tol = 1e-13 * spl.norm(A, 1) * spl.onenormest(inverse)
+    ctx = stmg.Context(2, n, 1, 0, 0.05, 0.1, vertices=prob.vertices, dirichlet_faces=prob.dirichlet_mask,
+                       prec_mg=stmg.STMG_F64, max_levels=1, fgmres_maxit=1)
+    assert ctx.num_levels() == 1 and ctx.N == N
+    ctx.smoother_rebuild(torch.tensor(U, device="cuda"))
+    r = I.uniform(N, 33)
+    x = ctx.vcycle(torch.tensor(r, device="cuda")).cpu().numpy()
+    ref = lu.solve(np.concatenate([r, np.zeros(A.shape[0] - N)]))[:N]
+    assert np.linalg.norm(x - ref) <= tol * np.linalg.norm(ref)
