@@ -327,9 +327,10 @@ int stmg_march(stmg_ctx *ctx, int nslabs, const double *rhs, long long rhs_strid
  * A batch of dense matrices of mixed sizes, factored by LU with partial
  * pivoting (the Vanka patch factorization of Sec. "Inexact space-time Vanka
  * smoother" as a standalone batch).  FP64 and FP32 matrices up to 1280 / 1856
- * rows: one launch, one workgroup per matrix (largest first), left-looking
- * block columns in MFMA accumulators (v_mfma_f64_16x16x4f64,
- * v_mfma_f32_16x16x4f32).  Longer matrices and BF16 / FP16 operands: one
+ * rows: one launch for those above 512 rows, one for the rest, one workgroup
+ * per matrix (largest first), left-looking block columns in MFMA accumulators
+ * (v_mfma_f64_16x16x4f64, v_mfma_f32_16x16x4f32).  Longer matrices (beside the
+ * others, on a stream of the call's own) and BF16 / FP16 operands: one
  * persistent launch whose workgroups take the matrices, largest first, from a
  * device work queue (blocked right-looking panels in LDS, trailing updates on
  * MFMA; workgroups per CU and panel widths from a table written by the
@@ -363,7 +364,7 @@ int stmg_batched_lu_config(int prec, void *A, const long long *a_off, const int 
 
 /* For callers that cannot allocate device memory (code under stream
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
- * factorization as stmg_batched_lu, with the device staging of the
+ * factorization as stmg_batched_lu, with all its launches on `stream` and the device staging of the
  * per-matrix sizes and offsets (32 bytes per matrix) in a fixed library
  * array of STMG_NOALLOC_MAX_BATCH entries per device (2 MiB, held by every
  * device the library runs on until the process ends) instead of a per-call

@@ -1440,17 +1440,16 @@ template <int R, int NQ, Mode MODE> struct VolLds {
     __host__ __device__ static constexpr int ys(int nt) { return 3 * N1 * px(nt); }
     __host__ __device__ static constexpr int yp(int nt) { return ys(nt) + N1 * ps(nt); }
     __host__ __device__ static constexpr int op(int nt) { return 3 * N1 * px(nt); }
-    // threads: one per item of the x stage, ALLC at least four wavefronts
+    // threads: one per item of the x stage; ALLC: two halves of two wavefronts,
+    // each with half of the points of every row
     static constexpr bool ALLC = R == 3;
-    static_assert(!ALLC || MAX_NT * NR <= 256, "one item per thread");
-    __host__ __device__ static constexpr int halves(int nt) { return nt * NR <= 128 ? 2 : 1; }
     __host__ __device__ static constexpr int threads(int nt)
     {
         return ALLC ? 256 : al64(3 * nt * NR);
     }
     __host__ __device__ static constexpr int ry(int nt)
     {
-        const int z = zp(nt) + nt * NQ * RP2, m = ALLC ? halves(nt) * N1 * px(nt) : 0;
+        const int z = zp(nt) + nt * NQ * RP2, m = ALLC ? 2 * N1 * px(nt) : 0;
         return RZ + al4(z > m ? z : m);
     }
     __host__ __device__ static constexpr int words(int nt)
@@ -1716,10 +1715,9 @@ __device__ __forceinline__ void vol_body(const CellArgs<T> &A, const int cell, c
     __syncthreads();
     // ---- x, point physics, x^T: item (time node, row) or (time node, component, row) ----
     if constexpr (LY::ALLC) {
-        // two halves of the workgroup, each with half of the points of every row, if
-        // that is one item per thread
-        const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nh = LY::halves(nt);
-        const int half = nh == 2 ? wave >> 1 : 0, q0 = half ? (NQ + 1) / 2 : 0, q1 = nh == 2 && !half ? (NQ + 1) / 2 : NQ;
+        static_assert(nt * NR <= 128, "one item per thread of a half");
+        const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), half = wave >> 1;
+        const int q0 = half ? (NQ + 1) / 2 : 0, q1 = half ? NQ : (NQ + 1) / 2;
         const int it0 = tid - 128 * half, a0 = it0 / NR, row = it0 - a0 * NR;
         const bool act = a0 < nt;
         const int a = act ? a0 : 0;
@@ -1847,10 +1845,8 @@ __device__ __forceinline__ void vol_body(const CellArgs<T> &A, const int cell, c
             for (int i = 0; i < RP1; ++i) put(oq + i * PX, rp[i]);
         };
         if (act && half == 0) store(std::false_type{});
-        if (nh == 2) {
-            __syncthreads();
-            if (act && half == 1) store(std::true_type{});
-        }
+        __syncthreads();
+        if (act && half == 1) store(std::true_type{});
     } else {
         const int f = tid / NR, row = tid - f * NR;
         const bool act = f < 3 * nt;
@@ -2972,11 +2968,14 @@ static hipError_t launch_vol_fused(const CellArgs<T> &a, int nvec, hipStream_t s
 //                  (mapped: registers)   r = 2, n_q = 4: 1.08, 1.11; 1.19, 1.30
 //                  r = 3, n_q = 7: 1.24, 1.02; 1.23, 0.90   n_q = 5: 1.08, 1.13; 0.96, 1.08
 //   FP32 Jacobian  r = 1: 1.01, 1.17; 1.26, 1.14   r = 2, n_q = 5: 0.92, 1.14; 0.97, 0.94
+//                  (n_q = 4, k = 2 at 16^3: 0.89)
 //                  r = 3, n_q = 7: 1.07, 0.87; 1.16, 0.88   n_q = 5: 0.68 .. 0.77
 //   residual       r = 1: 1.30, 1.35; 1.29, 1.35   r = 2: 1.08 .. 1.30
 //                  r = 3, n_q = 7: 1.27, 0.96; 1.34, 1.09   n_q = 5: 0.90 .. 1.02
 // One time node leaves most of a workgroup idle (k = 0: 0.46 .. 1.05), with four
-// one workgroup fills a CU's LDS (k = 3, r = 3: 0.51 .. 0.88).
+// one workgroup fills a CU's LDS (k = 3, r = 3: 0.51 .. 0.88).  r = 3, n_q = 5 is left
+// out as a whole: what the FP64 Jacobian gains on affine cells, the mapped ones,
+// the residual and FP32 lose.
 template <int R, int NQ, int NT, typename T, Mode MODE, bool MAPPED> constexpr bool vol_takes()
 {
     if (NT != 2 && NT != 3) return false;
@@ -3137,11 +3136,12 @@ hipError_t launch_face_op(Mode mode, int dim, int r, int nq, const CellArgs<T> &
 }
 
 // whether the 3D Jacobian runs its boundary faces in the volume launch: in
-// FP32 only.  Measured on one MI355X, one Jacobian application (separate
-// launches vs one launch): FP64, 16^3 cells, r = 2, k = 2: 79 vs 86 us; 24 x 20 x
-// 28 mapped, r = 3, k = 1: 553 vs 549; FP32, 16^3, r = 2, k = 2: the faces
-// alone take 21 us after the volume pass, one launch takes 60 in all.
-// STMG_JAC_FUSED=0/1 overrides the choice (for measurement).
+// FP32 only (16^3 cells, r = 2, k = 2: the faces alone take 21 us after the volume
+// pass, one launch takes 60 in all).  In FP64 a launch of both was no faster
+// (r = 2, k = 2: 86 us against 79 in two launches; 24 x 20 x 28 mapped cells,
+// r = 3, k = 1: 549 against 553), so vol_fused_kernel is built for FP32 only.
+// STMG_JAC_FUSED=0/1 overrides the choice (for measurement); in FP64, 1 means the
+// thread-per-point volume pass with the faces (jac_fused_kernel).
 bool jac_fuse_faces(int r, int nq, bool f64)
 {
     static const int env = [] {

@@ -232,7 +232,7 @@ int batched_lu_run(int prec, void *A, const long long *a_off, const int *m_of, i
             else e = launch_lu_queue<float>((float *)A, piv, q, budget, grid, tune.threads, info, sq, op);
         }
         if (e == hipSuccess && nq < batch) {
-            const LuBatch vl{0, dm + nq, da + nq, dp + nq, 0};
+            const LuBatch vl{0, dm + nq, da + nq, dp + nq};
             if (f64) e = launch_lu_std<double>((double *)A, piv, vl, ms + nq, batch - nq, info, s);
             else e = launch_lu_std<float>((float *)A, piv, vl, ms + nq, batch - nq, info, s);
         }

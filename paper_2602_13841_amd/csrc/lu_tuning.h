@@ -2,7 +2,9 @@
 // precision: workgroups per CU (which sets the LDS budget of the launch) and
 // the panel width per size class.  Written by paper_2602_13841_amd/tune_lu.py
 // (2026-12-03, AMD Radeon Graphics gfx950:sramecc+:xnack-) from the timings of the 4096-matrix mixed patch batch
-// (sizes 85 ... 1185) noted beside each row.
+// (sizes 85 ... 1185) noted beside each row.  Without explicit launch
+// parameters the f64 and f32 rows serve only matrices above the left-looking
+// kernel's limit (1280 and 1856 rows).
 #pragma once
 
 namespace stmg {

@@ -74,8 +74,6 @@ template <typename T, typename TP, typename TF = TP> struct SolveTdArgs {
     T omega;
 };
 
-// a batch of LU factorizations: uniform size m, or per-matrix sizes and
-// offsets (elements of A, entries of the pivot array)
 // row stride of the time-decoupled patch systems (elements): above 128
 // unknowns every row starts on a 32-element boundary (128 bytes in FP32, 64 in
 // the BF16 copy), so the 32-column blocks the substitutions read cover whole
@@ -84,12 +82,13 @@ template <typename T, typename TP, typename TF = TP> struct SolveTdArgs {
 // more registers than it saves in bytes)
 constexpr int td_ld(int ms) { return ms > 128 ? (ms + 31) & ~31 : ms; }
 
+// a batch of LU factorizations: uniform size m, or per-matrix sizes and
+// offsets (elements of A, entries of the pivot array); row stride = size
 struct LuBatch {
     int uniform_m;
     const int *m_of;
     const long long *a_off;
     const long long *p_off;
-    int uniform_ld;   // row stride of every matrix (0: its size m)
 };
 
 // a batch of LU factorizations taken from a device work queue by a fixed grid
@@ -127,8 +126,8 @@ hipError_t launch_solve(int dim, int r, const SolveArgs<T, TP> &a, int ncell, in
 template <typename TE, typename TP>
 hipError_t launch_patch_td(int dim, int r, const PatchTdArgs<TE, TP> &a, int ncell, hipStream_t s);
 // Time-decoupled patch systems (lu_td.hip): LU with partial pivoting of a batch
-// of m x m matrices (17 <= m <= 512, row stride ld; cplx: planar, real plane
-// then imaginary plane), rows in place: position p of the permuted matrix is
+// of m x m matrices (17 <= m <= 512, FP64 complex <= 423 by LDS; row stride ld;
+// cplx: planar, real plane then imaginary plane), rows in place: position p of the permuted matrix is
 // stored row perm[p].  Diagonal blocks of 32 hold the inverses of their
 // triangles (strict lower part: L^{-1}, upper triangle: U^{-1}).
 template <typename T>

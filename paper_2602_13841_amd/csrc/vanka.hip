@@ -1359,10 +1359,9 @@ __global__ void __launch_bounds__(LU_THREADS) lu_kernel(T *__restrict__ Aall, in
     extern __shared__ unsigned char lds_raw[];
     const int bid = blockIdx.x;
     const int m = B.m_of ? B.m_of[bid] : B.uniform_m;
-    const int ld = B.uniform_ld > 0 ? B.uniform_ld : m;   // row stride
-    T *A = Aall + (B.a_off ? B.a_off[bid] : (long long)bid * m * ld);
+    T *A = Aall + (B.a_off ? B.a_off[bid] : (long long)bid * m * m);
     int *piv = pivall + (B.p_off ? B.p_off[bid] : (long long)bid * m);
-    lu_one<T, NB, OP>(A, m, ld, piv, info, lds_raw);
+    lu_one<T, NB, OP>(A, m, m, piv, info, lds_raw);
 }
 
 // Persistent batched LU of matrices of mixed sizes: a fixed grid of

@@ -1,5 +1,9 @@
 """Tuner of the persistent batched LU (stmg_batched_lu).
 
+Calls without launch parameters use it for BF16 / FP16 operands and for
+matrices above 1280 (FP64) or 1856 rows (FP32); shorter ones go to the
+left-looking kernel, which has no parameters to tune.
+
 For each precision it times, on the GPU, factorizations of a seeded batch of
 dense matrices with the sizes of the mixed Vanka patch batch (3D patches of
 r in {1, 2, 3}, k in {0, 1, 2}: m = (k+1)(3(r+2)^3 + C(r+3, 3)), 85 ... 1185):
@@ -135,7 +139,9 @@ def write_table(result, path=os.path.join(HERE, "csrc", "lu_tuning.h")):
 // precision: workgroups per CU (which sets the LDS budget of the launch) and
 // the panel width per size class.  Written by paper_2602_13841_amd/tune_lu.py
 // ({stamp}, {dev}) from the timings of the 4096-matrix mixed patch batch
-// (sizes 85 ... 1185) noted beside each row.
+// (sizes 85 ... 1185) noted beside each row.  Without explicit launch
+// parameters the f64 and f32 rows serve only matrices above the left-looking
+// kernel's limit (1280 and 1856 rows).
 #pragma once
 
 namespace stmg {{
