@@ -364,7 +364,7 @@ int stmg_batched_lu_config(int prec, void *A, const long long *a_off, const int 
 
 /* For callers that cannot allocate device memory (code under stream
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
- * factorization as stmg_batched_lu, with all its launches on `stream` and the device staging of the
+ * factorization as stmg_batched_lu, with the device staging of the
  * per-matrix sizes and offsets (32 bytes per matrix) in a fixed library
  * array of STMG_NOALLOC_MAX_BATCH entries per device (2 MiB, held by every
  * device the library runs on until the process ends) instead of a per-call
