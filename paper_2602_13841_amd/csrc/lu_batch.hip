@@ -210,6 +210,7 @@ int batched_lu_run(int prec, void *A, const long long *a_off, const int *m_of, i
         return STMG_EHIP;
     }
     LuBatch vb{maxm, dm, da, dp};
+    SideStream fork(s);   // (destroyed after the synchronization below)
     hipError_t e = hipSuccess;
     if (solve) {
         if (prec == STMG_F64)
@@ -223,7 +224,6 @@ int batched_lu_run(int prec, void *A, const long long *a_off, const int *m_of, i
         // of 395 rows, FP64: 83.6 ms, 86.6 one after the other)
         int nq = 0;
         while (nq < batch && ms[nq] > lu_std_max_m(f64)) ++nq;
-        SideStream fork(s);
         if (nq > 0) {
             LuQueue q{nq, dm, da, dp, dnb, dcounter};
             const int grid = std::min(nq, device_cus() * std::max(1, (int)(CU_LDS_BYTES / (budget + 1024))));
